@@ -2095,7 +2095,14 @@ k_grid_interp(const LDesc *__restrict__ descs, const IoEntry *__restrict__, cons
 
 // ------------------------------------------------------------------ Lagrange levels
 constexpr int kMaxR1 = 8;
-constexpr int kAnterpChunk = 64;
+
+// Orders a wave's LDS writes before its own later reads (and its reads before later writes): a wave's LDS
+// operations complete in order, so only the compiler has to keep them in place.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // One-dimensional Lagrange polynomials on the Chebyshev nodes at t (denominators precomputed).
 __device__ __forceinline__ void lagrange_1d(float t, int r1, const float *nodes, const float *inv_den, float *ell) {
@@ -2126,111 +2133,166 @@ __device__ __forceinline__ void lagrange_1d_deriv(float t, int r1, const float *
 // With DL (the normal derivative at the sources) the weight of node (a, b, c) is n_j . grad_y of its polynomial:
 // (2 / d_l) (n_x l'_a l_b l_c + n_y l_a l'_b l_c + n_z l_a l_b l'_c); the staged derivative tables carry the
 // factors (2 / d_l) n.  Item (desc, source box).
+//
+// The sum over the points is a matrix product: rows (a, b), columns (c, part), one step of
+// v_mfma_f32_16x16x4f32 per four points and 16 rows, with l_a l_b as the A and l_c u as the B operand (DL: two
+// steps, A = l'_a l_b + l_a l'_b with B = l_c u, then A = l_a l_b with B = l'_c u).  Each wave takes every
+// nw-th 64 points of the box: a lane evaluates one point's bases into the wave's own part of LDS, which the
+// wave then reads as operands (rows of 2 r1 floats: the four points of a step lie in distinct banks), without
+// block barriers; the waves' tiles are added in wave order at the end.  MFMA issue bounds it (96 cycles per
+// four points at r1 = 6 against about 50 for its LDS reads).  Sphere of 1M points, r1 = 6, levels 2 to 6: 974,
+// 282, 96, 72, 82 us with one 256-thread block per box and a thread per node (three LDS reads and four VALU
+// operations per point and node) -> 141, 46, 39, 38, 42 us.
+template <bool DL>
+__host__ __device__ constexpr int anterp_floats(int r1) { return (DL ? 8 : 4) * r1; }   // LDS floats per point
+
 template <bool DL, int R1>
-__device__ __forceinline__ void lag_anterp_r1(const LDesc &d, const int4 wk, float (*ell)[(DL ? 6 : 3) * kMaxR1],
-                                              float2 *us, float *nodes, float *den) {
+__device__ __forceinline__ void lag_anterp_r1(const LDesc &d, const int4 wk, float *sm) {
+    constexpr int R2 = R1 * R1, NT = (R2 + 15) / 16, W = 2 * R1, PT = anterp_floats<DL>(R1);
     const int b = wk.y;
-    const int tid = threadIdx.x;
-    constexpr int r1 = R1, r = R1 * R1 * R1;
-    const int rp = d.rp;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nw = blockDim.x >> 6;
     const double two_over_dl = d.two_over_dl;
-    if (tid < r1) {
-        nodes[tid] = d.lnodes[tid];
-        den[tid] = d.lden[tid];
-    }
-    constexpr int kOut = (r + kThreads - 1) / kThreads;
-    float2 acc[kOut];
-    int ia[kOut], ib[kOut], ic[kOut];
+    float *my = sm + wv * 64 * PT;     // per point: l_x, l_y | l_z u (re, im) | DL: l'_x, l'_y | l'_z u
+    const int li = lane & 15, lk = lane >> 4;
+    int ia[NT], ib[NT];
+    floatx4 acc[NT];
 #pragma unroll
-    for (int o = 0; o < kOut; ++o) {
-        const int i = tid + o * kThreads;
-        acc[o] = make_float2(0.f, 0.f);
-        const int ii = i < r ? i : 0;
-        ia[o] = ii / (r1 * r1);
-        ib[o] = (ii / r1) % r1;
-        ic[o] = ii % r1;
+    for (int t = 0; t < NT; ++t) {
+        const int row = min(t * 16 + li, R2 - 1);
+        ia[t] = row / R1;
+        ib[t] = R1 + row % R1;
+        acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
-    constexpr int nout = kOut;
+    float nodes[R1], den[R1];
+#pragma unroll
+    for (int a = 0; a < R1; ++a) {
+        nodes[a] = d.lnodes[a];
+        den[a] = d.lden[a];
+    }
     const double cx = d.sctr[3 * b], cy = d.sctr[3 * b + 1], cz = d.sctr[3 * b + 2];
     const int i0 = d.sstart[b], i1 = d.sstart[b + 1];
-    for (int s0 = i0; s0 < i1; s0 += kAnterpChunk) {
-        const int cnt = min(kAnterpChunk, i1 - s0);
-        __syncthreads();
-        if (tid < cnt) {
-            const int j = s0 + tid;
-            lagrange_1d((float)((d.sxs[j] - cx) * two_over_dl), r1, nodes, den, &ell[tid][0]);
-            lagrange_1d((float)((d.sys[j] - cy) * two_over_dl), r1, nodes, den, &ell[tid][r1]);
-            lagrange_1d((float)((d.szs[j] - cz) * two_over_dl), r1, nodes, den, &ell[tid][2 * r1]);
+    for (int s0 = i0 + wv * 64; s0 < i1; s0 += nw * 64) {
+        const int cnt = min(64, i1 - s0);
+        {
+            // lanes past the last point repeat it with u = 0
+            const int j = min(s0 + lane, i1 - 1);
+            float2 u = d.u[j];
+            if (lane >= cnt) u = make_float2(0.f, 0.f);
+            const float tx = (float)((d.sxs[j] - cx) * two_over_dl), ty = (float)((d.sys[j] - cy) * two_over_dl);
+            const float tz = (float)((d.szs[j] - cz) * two_over_dl);
+            float *q = my + lane * PT;
+            float e[R1];
+            lagrange_1d(tx, R1, nodes, den, e);
+#pragma unroll
+            for (int a = 0; a < R1; ++a) q[a] = e[a];
+            lagrange_1d(ty, R1, nodes, den, e);
+#pragma unroll
+            for (int a = 0; a < R1; ++a) q[R1 + a] = e[a];
+            lagrange_1d(tz, R1, nodes, den, e);
+#pragma unroll
+            for (int a = 0; a < R1; ++a) {
+                q[W + 2 * a] = e[a] * u.x;
+                q[W + 2 * a + 1] = e[a] * u.y;
+            }
             if (DL) {
                 const float4 n = d.sn[j];
                 const float f = (float)two_over_dl;
-                float *g = &ell[tid][3 * r1];
-                lagrange_1d_deriv((float)((d.sxs[j] - cx) * two_over_dl), r1, nodes, den, g);
-                lagrange_1d_deriv((float)((d.sys[j] - cy) * two_over_dl), r1, nodes, den, g + r1);
-                lagrange_1d_deriv((float)((d.szs[j] - cz) * two_over_dl), r1, nodes, den, g + 2 * r1);
-                for (int a = 0; a < r1; ++a) {
-                    g[a] *= f * n.x;
-                    g[r1 + a] *= f * n.y;
-                    g[2 * r1 + a] *= f * n.z;
+                lagrange_1d_deriv(tx, R1, nodes, den, e);
+#pragma unroll
+                for (int a = 0; a < R1; ++a) q[2 * W + a] = e[a] * (f * n.x);
+                lagrange_1d_deriv(ty, R1, nodes, den, e);
+#pragma unroll
+                for (int a = 0; a < R1; ++a) q[2 * W + R1 + a] = e[a] * (f * n.y);
+                lagrange_1d_deriv(tz, R1, nodes, den, e);
+#pragma unroll
+                for (int a = 0; a < R1; ++a) {
+                    q[3 * W + 2 * a] = e[a] * (f * n.z) * u.x;
+                    q[3 * W + 2 * a + 1] = e[a] * (f * n.z) * u.y;
                 }
             }
-            us[tid] = d.u[j];
         }
-        __syncthreads();
-#pragma unroll 4
-        for (int jj = 0; jj < cnt; ++jj) {
-            const float2 uu = us[jj];
+        wave_lds_fence();
+        // two steps per round, their operands loaded before the products (points past the last have u = 0)
+        for (int p0 = 0; p0 < cnt; p0 += 8) {
+            float a[2][NT], g[2][NT], bv[2], bg[2];
 #pragma unroll
-            for (int o = 0; o < kOut; ++o) {
-                if (o < nout) {
-                    const float *e = ell[jj];
-                    float w;
+            for (int h = 0; h < 2; ++h) {
+                const float *q = my + (p0 + 4 * h + lk) * PT;
+                bv[h] = li < W ? q[W + li] : 0.f;
+                bg[h] = DL && li < W ? q[3 * W + li] : 0.f;
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    const float ex = q[ia[t]], ey = q[ib[t]];
+                    a[h][t] = ex * ey;
+                    if (DL) g[h][t] = fmaf(q[2 * W + ia[t]], ey, ex * q[2 * W + ib[t]]);
+                }
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
                     if (DL) {
-                        const float ex = e[ia[o]], ey = e[r1 + ib[o]], ez = e[2 * r1 + ic[o]];
-                        w = fmaf(e[3 * r1 + ia[o]], ey * ez, fmaf(ex, e[4 * r1 + ib[o]] * ez, ex * ey * e[5 * r1 + ic[o]]));
+                        acc[t] = mfma16(g[h][t], bv[h], acc[t]);
+                        acc[t] = mfma16(a[h][t], bg[h], acc[t]);
                     } else {
-                        w = e[ia[o]] * e[r1 + ib[o]] * e[2 * r1 + ic[o]];
+                        acc[t] = mfma16(a[h][t], bv[h], acc[t]);
                     }
-                    acc[o].x = fmaf(w, uu.x, acc[o].x);
-                    acc[o].y = fmaf(w, uu.y, acc[o].y);
                 }
+        }
+        wave_lds_fence();
+    }
+    // entry (row, j) of the product is float row W + j of u~: lane (j, g) holds rows 4 g + v of each tile
+    float *ut = reinterpret_cast<float *>(d.ut2 + (int64_t)b * d.rp);
+    if (nw == 1) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = t * 16 + 4 * lk + v;
+                if (li < W && row < R2) ut[row * W + li] = acc[t][v];
             }
+    } else {
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = t * 16 + 4 * lk + v;
+                if (li < W && row < R2) sm[(wv * R2 + row) * W + li] = acc[t][v];
+            }
+        __syncthreads();
+        for (int e = tid; e < R2 * W; e += blockDim.x) {
+            float a = 0.f;
+            for (int q = 0; q < nw; ++q) a += sm[q * R2 * W + e];
+            ut[e] = a;
         }
     }
-    float2 *ut = d.ut2 + (int64_t)b * rp;
-#pragma unroll
-    for (int o = 0; o < kOut; ++o) {
-        const int i = tid + o * kThreads;
-        if (o < nout && i < rp) ut[i] = (i < r) ? acc[o] : make_float2(0.f, 0.f);
-    }
-    for (int i = r + tid; i < rp; i += kThreads) ut[i] = make_float2(0.f, 0.f);
+    for (int e = R2 * W + tid; e < 2 * d.rp; e += blockDim.x) ut[e] = 0.f;
 }
 
 template <bool DL>
 __device__ __forceinline__ void lag_anterp_body(const LDesc &d, const int4 wk) {
-    __shared__ float ell[kAnterpChunk][(DL ? 6 : 3) * kMaxR1];
-    __shared__ float2 us[kAnterpChunk];
-    __shared__ float nodes[kMaxR1], den[kMaxR1];
-    // the node count as a compile-time constant: the basis loops unroll and the outputs per thread are fixed
+    extern __shared__ float anterp_sm[];   // [waves][64][anterp_floats], then the waves' tiles
+    // the node count as a compile-time constant: the basis loops unroll and the tiles per wave are fixed
     switch (d.r1) {
-        case 1: lag_anterp_r1<DL, 1>(d, wk, ell, us, nodes, den); break;
-        case 2: lag_anterp_r1<DL, 2>(d, wk, ell, us, nodes, den); break;
-        case 3: lag_anterp_r1<DL, 3>(d, wk, ell, us, nodes, den); break;
-        case 4: lag_anterp_r1<DL, 4>(d, wk, ell, us, nodes, den); break;
-        case 5: lag_anterp_r1<DL, 5>(d, wk, ell, us, nodes, den); break;
-        case 6: lag_anterp_r1<DL, 6>(d, wk, ell, us, nodes, den); break;
-        case 7: lag_anterp_r1<DL, 7>(d, wk, ell, us, nodes, den); break;
-        default: lag_anterp_r1<DL, 8>(d, wk, ell, us, nodes, den); break;
+        case 1: lag_anterp_r1<DL, 1>(d, wk, anterp_sm); break;
+        case 2: lag_anterp_r1<DL, 2>(d, wk, anterp_sm); break;
+        case 3: lag_anterp_r1<DL, 3>(d, wk, anterp_sm); break;
+        case 4: lag_anterp_r1<DL, 4>(d, wk, anterp_sm); break;
+        case 5: lag_anterp_r1<DL, 5>(d, wk, anterp_sm); break;
+        case 6: lag_anterp_r1<DL, 6>(d, wk, anterp_sm); break;
+        case 7: lag_anterp_r1<DL, 7>(d, wk, anterp_sm); break;
+        default: lag_anterp_r1<DL, 8>(d, wk, anterp_sm); break;
     }
 }
 
-__global__ void __launch_bounds__(kThreads)
+__global__ void __launch_bounds__(1024)
 k_lag_anterp(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const int4 *__restrict__ work) {
     const int4 wk = work[blockIdx.x];
     lag_anterp_body<false>(descs[wk.x], wk);
 }
 
-__global__ void __launch_bounds__(kThreads)
+__global__ void __launch_bounds__(512)
 k_lag_anterp_dl(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const int4 *__restrict__ work) {
     const int4 wk = work[blockIdx.x];
     lag_anterp_body<true>(descs[wk.x], wk);
@@ -2635,7 +2697,7 @@ __device__ __forceinline__ void lag_interp_r1(const LDesc &d, const int4 wk, flo
     }
     __syncthreads();
     const double cx = d.tctr[3 * t], cy = d.tctr[3 * t + 1], cz = d.tctr[3 * t + 2];
-    for (int i = d.tstart[t] + tid; i < d.tstart[t + 1]; i += kThreads) {
+    for (int i = wk.z + tid; i < wk.w; i += kThreads) {
         float lx[R1], ly[R1], lz[R1];
         const float tx = (float)((d.txs[i] - cx) * two_over_dl), ty = (float)((d.tys[i] - cy) * two_over_dl);
         const float tz = (float)((d.tzs[i] - cz) * two_over_dl);
@@ -2725,7 +2787,9 @@ __device__ __forceinline__ void lag_interp_body(const LDesc &d, const int4 wk) {
 }
 
 // v_i += L_X^T v~_t (or its normal derivative at x_i, k_lag_interp_dn) with v~_t = sum_{e in far(t)} Z_e (fixed
-// order), t = 2 (x - c_t) / d_l.  Item (desc, target box).
+// order), t = 2 (x - c_t) / d_l.  Item (desc, target box, first point, end): boxes with many points are cut into
+// ranges (plan.hip, kInterpBlocks), each forming v~_t anew (sphere of 1M points, r1 = 6: level 2 443 -> 41 us,
+// level 3 135 -> 51).
 __global__ void __launch_bounds__(kThreads)
 k_lag_interp(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const int4 *__restrict__ work) {
     const int4 wk = work[blockIdx.x];
@@ -3676,8 +3740,9 @@ KernelFn kernel_of(const Stage &S, int &threads) {
             if (S.a == 2) return S.b ? k_pw_backward_rings<2, 2, true> : k_pw_backward_rings<2, 2, false>;
             return S.b ? k_pw_backward_rings<1, 4, true> : k_pw_backward_rings<1, 4, false>;
         case K_BSUM: return k_sum_parts;
-        case K_ANTERP: return k_lag_anterp;
-        case K_ANTERP_DL: return k_lag_anterp_dl;
+        // a = waves per block
+        case K_ANTERP: threads = 64 * std::max(1, S.a); return k_lag_anterp;
+        case K_ANTERP_DL: threads = 64 * std::max(1, S.a); return k_lag_anterp_dl;
         case K_DIRSCALE: return k_dir_scale;
         case K_DNCOMBINE: return k_dn_combine;
         case K_DLCOMBINE: return k_dl_combine;

@@ -2050,6 +2050,21 @@ static void pick_pair_tile(int64_t npair, int ppt_max, int &bs, int &ppt) {
     }
 }
 
+// Blocks of a Lagrange level's interpolation that boxes with many points are cut for (four 256-thread blocks per
+// CU; every block sums v~ of its box anew).
+constexpr double kInterpBlocks = 1024.0;
+
+// Waves per block of the anterpolation for boxes of avg points on average: one wave serves a leaf box, and boxes
+// of coarse levels (thousands of points in a few tens of boxes) take sixteen, eight for the double layer, whose
+// points stage twice the LDS.
+int anterp_waves(double avg, bool dl) { return avg <= 192.0 ? 1 : (avg <= 1024.0 ? 4 : (dl ? 8 : 16)); }
+
+// Its dynamic LDS: 64 points per wave (the waves' tiles, r1^2 x 2 r1 floats each, fit in the same space), rounded
+// up to 6 or 8 nodes per axis so that a batch's instances of different r1 share launches.
+size_t anterp_shmem(int nw, int r1, bool dl) {
+    return (size_t)nw * 64 * (dl ? 8 : 4) * (r1 <= 6 ? 6 : 8) * sizeof(float);
+}
+
 // The transfer stage of a Gegenbauer level: class tables in LDS where boxes have many direction pairs
 // (measured faster from n_pair ~ 4096 on), one target per block otherwise.
 // Gradient plans: v~ of the three components of a Gegenbauer level (k_dir_scale), over the level's target boxes.
@@ -2331,8 +2346,15 @@ void plan_stages(Plan &P, const Tune &tu, hipStream_t st, Scratch *keep) {
                         if (g < LV.ngrp) mf.push_back(make_int4(l, g, 0, 0));
                     }
             }
-            for (int32_t t : LV.h_tgt) ip.push_back(make_int4(l, t, 0, 0));
-            LV.stages.push_back(make_stage(P.dl ? K_ANTERP_DL : K_ANTERP, 0, 0, s1, l, 0, std::move(an), st, SC));
+            // target boxes with many points in ranges of whole 256-point steps, about kInterpBlocks blocks in all
+            const double per_blk = LV.pts_tgt / kInterpBlocks;
+            const int32_t range = kThreads * std::max(1, (int)std::ceil(per_blk / kThreads));
+            for (int32_t t : LV.h_tgt)
+                for (int32_t i = sx[t]; i < sx[t + 1]; i += range)
+                    ip.push_back(make_int4(l, t, i, std::min(i + range, sx[t + 1])));
+            const int nwa = anterp_waves(LV.pts_src / std::max<double>(1.0, (double)LV.h_fwd.size()), P.dl);
+            LV.stages.push_back(make_stage(P.dl ? K_ANTERP_DL : K_ANTERP, nwa, 0, s1, l, anterp_shmem(nwa, LV.r1, P.dl),
+                                           std::move(an), st, SC));
             if (LV.aca)
                 LV.stages.push_back(make_stage(K_ACA, std::min(4, LV.rp / 32), 0, s2, l, (size_t)LV.rp * 32 * 4,
                                                std::move(mf), st, SC));

@@ -1,0 +1,51 @@
+"""Lagrange levels at the edges of their kernels' tiles: every node count per axis (16-row MFMA tiles of r1^2 rows,
+2 r1 columns), boxes of a few points and of thousands (one to sixteen waves per box in the anterpolation, several
+point ranges per box in the interpolation), against the oracle with identical parameters (FP32_RTOL) and bitwise
+repeatable."""
+import numpy as np
+import pytest
+
+import ffm_workloads as W
+from gpu_common import FP32_RTOL, gpu_apply, gpu_plan, oracle_like, rel
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kernel,r1", [(0, r1) for r1 in range(1, 9)] + [(1, 3), (1, 6)])
+def test_node_counts(orc, kernel, r1):
+    rng = np.random.default_rng(r1)
+    X = W.sphere_points(3001, rng)
+    wu = ((rng.standard_normal(3001) + 1j * rng.standard_normal(3001)) / 3001).astype(np.complex64)
+    k = 2.0 if kernel else 0.0
+    gp = gpu_plan(X, X, kernel, k, 1e-3, n_leaf=40, r1_override=r1, aca="off")
+    st = gp.stats()
+    assert any(o == r1 for o in st["order"][1:st["leaf"] + 1])
+    v = gpu_apply(gp, wu)
+    vo = oracle_like(orc, gp, X, X, kernel, k, 1e-3, n_leaf=40, r1=r1).apply(wu)
+    print("kernel %d r1 %d: vs oracle %.3e" % (kernel, r1, rel(v, vo)))
+    assert rel(v, vo) < FP32_RTOL
+    assert np.array_equal(v, gpu_apply(gp, wu))
+
+
+@pytest.mark.parametrize("n", [11000, 57001, 90000])     # 196, 1018 and 1607 points per box of level 2
+@pytest.mark.parametrize("dl", [False, True])
+def test_points_per_box(orc, n, dl):
+    import torch
+    import paper_1909_05600_amd as ffm
+    rng = np.random.default_rng(n)
+    Y = W.sphere_points(n, rng)
+    X = W.sphere_points(700, rng) * 0.98
+    wu = ((rng.standard_normal(n) + 1j * rng.standard_normal(n)) / n).astype(np.complex64)
+    kernel = 4 if dl else 0
+    kw = {"max_level": 3}
+    nrm = {"source_normals": torch.from_numpy(Y).cuda()} if dl else {}
+    gp = ffm.Plan(torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda(), kernel, 0.0, 1e-3, **kw, **nrm)
+    v = gpu_apply(gp, wu)
+    vo = oracle_like(orc, gp, X, Y, kernel, 0.0, 1e-3, **kw, **({"source_normals": Y} if dl else {})).apply(wu)
+    print("n %d dl %d: vs oracle %.3e" % (n, dl, rel(v, vo)))
+    assert rel(v, vo) < FP32_RTOL
+    # the roles exchanged: many targets per box
+    if not dl:
+        gt = gpu_plan(Y, X, 0, 0.0, 1e-3, **kw)
+        w2 = wu[:700]
+        assert rel(gpu_apply(gt, w2), oracle_like(orc, gt, Y, X, 0, 0.0, 1e-3, **kw).apply(w2)) < FP32_RTOL
