@@ -609,7 +609,7 @@ def aca_study(n, reps=5):
             v = p.apply(wu)
             t_apply = _sync_time(lambda: p.apply(wu, out=v), reps)
             lt = p.launch_timing()
-            tr = sum(r["ms"] for r in lt if r["kernel"] in ("k_lag_mfma", "k_lag_aca"))
+            tr = sum(r["ms"] for r in lt if r["kernel"].startswith(("k_lag_mfma", "k_lag_project", "k_lag_expand")))
             st = p.stats()
             vv = v.cpu().numpy()[w.rows].astype(np.complex128)
             r = {"kernel": "laplace" if kernel == 0 else "helmholtz", "k": k, "eps": eps, "aca": aca,

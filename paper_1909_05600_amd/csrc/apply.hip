@@ -2402,151 +2402,243 @@ k_lag_mfma(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const i
     }
 }
 
-// Transfer of one class group through the ACA factors of its class (Sec. 2.2.2, eq. ffmACAmatvec): Z_e =
-// A_c (B_c^T u~_{s(e)}) for up to 16 pairs e, two products on MFMA with the operand layouts of k_lag_mfma.
-// Phase 1: Y (kp x 32) = B_c^T (kp x rp) U (rp x 32): the class's padded rank kp is at most one 32-row tile per
-// wave (the planner keeps kp <= 32 x waves), and each tile's K steps are split over the waves left, their
-// partial tiles added in LDS in a fixed order; phase 2, once every wave has read U: Y is written over U in LDS
-// and C (rp x 32) = A_c (rp x kp) Y.  Complex factors are two planes, and the complex products are formed from the
-// real and imaginary columns as in k_lag_mfma.  Item (desc, group).
-__global__ void __launch_bounds__(256)
-k_lag_aca(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const int4 *__restrict__ work) {
-    extern __shared__ float U[];   // [rp][32], then Y [kp][32]
-    const int4 wk = work[blockIdx.x];
-    const LDesc &d = descs[wk.x];
-    const int g = wk.y;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nwv = blockDim.x >> 6;
-    const int rp = d.rp, helm = d.helm, kpm = d.kpm;
-    const int c = d.grp_cls[g];
-    const int kp = d.acaKp[c];
-    __shared__ int pe[16], ps[16];
-    if (tid < 16) {
-        const int e = d.grp_pair[(int64_t)g * 16 + tid];
-        pe[tid] = e;
-        ps[tid] = e >= 0 ? d.far_src[e] : -1;
-    }
-    __syncthreads();
-    stage_group_sources(d.ut2, ps, rp, U);
-    __syncthreads();
-    const int planes = helm ? 2 : 1;
-    const int col = lane & 31, kh = lane >> 5;
-    // phase 1: B^T U.  The kp / 32 rank tiles times nparts ranges of the K steps go to the waves (every wave
-    // busy when kp is one or two tiles); each range is a multiple of four steps, the last takes the rest
-    const int ntile = kp / 32, nparts = nwv / ntile, steps = rp / 2;
-    const int mt1 = wv % ntile, part = wv / ntile;
-    const bool active = part < nparts;
-    const int chunk = (steps / nparts) / 4 * 4;
-    const int k0 = part * chunk, k1 = part == nparts - 1 ? steps : k0 + chunk;
-    floatx16 y;
-    if (active) {
-        const float *Bre = d.acaB + (int64_t)c * planes * rp * kpm;
-        const float *Bim = Bre + (int64_t)rp * kpm;
-        const gcf BreG = gfl(Bre) + mt1 * 32 + col, BimG = gfl(Bim) + mt1 * 32 + col;
-        floatx16 acc1, acc2;
-        for (int v = 0; v < 16; ++v) {
-            acc1[v] = 0.f;
-            acc2[v] = 0.f;
-        }
-        float a1n[4], a2n[4];
-        auto load = [&](int kk0) {
+// Transfers through the ACA factors of the classes (Sec. 2.2.2, eq. ffmACAmatvec: T_c ~ A_c B_c^T) in two kernels:
+// k_lag_project forms Y_e = B_c^T u~_{s(e)} for every far pair e, by class groups; k_lag_expand forms v~_t = sum_e
+// A_c(e) Y_e by target groups, so that only the rank's worth of values per pair goes through memory (128 B per 16
+// ranks, against 1.7 KB for a transferred pair at r1 = 6), and the reductions per target need no buffer of pairs.
+// Both are bound by what the L2s deliver (10 to 14 TB/s measured: the gathered sources, and the classes' tables once
+// per group).  Sphere of 1M points, Laplace, r1 = 6, level 6 (833,000 pairs): one kernel with both products
+// through LDS and Z per pair 1570 us and its sum in the interpolation 326 -> 227 + 335 and 54 us; sphere of 300,000
+// points, Helmholtz gradient, level 6: 1644 + 3 x 278 -> 290 + 600 + 3 x 53 us; workspaces of these plans 1.6 GB ->
+// 0.3 and 0.46 GB.  Rank 4 u + g of a tile of 16 sits at position 4 g + u:
+// a lane of k_lag_expand reads the positions of its g as one 16-byte load and uses them in steps u, so steps
+// beyond the rank are left out.
+//
+// k_lag_project: one wave per class group of up to 16 pairs, products of v_mfma_f32_16x16x4f32 with the class's
+// ranks as rows (tiles of 16) and the pairs as columns, the real and the imaginary parts of u~ in two products.
+// Column m's lanes take their source's entries 16 jb + 4 g .. + 3 for the four steps of a block of 16 nodes, and
+// B_c^T is stored in that fragment order ([class][plane][rank tile][jb][lane][4 steps]), so a lane's four A
+// operands are one 16-byte load.  The sources go through the wave's own LDS, 32 nodes at a time, so that 16
+// consecutive lanes read 256 consecutive bytes of one source (reading the columns straight from memory puts every
+// lane of a load in another line, at a quarter of the rate).  The next step's loads are issued before a step's
+// products.  Ranks above 16 (few classes) go over the sources once more per tile.
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef const v4f __attribute__((address_space(1))) *gc4;
+typedef v4f __attribute__((address_space(1))) *gm4;
+typedef const char __attribute__((address_space(1))) *gcb;
+
+constexpr int kProjRow = 72;        // LDS floats per staged source: 32 nodes (64 floats) and a pad of two 16-byte slots
+
+template <bool HELM>
+__device__ __forceinline__ void lag_project_group(const LDesc &d, int grp, float *st, int *srcs, int lane) {
+    const int g = lane >> 4, m = lane & 15, nb = d.aca_nb, kt = d.aca_kt;
+    const int c = __builtin_amdgcn_readfirstlane(d.grp_cls[grp]);
+    const int e = d.grp_pair[(int64_t)grp * 16 + m];
+    // an empty slot computes some source's column and stores nothing
+    if (lane < 16) srcs[lane] = d.far_src[max(e, 0)];
+    wave_lds_fence();
+    // staging: this lane moves 16 bytes (two nodes) of sources lane / 16 + 4 i
+    gc4 U[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int k = 2 * (kk0 + u) + kh;
-                a1n[u] = BreG[(int64_t)k * kpm];
-                a2n[u] = 0.f;
-                if (helm) a2n[u] = BimG[(int64_t)k * kpm];
-            }
-        };
-        load(k0);
-        for (int kk0 = k0; kk0 < k1; kk0 += 4) {
-            float bv[4], a1[4], a2[4];
+    for (int i = 0; i < 4; ++i) U[i] = (gc4)(const v4f *)(d.ut2 + (int64_t)srcs[g + 4 * i] * d.rp) + m;
+    float *sw = st + g * kProjRow + 4 * m;
+    const float *sr = st + m * kProjRow + 8 * g;
+    const int64_t tile = (int64_t)nb * 64, plane = tile * kt;
+    const int ntile = (d.acaKp[c] + 15) >> 4;
+    for (int rt = 0; rt < ntile; ++rt) {
+        const gc4 B = (gc4)(d.acaB) + ((int64_t)c * (HELM ? 2 : 1) * kt + rt) * tile + lane;
+        floatx4 yr = floatx4{0.f, 0.f, 0.f, 0.f}, yi = floatx4{0.f, 0.f, 0.f, 0.f};
+        v4f u[4], br[2], bi[2];
+        auto load = [&](int jb) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                bv[u] = U[(2 * (kk0 + u) + kh) * 32 + col];
-                a1[u] = a1n[u];
-                a2[u] = a2n[u];
-            }
-            if (kk0 + 4 < k1) load(kk0 + 4);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int i = 0; i < 4; ++i) u[i] = U[i][8 * jb];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[u], bv[u], acc1, 0, 0, 0);
-                if (helm) acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a2[u], bv[u], acc2, 0, 0, 0);
-            }
-        }
-        for (int v = 0; v < 16; ++v) {
-            float val = acc1[v];
-            if (helm) {
-                const float sw = __shfl_xor(acc2[v], 1, 64);
-                val = (col & 1) ? val + sw : val - sw;
-            }
-            y[v] = val;
-        }
-    }
-    __syncthreads();              // every wave is done with U: its space holds the partial tiles, then Y
-    if (active)
-        for (int v = 0; v < 16; ++v)
-            U[(part * ntile + mt1) * 1024 + (8 * (v >> 2) + 4 * kh + (v & 3)) * 32 + col] = y[v];
-    __syncthreads();
-    float ys[16];                 // kp x 32 entries of Y, at most 16 per thread; partial tiles added in order
-    int ny = 0;
-    for (int e = tid; e < kp * 32; e += blockDim.x, ++ny) {
-        const int tile = e >> 10, within = e & 1023;
-        float acc = 0.f;
-        for (int q = 0; q < nparts; ++q) acc += U[(q * ntile + tile) * 1024 + within];
-        ys[ny] = acc;
-    }
-    __syncthreads();
-    ny = 0;
-    for (int e = tid; e < kp * 32; e += blockDim.x, ++ny) U[e] = ys[ny];
-    __syncthreads();
-    // phase 2: A Y
-    const float *Are = d.acaA + (int64_t)c * planes * kpm * rp;
-    const float *Aim = Are + (int64_t)kpm * rp;
-    const int e = pe[col >> 1];
-    for (int mt = wv; mt < rp / 32; mt += nwv) {
-        floatx16 acc1, acc2;
-        for (int v = 0; v < 16; ++v) {
-            acc1[v] = 0.f;
-            acc2[v] = 0.f;
-        }
-        const gcf AreG = gfl(Are) + mt * 32 + col, AimG = gfl(Aim) + mt * 32 + col;
-        float a1n[4], a2n[4];
-        auto load = [&](int kk0) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int k = 2 * (kk0 + u) + kh;
-                a1n[u] = AreG[(int64_t)k * rp];
-                a2n[u] = 0.f;
-                if (helm) a2n[u] = AimG[(int64_t)k * rp];
+            for (int h = 0; h < 2; ++h) {
+                br[h] = B[(int64_t)(jb + h) * 64];
+                if (HELM) bi[h] = B[plane + (int64_t)(jb + h) * 64];
             }
         };
         load(0);
-        for (int kk0 = 0; kk0 < kp / 2; kk0 += 4) {
-            float bv[4], a1[4], a2[4];
+        for (int jb = 0; jb < nb; jb += 2) {          // 32 nodes (nb is even)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                bv[u] = U[(2 * (kk0 + u) + kh) * 32 + col];
-                a1[u] = a1n[u];
-                a2[u] = a2n[u];
+            for (int i = 0; i < 4; ++i) *reinterpret_cast<v4f *>(sw + 4 * i * kProjRow) = u[i];
+            const v4f cr[2] = {br[0], br[1]}, ci[2] = {bi[0], bi[1]};
+            wave_lds_fence();
+            v4f c0[2], c1[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const v4f *q = reinterpret_cast<const v4f *>(sr + 32 * h);
+                c0[h] = q[0];
+                c1[h] = q[1];
             }
-            if (kk0 + 4 < kp / 2) load(kk0 + 4);
+            wave_lds_fence();
+            if (jb + 2 < nb) load(jb + 2);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[u], bv[u], acc1, 0, 0, 0);
-                if (helm) acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a2[u], bv[u], acc2, 0, 0, 0);
+            for (int h = 0; h < 2; ++h) {
+                const float ur[4] = {c0[h].x, c0[h].z, c1[h].x, c1[h].z}, ui[4] = {c0[h].y, c0[h].w, c1[h].y, c1[h].w};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    yr = mfma16(cr[h][q], ur[q], yr);
+                    yi = mfma16(cr[h][q], ui[q], yi);
+                    if (HELM) {
+                        yr = mfma16(-ci[h][q], ui[q], yr);
+                        yi = mfma16(ci[h][q], ur[q], yi);
+                    }
+                }
             }
         }
-        for (int v = 0; v < 16; ++v) {
-            const int i = mt * 32 + 8 * (v >> 2) + 4 * kh + (v & 3);
-            float val = acc1[v];
-            if (helm) {
-                const float sw = __shfl_xor(acc2[v], 1, 64);
-                val = (col & 1) ? val + sw : val - sw;
-            }
-            if (e >= 0) reinterpret_cast<float *>(d.Z + (int64_t)e * rp + i)[col & 1] = val;
+        // Y_e: [tile][re, im][16]; lane (pair m, g) holds positions 4 g .. 4 g + 3 of the tile
+        if (e >= 0) {
+            const gm4 Y = (gm4)(v4f *)(d.Z) + ((int64_t)e * kt + rt) * 8 + g;
+            Y[0] = v4f{yr[0], yr[1], yr[2], yr[3]};
+            Y[4] = v4f{yi[0], yi[1], yi[2], yi[3]};
         }
+    }
+}
+
+// Item (desc, first group, groups' end, 0): four class groups per block, one per wave.
+template <bool HELM>
+__global__ void __launch_bounds__(256)
+k_lag_project(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const int4 *__restrict__ work) {
+    __shared__ float st[4][16 * kProjRow];
+    __shared__ int srcs[4][16];
+    const int4 wk = work[blockIdx.x];
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = wk.y + wv;
+    if (grp < wk.z) lag_project_group<HELM>(descs[wk.x], grp, st[wv], srcs[wv], threadIdx.x & 63);
+}
+
+// k_lag_expand: v~ of a group of target boxes of the same octant of their parents, neighbours in Morton order, which
+// share most of their translation classes: 16 columns (target, part) for eight targets, one unit of products per
+// class that occurs in the group and rank tile (the plan lists them with each target's pair, k_expand_fill), 16
+// rows and 4 ranks per v_mfma_f32_16x16x4f32.  A wave keeps RT row tiles of the group (the last block of a group the
+// one or two that are left) in registers and walks its share of the group's units; A_c is stored in fragment order
+// ([class][rank tile][row tile][plane][lane][4 steps]), so a unit is RT + 1 loads of 16 bytes per lane (twice that
+// for the complex kernel), issued one or two units ahead (the unit list is staged in
+// LDS: read from memory unit by unit it put its misses into the chain, 335 -> 517 us at level 6).  A target without the class has a
+// zero column: half of them on a sphere (a quarter in a volume), which still costs less than FMAs on the VALU
+// with Y_e broadcast (LDS or scalar loads in a serial chain per pair).  The complex kernel, whose A_c is twice as
+// long, takes two tiles of eight targets per group for each load of A_c, and leaves a tile out where none of its
+// targets has the class.  The waves' tiles are added in wave order in LDS.  Item (desc, target group, first row tile).
+template <bool HELM, int RT>
+__device__ __forceinline__ void lag_expand_body(const LDesc &d, const int grp, const int rt0, float *sm) {
+    constexpr int CT = HELM ? 2 : 1, NP = HELM ? 2 : 1;        // column tiles of eight targets, planes of A
+    const int tid = threadIdx.x, lane = tid & 63, nw = blockDim.x >> 6;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15, g = lane >> 4, part = col & 1;
+    const int r = d.r1 * d.r1 * d.r1, nrt = (r + 15) >> 4, kt = d.aca_kt;
+    const int off = __builtin_amdgcn_readfirstlane(d.exp_ptr[grp]), n = __builtin_amdgcn_readfirstlane(d.exp_cnt[grp]);
+    // the group's units in LDS: addresses then depend on no load in flight
+    int *se = reinterpret_cast<int *>(sm), *sc = se + 8 * CT * n;      // [n][8 CT] pairs, [n] codes
+    for (int i = tid; i < 8 * CT * n; i += blockDim.x) se[i] = d.exp_e[(int64_t)off * (8 * CT) + i];
+    for (int i = tid; i < n; i += blockDim.x) sc[i] = d.exp_cls[off + i];
+    const int q0 = n * wv / nw, q1 = n * (wv + 1) / nw;
+    const uint32_t ustride = (uint32_t)nrt * NP * 1024;        // bytes of A per (class, rank tile)
+    const gcb A0 = (gcb)(d.acaA) + (uint32_t)rt0 * NP * 1024;
+    const gcb Y0 = (gcb)(d.Z);
+    const uint32_t alane = 16 * lane, ylane = 16 * g + 64 * part, ystride = 128 * kt;
+    const float sgn = part ? 1.f : -1.f;                       // (re, im) columns of i Y: (-Y_im, Y_re)
+    floatx4 acc[RT][CT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int h = 0; h < CT; ++h) acc[t][h] = floatx4{0.f, 0.f, 0.f, 0.f};
+    struct Unit {
+        v4f a[RT][NP], y[CT][NP];
+        int steps, e[CT];
+    };
+    // operands in flight: two units ahead, one for the complex kernel's four tiles (registers)
+    constexpr int NB = HELM && RT == 4 ? 2 : 3;
+    Unit buf[NB];
+    __syncthreads();
+    auto load = [&](int q, Unit &u) {
+        q = min(q, q1 - 1);
+        const uint32_t code = __builtin_amdgcn_readfirstlane(sc[q]), kb = (code >> 2) & 7;
+        u.steps = code & 3;
+        const gcb A = A0 + (uint64_t)((code >> 5) * kt + kb) * ustride;
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+#pragma unroll
+            for (int p = 0; p < NP; ++p) u.a[t][p] = *(gc4)(A + (t * NP + p) * 1024 + alane);
+#pragma unroll
+        for (int h = 0; h < CT; ++h) {
+            u.e[h] = se[(8 * CT) * q + 8 * h + (col >> 1)];
+            // a target without the class reads pair 0 instead (a branch here costs more: 335 -> 460 us at level 6); its
+            // column is zeroed before the products
+            const gcb Y = Y0 + (uint64_t)(uint32_t)max(u.e[h], 0) * ystride + (kb * 128 + ylane);
+            u.y[h][0] = *(gc4)Y;
+            if (HELM) u.y[h][NP - 1] = *(gc4)(Y + (64 - 128 * part));
+        }
+    };
+    auto products = [&](const Unit &u) {
+#pragma unroll
+        for (int h = 0; h < CT; ++h) {
+            if (CT > 1 && __ballot(u.e[h] >= 0) == 0) continue;    // none of these eight targets has the class
+            v4f y0, y1;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                y0[k] = u.e[h] < 0 ? 0.f : u.y[h][0][k];
+                if (HELM) y1[k] = u.e[h] < 0 ? 0.f : sgn * u.y[h][NP - 1][k];
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (k > u.steps) break;
+#pragma unroll
+                for (int t = 0; t < RT; ++t) {
+                    acc[t][h] = mfma16(u.a[t][0][k], y0[k], acc[t][h]);
+                    if (HELM) acc[t][h] = mfma16(u.a[t][NP - 1][k], y1[k], acc[t][h]);
+                }
+            }
+        }
+    };
+    if (q0 < q1) {
+#pragma unroll
+        for (int i = 0; i < NB - 1; ++i) load(q0 + i, buf[i]);
+        for (int q = q0; q < q1; q += NB) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                load(q + i + NB - 1, buf[(i + NB - 1) % NB]);
+                __builtin_amdgcn_sched_barrier(0);
+                if (q + i < q1) products(buf[i]);
+            }
+        }
+    }
+    // one column tile after the other, the waves' tiles added in wave order
+#pragma unroll
+    for (int h = 0; h < CT; ++h) {
+        __syncthreads();                          // every wave is done with the unit list, or with the other tile
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) sm[((wv * RT + t) * 16 + 4 * g + v) * 16 + col] = acc[t][h][v];
+        __syncthreads();
+        for (int i = tid; i < 8 * 16 * RT; i += blockDim.x) {
+            const int q = i / (16 * RT), row = i % (16 * RT), t = d.exp_tgt[((int64_t)grp * CT + h) * 8 + q];
+            if (t < 0 || rt0 * 16 + row >= r) continue;
+            float2 s = make_float2(0.f, 0.f);
+            for (int w = 0; w < nw; ++w) {
+                const float *p = sm + (w * RT * 16 + row) * 16 + 2 * q;
+                s.x += p[0];
+                s.y += p[1];
+            }
+            // over u~, which k_lag_project has read for the last time
+            d.ut2[(int64_t)t * d.rp + rt0 * 16 + row] = s;
+        }
+    }
+}
+
+template <bool HELM, int RT>
+__global__ void __launch_bounds__(RT == 1 ? 1024 : 512)
+k_lag_expand(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const int4 *__restrict__ work) {
+    extern __shared__ float expand_sm[];      // the group's units, then [waves][RT][16][16]
+    const int4 wk = work[blockIdx.x];
+    const LDesc &d = descs[wk.x];
+    const int left = ((d.r1 * d.r1 * d.r1 + 15) >> 4) - wk.z;        // row tiles from this block's first on
+    if (RT == 4 && left < 4) {
+        if (left > 1) lag_expand_body<HELM, 2>(d, wk.y, wk.z, expand_sm);
+        else lag_expand_body<HELM, 1>(d, wk.y, wk.z, expand_sm);
+    } else {
+        lag_expand_body<HELM, RT>(d, wk.y, wk.z, expand_sm);
     }
 }
 
@@ -2675,7 +2767,15 @@ __device__ __forceinline__ void lag_interp_r1(const LDesc &d, const int4 wk, flo
     const double two_over_dl = d.two_over_dl;
     const int64_t e0 = d.far_ptr[t], e1 = d.far_ptr[t + 1];
     const gc2 Z = gl(d.Z);
-    for (int i = tid; i < r; i += kThreads) {
+    if (d.acaA) {
+        // ACA levels: k_lag_expand has summed v~
+        const gc2 V = gl(d.ut2) + (int64_t)t * rp;
+        for (int i = tid; i < r; i += blockDim.x) {
+            const v2f z = V[i];
+            vt[i] = make_float2(z.x, z.y);
+        }
+    } else
+    for (int i = tid; i < r; i += blockDim.x) {
         float ax = 0.f, ay = 0.f;
         int64_t e = e0;
         for (; e + 8 <= e1; e += 8) {
@@ -2697,7 +2797,7 @@ __device__ __forceinline__ void lag_interp_r1(const LDesc &d, const int4 wk, flo
     }
     __syncthreads();
     const double cx = d.tctr[3 * t], cy = d.tctr[3 * t + 1], cz = d.tctr[3 * t + 2];
-    for (int i = wk.z + tid; i < wk.w; i += kThreads) {
+    for (int i = wk.z + tid; i < wk.w; i += blockDim.x) {
         float lx[R1], ly[R1], lz[R1];
         const float tx = (float)((d.txs[i] - cx) * two_over_dl), ty = (float)((d.tys[i] - cy) * two_over_dl);
         const float tz = (float)((d.tzs[i] - cz) * two_over_dl);
@@ -3749,8 +3849,13 @@ KernelFn kernel_of(const Stage &S, int &threads) {
         // a = waves per block (each takes its own 32-row tiles of T over the block's staged sources)
         case K_MFMA32: threads = 64 * std::max(1, S.a); return k_lag_mfma;
         case K_MFMA16: threads = 64 * std::max(1, S.a); return k_lag_mfma16;
-        case K_ACA: threads = 64 * std::max(1, S.a); return k_lag_aca;
-        case K_INTERP: return k_lag_interp;
+        case K_ACA: return S.b ? k_lag_project<true> : k_lag_project<false>;
+        case K_EXPAND:
+            // a = 100 (row tiles per wave) + waves
+            threads = 64 * std::max(1, S.a % 100);
+            if (S.a < 200) return S.b ? k_lag_expand<true, 1> : k_lag_expand<false, 1>;
+            return S.b ? k_lag_expand<true, 4> : k_lag_expand<false, 4>;
+        case K_INTERP: threads = 64 * std::max(1, S.a); return k_lag_interp;
         case K_NEAR: threads = 64; return S.b ? (S.a ? k_near<true, true> : k_near<true, false>) : k_near<false, false>;
         case K_NEAR_SYM:
             // a = BIG + 2 NRM (NRM 0: the kernel itself, 1: normal derivative at the targets, 2: at the sources,
@@ -3779,7 +3884,7 @@ KernelFn kernel_of(const Stage &S, int &threads) {
         case K_NEAR_GRAD:
             threads = 64;
             return S.b ? (S.a ? k_near_grad<true, true> : k_near_grad<true, false>) : k_near_grad<false, false>;
-        case K_INTERP_DN: return k_lag_interp_dn;
+        case K_INTERP_DN: threads = 64 * std::max(1, S.a); return k_lag_interp_dn;
         case K_BWD_PAIR_DN:
             if (S.a == 100) {
                 threads = 64;
@@ -3966,7 +4071,8 @@ std::string kernel_name(int kern, int a, int b) {
         case K_DLCOMBINE: return "k_dl_combine";
         case K_MFMA32: return "k_lag_mfma";
         case K_MFMA16: return "k_lag_mfma16";
-        case K_ACA: return "k_lag_aca";
+        case K_ACA: return "k_lag_project<" + tf(b) + ">";
+        case K_EXPAND: return "k_lag_expand<" + tf(b) + (a < 200 ? ", 1>" : ", 4>");
         case K_INTERP: return "k_lag_interp";
         case K_NEAR: return "k_near<" + tf(b) + ", " + tf(b && a) + ">";
         case K_NEAR_SYM:

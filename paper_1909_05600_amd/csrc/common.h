@@ -243,9 +243,14 @@ struct LDesc {
     float2 *ucomp;                         // split double layer: the densities u n_c (ny apart), or null
     float4 *utx;                           // split double layer: u~ of the densities u n_1, u n_2, utstride apart
     int64_t utstride;
-    const float *acaA, *acaB;              // ACA factors: A [class][plane][kpm][rp], B^T [class][plane][rp][kpm]
-    const int32_t *acaKp;                  // [class] rank padded to 32
-    int kpm;                               // largest padded rank
+    const float *acaA, *acaB;              // ACA factors in fragment order: A [class][aca_kt][row tile][plane][64][4]
+                                           // (k_lag_expand), B^T [class][plane][aca_kt][aca_nb][64][4] (k_lag_project)
+    const int32_t *acaKp;                  // [class] rank
+    int aca_kt, aca_nb;                    // rank tiles of 16 (most of any class), blocks of 16 nodes
+    const int32_t *exp_tgt;                // target groups of k_lag_expand, [group][8, Helmholtz 16] (-1: none)
+    const int32_t *exp_ptr, *exp_cnt;      // per group: first unit, units (one per class that occurs and rank tile)
+    const int32_t *exp_cls;                // unit: 32 class + 4 rank tile + steps - 1
+    const int32_t *exp_e;                  // unit: each target's far pair of the class (-1: none)
     const int32_t *grp_pair, *grp_cls;
     float2 *ut2, *Z;
     double two_over_dl;
@@ -272,7 +277,7 @@ enum Kern {
     K_ANTERP, K_MFMA32, K_MFMA16, K_INTERP, K_NEAR, K_PERM_OUT, K_ZERO_OUT, K_BSUM,
     K_GSPREAD, K_GZ, K_GPHI, K_GPHIT, K_GZT, K_GINTERP, K_ACA, K_NEAR_DN, K_BWD_PAIR_DN, K_INTERP_DN,
     K_NEAR_SYM, K_NEAR_GATHER, K_NEAR_DL, K_ANTERP_DL, K_FWD_PAIR_DL, K_DIRSCALE, K_DNCOMBINE, K_DLCOMBINE,
-    K_NEAR_GRAD
+    K_NEAR_GRAD, K_EXPAND
 };
 
 struct Stage {
@@ -347,7 +352,12 @@ struct Level {
     // ACA factors of the transfer matrices (T is not kept): ranks, padded ranks, their maximum
     bool aca = false;
     double aca_rank = 0.0;               // mean rank over the classes (whenever ACA was evaluated)
-    int kpm = 0;
+    int aca_kt = 0, aca_nb = 0;          // rank tiles of 16, blocks of 16 nodes (LDesc)
+    DevBuf<int32_t> exp_tgt, exp_ptr, exp_cnt;   // target groups of k_lag_expand and their classes (LDesc)
+    DevBuf<int32_t> exp_cls, exp_e;
+    int exp_max = 0;                     // most units of a group
+    std::vector<int64_t> h_far_ptr;      // Lagrange levels: far list offsets of the target boxes
+    std::vector<int32_t> h_ijk;          // Lagrange levels: integer coordinates of the target boxes
     std::vector<int32_t> aca_ranks;
     DevBuf<float> acaA, acaB;
     DevBuf<int32_t> acaKp;

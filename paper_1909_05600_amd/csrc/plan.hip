@@ -589,21 +589,72 @@ k_lagrange_T(int ncls, const double *r0, int r1, int rp, const double *nodes, do
     }
 }
 
-__global__ void __launch_bounds__(kThreads)
-k_count_cls(const int32_t *cls, int64_t n, int32_t *cnt) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) atomicAdd(&cnt[cls[i]], 1);
+// Class groups are formed per region, one of nreg equal ranges of the far pairs (the pairs are in target order, so a
+// region's pairs lie in one part of the tree): bin (region, class).
+__device__ __forceinline__ int class_bin(int64_t i, int64_t per_reg, int ncls, const int32_t *cls) {
+    return (int)(i / per_reg) * ncls + cls[i];
 }
 
-// Pairs of one class go to consecutive 16-slot groups (order inside a class is free: every
+__global__ void __launch_bounds__(kThreads)
+k_count_cls(const int32_t *cls, int64_t n, int64_t per_reg, int ncls, int32_t *cnt) {
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) atomicAdd(&cnt[class_bin(i, per_reg, ncls, cls)], 1);
+}
+
+// Pairs of one bin go to consecutive 16-slot groups (order inside a bin is free: every
 // pair's product is computed on its own and written to its own slot).
 __global__ void __launch_bounds__(kThreads)
-k_fill_groups(const int32_t *cls, int64_t n, const int32_t *gstart, int32_t *cursor, int32_t *grp_pair) {
+k_fill_groups(const int32_t *cls, int64_t n, int64_t per_reg, int ncls, const int32_t *gstart, int32_t *cursor,
+              int32_t *grp_pair) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const int c = cls[i];
+    const int c = class_bin(i, per_reg, ncls, cls);
     const int slot = atomicAdd(&cursor[c], 1);
     grp_pair[(int64_t)gstart[c] * 16 + slot] = (int32_t)i;
+}
+
+// The classes that occur in a target group (G boxes) of k_lag_expand, ascending, with each target's far pair of the
+// class: a table in LDS, then its non-empty rows in order (one wave, by lane scans).
+template <int G>
+__global__ void __launch_bounds__(kThreads)
+k_expand_fill(const int32_t *tgt, const int64_t *far_ptr, const int32_t *far_cls, int ncls, const int32_t *ranks,
+              const int32_t *ptr, int32_t *cnt, int32_t *out_cls, int32_t *out_e) {
+    extern __shared__ int32_t tab[];        // [ncls][G]
+    const int g = blockIdx.x, tid = threadIdx.x;
+    for (int i = tid; i < G * ncls; i += kThreads) tab[i] = -1;
+    __syncthreads();
+    constexpr int per = kThreads / G;       // threads per target
+    const int q = tid / per;
+    const int t = tgt[G * g + q];
+    if (t >= 0) {
+        const int64_t e0 = far_ptr[t];
+        const int n = (int)(far_ptr[t + 1] - e0);
+        for (int j = tid % per; j < n; j += per) tab[G * far_cls[e0 + j] + q] = (int32_t)(e0 + j);
+    }
+    __syncthreads();
+    if (tid >= 64) return;
+    int64_t o = ptr[g];
+    for (int c0 = 0; c0 < ncls; c0 += 64) {
+        const int c = c0 + tid;
+        int m = 0;                          // units of class c
+        if (c < ncls) {
+            bool any = false;
+            for (int s = 0; s < G; ++s) any = any || tab[G * c + s] >= 0;
+            if (any) m = (ranks[c] + 15) >> 4;
+        }
+        int at = m;                         // inclusive sum over the lanes
+        for (int k = 1; k < 64; k <<= 1) {
+            const int v = __shfl_up(at, k, 64);
+            if (tid >= k) at += v;
+        }
+        for (int kb = 0; kb < m; ++kb) {
+            const int64_t u = o + at - m + kb;
+            out_cls[u] = 32 * c + 4 * kb + min(4, (ranks[c] - 16 * kb + 3) >> 2) - 1;
+            for (int s = 0; s < G; ++s) out_e[G * u + s] = tab[G * c + s];
+        }
+        o += __shfl(at, 63, 64);
+    }
+    if (tid == 0) cnt[g] = (int)(o - ptr[g]);
 }
 
 // ------------------------------------------------------------------ Gegenbauer tables
@@ -1055,6 +1106,50 @@ T *keep(Scratch &SC, const std::vector<T> &h, hipStream_t st) {
     return p;
 }
 
+// Target groups of k_lag_expand: the level's targets in Morton order, octant of the parent by octant (targets of one
+// octant meet the same translation classes), G to a group, and each group's list of units (k_expand_fill;
+// room for as many as the group can have: its far pairs, or all classes, times the most rank tiles).
+// Returns the groups' unit counts in pinned memory, valid once the stream has passed.
+const int32_t *expand_lists(Level &LV, int G, hipStream_t st, Scratch &SC) {
+    std::vector<char> on(LV.h_ijk.size() / 3, 0);
+    for (int32_t t : LV.h_tgt) on[(size_t)t] = 1;
+    std::vector<int32_t> by_oct[8], tgt, ptr;
+    for (size_t t = 0; t < on.size(); ++t)
+        if (on[t]) {
+            const int32_t *q = &LV.h_ijk[3 * t];
+            by_oct[(q[0] & 1) * 4 + (q[1] & 1) * 2 + (q[2] & 1)].push_back((int32_t)t);
+        }
+    for (auto &v : by_oct) {
+        tgt.insert(tgt.end(), v.begin(), v.end());
+        while (tgt.size() % G) tgt.push_back(-1);
+    }
+    const int ng = (int)(tgt.size() / G);
+    // a unit's code is 32 class + 4 rank tile + steps - 1 (the planner keeps ranks at 128 or below)
+    FFM_CHECK(LV.aca_kt <= 8 && LV.nfar < ((int64_t)1 << 31), FFM_EINTERNAL, "ffm_plan: ACA rank or far pair count out of range");
+    int64_t off = 0;
+    for (int g = 0; g < ng; ++g) {
+        ptr.push_back((int32_t)off);
+        int64_t np = 0;
+        for (int q = 0; q < G; ++q) {
+            const int32_t t = tgt[(size_t)G * g + q];
+            if (t >= 0) np += LV.h_far_ptr[(size_t)t + 1] - LV.h_far_ptr[(size_t)t];
+        }
+        off += std::min<int64_t>(np, LV.ncls) * LV.aca_kt;
+    }
+    FFM_CHECK(off < ((int64_t)1 << 31), FFM_EINTERNAL, "ffm_plan: too many target group classes");
+    upload(LV.exp_tgt, tgt, st, SC);
+    upload(LV.exp_ptr, ptr, st, SC);
+    LV.exp_cnt.alloc((size_t)ng);
+    LV.exp_cls.alloc((size_t)off);
+    LV.exp_e.alloc((size_t)off * G);
+    // (at most kWin^3 classes: 110 KB of LDS at G = 16, the most a launch asks for)
+    FFM_LAUNCH(G == 16 ? k_expand_fill<16> : k_expand_fill<8>, ng, kThreads, sizeof(int32_t) * G * LV.ncls, st, LV.exp_tgt.p,
+               LV.far_ptr.p, LV.far_cls.p, LV.ncls, LV.acaKp.p, LV.exp_ptr.p, LV.exp_cnt.p, LV.exp_cls.p, LV.exp_e.p);
+    int32_t *cnt = SC.pin<int32_t>((size_t)ng);
+    FFM_HIP(hipMemcpyAsync(cnt, LV.exp_cnt.p, sizeof(int32_t) * ng, hipMemcpyDeviceToHost, st));
+    return cnt;
+}
+
 // ------------------------------------------------------------------ tree construction
 void build_tree(Tree &T, const double *P, int64_t n, const double corner[3], double S, hipStream_t st,
                 Scratch &SC) {
@@ -1128,6 +1223,7 @@ void build_level(Tree &T, LevelScratch &S, int l, double d0, hipStream_t st) {
 // lists of every level are read after one synchronisation.
 struct WorkFetch {
     int32_t *par = nullptr;              // one tree, far levels: parent of every box
+    int32_t *ijk = nullptr;              // Lagrange levels: integer coordinates of every target box
     int32_t *sx = nullptr, *sy = nullptr;
     int64_t *ptr = nullptr;
     uint8_t *act = nullptr;
@@ -1137,8 +1233,12 @@ struct WorkFetch {
 };
 
 void fetch_work_lists(Level &LV, const TreeLevel &LX, const TreeLevel &LY, bool near, hipStream_t st, Scratch &SC,
-                      WorkFetch &F, bool sym = false) {
+                      WorkFetch &F, bool sym = false, bool ijk = false) {
     F.nbx = LX.nbox;
+    if (ijk) {
+        F.ijk = SC.pin<int32_t>(3 * (size_t)LX.nbox);
+        FFM_HIP(hipMemcpyAsync(F.ijk, LX.ijk.p, sizeof(int32_t) * 3 * LX.nbox, hipMemcpyDeviceToHost, st));
+    }
     F.nby = LY.nbox;
     F.sx = SC.pin<int32_t>(LX.nbox + 1);
     F.sy = SC.pin<int32_t>(LY.nbox + 1);
@@ -1191,6 +1291,10 @@ void fetch_work_lists(Level &LV, const TreeLevel &LX, const TreeLevel &LY, bool 
 void build_work_lists(Plan &P, Level &LV, bool near, const WorkFetch &F) {
     std::vector<int32_t> sx(F.sx, F.sx + F.nbx + 1), sy(F.sy, F.sy + F.nby + 1);
     if (F.par) LV.h_par.assign(F.par, F.par + F.nbx);
+    if (F.ijk) {
+        LV.h_ijk.assign(F.ijk, F.ijk + 3 * (size_t)F.nbx);
+        LV.h_far_ptr.assign(F.ptr, F.ptr + F.nbx + 1);
+    }
     const int64_t *ptr = F.ptr;
     const uint8_t *act = F.act;
     const unsigned long long near_pairs = F.near_pairs ? *F.near_pairs : 0ull;
@@ -1484,7 +1588,8 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
     WorkFetch wf_near;
     std::vector<WorkFetch> wf_early(P.leaf + 1);
     for (int l = 1; l <= P.leaf; ++l) {
-        if (P.lev[l].nfar) fetch_work_lists(P.lev[l], TX.lev[l], TY.lev[l], false, st, SC, wf[l], P.same);
+        const bool geg = P.kernel == FFM_HELMHOLTZ && P.k * std::ldexp(d0, -l) >= P.opt.kd_switch;
+        if (P.lev[l].nfar) fetch_work_lists(P.lev[l], TX.lev[l], TY.lev[l], false, st, SC, wf[l], P.same, !geg);
         if (l < P.leaf && P.lev[l].nearly) fetch_early_lists(P.lev[l], TX.lev[l], TY.lev[l], st, SC, wf_early[l]);
     }
     // one set: the leaf near field evaluates each unordered pair of distinct boxes once (G is symmetric; the
@@ -1735,18 +1840,25 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
             // (the double layer's anterpolated u~ carries the factor 2 / d_l of the derivative, beyond the
             // range the FP16 scaling of the sources provides for: its transfers stay FP32)
             LV.fp16 = P.opt.precision == FFM_PREC_MIXED && !P.dl && std::ldexp(1.0, -11) * cond <= P.eps;
-            // class groups of 16 pairs for the MFMA transfer
-            DevBuf<int32_t> cnt(LV.ncls), cursor(LV.ncls);
-            FFM_HIP(hipMemsetAsync(cnt.p, 0, sizeof(int32_t) * LV.ncls, st));
-            FFM_LAUNCH(k_count_cls, nblocks(LV.nfar), kThreads, 0, st, LV.far_cls.p, LV.nfar, cnt.p);
-            std::vector<int32_t> hc(LV.ncls), gstart(LV.ncls), gcls;
-            FFM_HIP(hipMemcpyAsync(hc.data(), cnt.p, sizeof(int32_t) * LV.ncls, hipMemcpyDeviceToHost, st));
+            // class groups of 16 pairs for the MFMA transfer, by region and class: the blocks of one XCD then gather
+            // their sources from one part of the tree, which stays in its L2, where there are pairs enough for
+            // eight regions of on average 160 pairs per class (half a group per bin is left empty, 5%)
+            int nreg = 8;
+            while (nreg > 1 && LV.nfar < (int64_t)160 * LV.ncls * nreg) nreg /= 2;
+            const int64_t per_reg = (LV.nfar + nreg - 1) / nreg;
+            const int nbin = nreg * LV.ncls;
+            DevBuf<int32_t> cnt(nbin), cursor(nbin);
+            FFM_HIP(hipMemsetAsync(cnt.p, 0, sizeof(int32_t) * nbin, st));
+            FFM_LAUNCH(k_count_cls, nblocks(LV.nfar), kThreads, 0, st, LV.far_cls.p, LV.nfar, per_reg, LV.ncls, cnt.p);
+            std::vector<int32_t> hb(nbin), hc(LV.ncls, 0), gstart(nbin), gcls;
+            FFM_HIP(hipMemcpyAsync(hb.data(), cnt.p, sizeof(int32_t) * nbin, hipMemcpyDeviceToHost, st));
             FFM_HIP(hipStreamSynchronize(st));
             int32_t g = 0;
-            for (int c = 0; c < LV.ncls; ++c) {
-                gstart[c] = g;
-                const int ng = (hc[c] + 15) / 16;
-                for (int q = 0; q < ng; ++q) gcls.push_back(c);
+            for (int b = 0; b < nbin; ++b) {
+                gstart[b] = g;
+                hc[b % LV.ncls] += hb[b];
+                const int ng = (hb[b] + 15) / 16;
+                for (int q = 0; q < ng; ++q) gcls.push_back(b % LV.ncls);
                 g += ng;
             }
             LV.ngrp = g;
@@ -1755,6 +1867,7 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
             // pair then costs 2 rp kp instead of rp^2 multiply-adds.  Not at FP16 levels (FP16 runs 16x the FP32
             // rate on full matrices) nor below r1 = 5 (r = 64: one 32-row tile already costs as much as T).
             LV.aca = false;
+            const int32_t *exp_cnt = nullptr;
             const int nwv = std::min(4, LV.rp / 32);
             const bool force_aca = (P.opt.flags & FFM_FLAG_ACA) != 0;
             if (!LV.fp16 && !(P.opt.flags & FFM_FLAG_NO_ACA) && (LV.r1 >= 5 || force_aca)) {
@@ -1785,27 +1898,35 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
                 LV.aca = kpm <= 32 * nwv && (force_aca || cost_a <= 0.75 * cost_t);
                 LV.aca_rank = LV.ncls ? rank_sum / LV.ncls : 0.0;
                 if (LV.aca) {
-                    LV.kpm = kpm;
+                    const int r = LV.r, planes = helm ? 2 : 1;
+                    const int rmax = *std::max_element(rank.begin(), rank.end());
+                    const int kt = LV.aca_kt = std::max(1, (rmax + 15) / 16), nrt = (r + 15) / 16;
+                    const int nb = LV.aca_nb = LV.rp / 16;
                     LV.aca_ranks.assign(rank.begin(), rank.end());
-                    const int planes = helm ? 2 : 1;
-                    std::vector<float> ha((size_t)LV.ncls * planes * kpm * LV.rp, 0.f);
-                    std::vector<float> hb((size_t)LV.ncls * planes * LV.rp * kpm, 0.f);
-                    const int r = LV.r;
+                    std::vector<float> ha((size_t)LV.ncls * kt * nrt * planes * 256, 0.f);
+                    std::vector<float> hf((size_t)LV.ncls * planes * kt * nb * 256, 0.f);
                     for (int c = 0; c < LV.ncls; ++c)
                         for (int q = 0; q < rank[c]; ++q)
                             for (int i = 0; i < r; ++i) {
                                 const cd a = Af[c][(size_t)q * r + i], b = Bf[c][(size_t)q * r + i];
-                                // A: element (i, q) at [c][plane][q][i]; B^T: element (q, j = i) at [c][plane][j][q]
-                                ha[(((size_t)c * planes) * kpm + q) * LV.rp + i] = (float)a.real();
-                                hb[(((size_t)c * planes) * LV.rp + i) * kpm + q] = (float)b.real();
+                                // rank q = 16 kb + 4 u + g at position 4 g + u of its tile.  A: row i % 16, lane
+                                // group g, step u; B^T: the position as row, node i as lane group and step
+                                const int kb = q / 16, u = (q % 16) / 4, g = q % 4, pos = 4 * g + u;
+                                const size_t ia = (((size_t)c * kt + kb) * nrt + i / 16) * planes * 256 +
+                                                  (i % 16 + 16 * g) * 4 + u;
+                                const size_t ib = (((size_t)c * planes * kt + kb) * nb + i / 16) * 256 +
+                                                  (pos + 16 * ((i % 16) / 4)) * 4 + i % 4;
+                                ha[ia] = (float)a.real();
+                                hf[ib] = (float)b.real();
                                 if (helm) {
-                                    ha[(((size_t)c * planes + 1) * kpm + q) * LV.rp + i] = (float)a.imag();
-                                    hb[(((size_t)c * planes + 1) * LV.rp + i) * kpm + q] = (float)b.imag();
+                                    ha[ia + 256] = (float)a.imag();
+                                    hf[ib + (size_t)kt * nb * 256] = (float)b.imag();
                                 }
                             }
                     upload(LV.acaA, ha, st, SC);
-                    upload(LV.acaB, hb, st, SC);
-                    upload(LV.acaKp, kp, st, SC);
+                    upload(LV.acaB, hf, st, SC);
+                    upload(LV.acaKp, LV.aca_ranks, st, SC);
+                    exp_cnt = expand_lists(LV, helm ? 16 : 8, st, SC);
                 }
             }
             if (!LV.aca) {
@@ -1826,12 +1947,14 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
             upload(LV.grp_cls, gcls, st, SC);
             LV.grp_pair.alloc((size_t)16 * std::max(g, 1));
             FFM_HIP(hipMemsetAsync(LV.grp_pair.p, 0xff, sizeof(int32_t) * 16 * std::max(g, 1), st));
-            FFM_HIP(hipMemsetAsync(cursor.p, 0, sizeof(int32_t) * LV.ncls, st));
-            FFM_LAUNCH(k_fill_groups, nblocks(LV.nfar), kThreads, 0, st, LV.far_cls.p, LV.nfar, dgs.p, cursor.p,
-                       LV.grp_pair.p);
+            FFM_HIP(hipMemsetAsync(cursor.p, 0, sizeof(int32_t) * nbin, st));
+            FFM_LAUNCH(k_fill_groups, nblocks(LV.nfar), kThreads, 0, st, LV.far_cls.p, LV.nfar, per_reg, LV.ncls, dgs.p,
+                       cursor.p, LV.grp_pair.p);
             FFM_HIP(hipStreamSynchronize(st));
-            ws_src = std::max(ws_src, ((size_t)nby * LV.rp + 1) / 2);
-            ws_z = std::max(ws_z, (size_t)LV.nfar * LV.rp);
+            LV.exp_max = exp_cnt ? *std::max_element(exp_cnt, exp_cnt + LV.exp_cnt.n) : 0;
+            // u~ (and, at ACA levels, v~ in its place); per far pair Z, or Y of its rank tiles
+            ws_src = std::max(ws_src, ((size_t)(LV.aca ? std::max(nbx, nby) : nby) * LV.rp + 1) / 2);
+            ws_z = std::max(ws_z, (size_t)LV.nfar * (LV.aca ? 16 * LV.aca_kt : LV.rp));
         }
     }
     plog.mark("tables");
@@ -2332,19 +2455,34 @@ void plan_stages(Plan &P, const Tune &tu, hipStream_t st, Scratch *keep) {
                 LV.stages.push_back(make_stage(K_BSUM, 0, 0, s3, l, 0, std::move(bs), st, SC));
             }
         } else {
-            std::vector<int4> an, mf, ip;
+            std::vector<int4> an, mf, ex, ip;
             for (int32_t b : LV.h_fwd) an.push_back(make_int4(l, b, 0, 0));
-            // class groups are numbered class by class; blocks are dealt to the 8 XCDs in turn, so block b takes
-            // group (b mod 8) per + b / 8 and each XCD works through a contiguous range of classes, reading
-            // each class's T into its own L2 once
-            {
+            // class groups are numbered region by region and class by class; blocks are dealt to the 8 XCDs in turn, so
+            // block b takes the groups of (b mod 8) per + b / 8 and each XCD works through one contiguous range: its
+            // own region (or, with one region, its own classes)
+            auto xcd_deal = [](int32_t n, auto &&put) {
                 constexpr int kXcd = 8;
-                const int32_t per = (LV.ngrp + kXcd - 1) / kXcd;
+                const int32_t per = (n + kXcd - 1) / kXcd;
                 for (int32_t k = 0; k < per; ++k)
-                    for (int x = 0; x < kXcd; ++x) {
-                        const int32_t g = x * per + k;
-                        if (g < LV.ngrp) mf.push_back(make_int4(l, g, 0, 0));
-                    }
+                    for (int x = 0; x < kXcd; ++x)
+                        if (x * per + k < n) put(x * per + k);
+            };
+            // k_lag_expand: four row tiles per wave; one, over sixteen waves, where that leaves too few blocks.  The
+            // waves of a block share a group's units: two where blocks are many, else eight
+            const int nrt = (LV.r + 15) / 16;
+            const int ex_rt = LV.aca && (int64_t)LV.exp_cnt.n * ((nrt + 3) / 4) >= 192 ? 4 : 1;
+            const int ex_chunks = (nrt + ex_rt - 1) / ex_rt;
+            const int ex_nw = ex_rt == 1 ? 16 : ((int64_t)LV.exp_cnt.n * ex_chunks < 4096 ? 8 : 2);
+            // its LDS: a group's units (in steps of 64, so that a batch's levels share launches), or the waves' tiles
+            const size_t ex_shmem = std::max((size_t)((LV.exp_max + 63) / 64 * 64) * 4 * (P.kernel == FFM_HELMHOLTZ ? 17 : 9),
+                                             (size_t)ex_nw * ex_rt * 256 * sizeof(float));
+            if (LV.aca) {
+                xcd_deal((LV.ngrp + 3) / 4, [&](int32_t b) { mf.push_back(make_int4(l, 4 * b, LV.ngrp, 0)); });
+                xcd_deal((int32_t)(LV.exp_cnt.n) * ex_chunks, [&](int32_t i) {
+                    ex.push_back(make_int4(l, i / ex_chunks, i % ex_chunks * ex_rt, 0));
+                });
+            } else {
+                xcd_deal(LV.ngrp, [&](int32_t g) { mf.push_back(make_int4(l, g, 0, 0)); });
             }
             // target boxes with many points in ranges of whole 256-point steps, about kInterpBlocks blocks in all
             const double per_blk = LV.pts_tgt / kInterpBlocks;
@@ -2355,13 +2493,17 @@ void plan_stages(Plan &P, const Tune &tu, hipStream_t st, Scratch *keep) {
             const int nwa = anterp_waves(LV.pts_src / std::max<double>(1.0, (double)LV.h_fwd.size()), P.dl);
             LV.stages.push_back(make_stage(P.dl ? K_ANTERP_DL : K_ANTERP, nwa, 0, s1, l, anterp_shmem(nwa, LV.r1, P.dl),
                                            std::move(an), st, SC));
-            if (LV.aca)
-                LV.stages.push_back(make_stage(K_ACA, std::min(4, LV.rp / 32), 0, s2, l, (size_t)LV.rp * 32 * 4,
-                                               std::move(mf), st, SC));
+            if (LV.aca) {
+                LV.stages.push_back(make_stage(K_ACA, 0, P.kernel == FFM_HELMHOLTZ, -1, l, 0, std::move(mf), st, SC));
+                LV.stages.push_back(make_stage(K_EXPAND, 100 * ex_rt + ex_nw, P.kernel == FFM_HELMHOLTZ, s2, l,
+                                               ex_shmem, std::move(ex), st, SC));
+            }
             else
                 LV.stages.push_back(make_stage(LV.fp16 ? K_MFMA16 : K_MFMA32, LV.fp16 ? 1 : std::min(4, LV.rp / 32), 0,
                                                s2, l, (size_t)LV.rp * 32 * (LV.fp16 ? 2 : 4), std::move(mf), st, SC));
-            LV.stages.push_back(make_stage(P.dn || P.grad ? K_INTERP_DN : K_INTERP, 0, 0, s3, l, sizeof(float2) * LV.r,
+            // one wave per block where target boxes hold at most a wave's worth and v~ takes few rows to gather
+            const bool one = (LV.aca || LV.r <= 64) && LV.pts_tgt <= 96.0 * (double)std::max<size_t>(1, LV.h_tgt.size());
+            LV.stages.push_back(make_stage(P.dn || P.grad ? K_INTERP_DN : K_INTERP, one ? 1 : 4, 0, s3, l, sizeof(float2) * LV.r,
                                            std::move(ip), st, SC));
         }
     }
@@ -2584,7 +2726,13 @@ LDesc make_desc(const Plan &P, int l, int inst, float2 *u, float2 *v, float *ama
     d.acaA = LV.acaA.p;
     d.acaB = LV.acaB.p;
     d.acaKp = LV.acaKp.p;
-    d.kpm = LV.kpm;
+    d.aca_kt = LV.aca_kt;
+    d.aca_nb = LV.aca_nb;
+    d.exp_tgt = LV.exp_tgt.p;
+    d.exp_ptr = LV.exp_ptr.p;
+    d.exp_cnt = LV.exp_cnt.p;
+    d.exp_cls = LV.exp_cls.p;
+    d.exp_e = LV.exp_e.p;
     d.grp_pair = LV.grp_pair.p;
     d.grp_cls = LV.grp_cls.p;
     d.ut2 = w.ut2;
@@ -2682,7 +2830,8 @@ size_t plan_device_bytes(const Plan &P) {
         b += L.far_ptr.bytes() + L.near_ptr.bytes() + L.far_src.bytes() + L.far_cls.bytes() + L.near_src.bytes() +
              L.T.bytes() + L.grp_pair.bytes() + L.grp_cls.bytes() + L.dirs.bytes() + L.dirs64.bytes() + L.D.bytes() +
              L.lnodes.bytes() + L.lden.bytes() + L.rings.bytes() + L.phis.bytes() + L.T16.bytes() + L.acaA.bytes() +
-             L.acaB.bytes() + L.acaKp.bytes() + L.Ez.bytes() +
+             L.acaB.bytes() + L.acaKp.bytes() + L.exp_tgt.bytes() + L.exp_ptr.bytes() + L.exp_cnt.bytes() + L.exp_cls.bytes() +
+             L.exp_e.bytes() + L.Ez.bytes() +
              L.Ex.bytes() + L.Ey.bytes() + L.ExT.bytes() + L.EyT.bytes() + L.gperm.bytes() + L.gzs.bytes() + L.gxyz.bytes() +
              L.tr_tgt.bytes() + L.gslot_s.bytes() + L.gslot_t.bytes() + L.near_off.bytes() + L.sib_tgt.bytes() + L.sib_src.bytes() + L.sib_cnt.bytes() +
              L.sib_cls.bytes();

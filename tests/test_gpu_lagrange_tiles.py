@@ -49,3 +49,26 @@ def test_points_per_box(orc, n, dl):
         gt = gpu_plan(Y, X, 0, 0.0, 1e-3, **kw)
         w2 = wu[:700]
         assert rel(gpu_apply(gt, w2), oracle_like(orc, gt, Y, X, 0, 0.0, 1e-3, **kw).apply(w2)) < FP32_RTOL
+
+
+@pytest.mark.parametrize("kernel,r1,eps,shift", [(0, 1, 1e-3, False), (0, 2, 1e-3, False), (0, 3, 1e-3, True),
+                                                 (0, 4, 1e-3, False), (1, 3, 1e-3, False), (1, 5, 1e-3, True),
+                                                 (0, 7, 1e-5, False), (1, 7, 1e-6, False)])
+def test_aca_tiles(orc, kernel, r1, eps, shift):
+    """The two ACA transfer kernels with ranks below and above one tile of 16, r1^3 below and above one tile of rows,
+    groups of targets that do not fill, and two shifted sets (more classes, most targets without most of them)."""
+    rng = np.random.default_rng(10 * r1 + kernel)
+    X = W.sphere_points(2503, rng)
+    Y = X if not shift else W.cube_points(1901, rng, (0.31, 0.17, -0.23), 1.7)
+    wu = ((rng.standard_normal(len(Y)) + 1j * rng.standard_normal(len(Y))) / len(Y)).astype(np.complex64)
+    k = 2.0 if kernel else 0.0
+    gp = gpu_plan(X, Y, kernel, k, eps, n_leaf=40, r1_override=r1, aca="on")
+    st = gp.stats()
+    lev = [l for l in range(1, st["leaf"] + 1) if st["aca"][l]]
+    assert lev
+    op = oracle_like(orc, gp, X, Y, kernel, k, eps, n_leaf=40, r1=r1)
+    v = gpu_apply(gp, wu)
+    print("kernel %d r1 %d eps %g shift %d: mean ranks %s, vs oracle %.3e"
+          % (kernel, r1, eps, shift, [round(st["aca_rank"][l], 1) for l in lev], rel(v, op.apply(wu))))
+    assert rel(v, op.apply(wu)) < FP32_RTOL
+    assert np.array_equal(v, gpu_apply(gp, wu))
