@@ -15,7 +15,6 @@
 #include <chrono>
 #include <map>
 #include <mutex>
-#include <thread>
 #include <tuple>
 #include <cmath>
 #include <complex>
@@ -613,6 +612,252 @@ k_fill_groups(const int32_t *cls, int64_t n, int64_t per_reg, int ncls, const in
     grp_pair[(int64_t)gstart[c] * 16 + slot] = (int32_t)i;
 }
 
+// ---- ACA of the transfer matrices of a Lagrange level (Sec. 2.2.2, eq. ffmACAmatvec): T_c ~ A_c B_c^T by cross
+// approximation with complete pivoting (Bebendorf), in FP64, one block per class.  Step k takes the largest entry
+// (i, j) of the residual R = T - sum of the terms so far, a_k = R(:, j), b_k = R(i, :) / R(i, j), and the rank is the
+// first k with |R|_F <= tol |T|_F, so every class meets the tolerance exactly.  The pivot is the first entry in
+// row-major order whose squared modulus is within a relative 2e-9 of the largest, so that entries equal up to
+// rounding (the tensor grid is symmetric) pick the same pivot on every machine.  R stays in global memory (746 KB at
+// r = 216, complex): each step is one read and write of it, in which the next step's sum and largest entry are
+// formed, with each lane's first candidate for the pivot.  The blocks' R together stay within
+// kAcaBytes, which the last-level cache holds.  The first `cap` columns of A and B go to FA and FB, [class][cap][r].
+// A 50,000-point Helmholtz plan with ACA at two levels (r = 216 and 125): 70 ms of 16 host threads -> 1.17 and 0.32 ms
+// here, bound by the traffic of R (6 TB/s).
+constexpr size_t kAcaBytes = (size_t)256 << 20;
+constexpr int kAcaThreads = 512;
+
+// A lane's largest value so far over the rows it walks, and the first row within a relative 2e-9 of it; unsure where a
+// later rise may have left an earlier row within that distance.
+struct Largest {
+    double mx = 0.0, qf = 0.0;
+    int row = 0;
+    bool unsure = false;
+    __device__ __forceinline__ void add(double q, int i) {
+        if (q > mx) {
+            const double thr = (1.0 - 2e-9) * q;
+            if (qf < thr) {
+                unsure = mx >= thr;
+                qf = q;
+                row = i;
+            }
+            mx = q;
+        }
+    }
+};
+
+// NJ: 64-column pieces of a row (r <= 64 NJ).  A wave walks every nw-th row, its lanes holding their columns' b.
+template <bool HELM, int NJ>
+__global__ void __launch_bounds__(kAcaThreads, 4)
+k_aca(int ncls, const double *r0, const double *nodes, int r1, double dl, double k, double tol, int cap, double *Rall,
+      float *FA, float *FB, int32_t *ranks) {
+#pragma clang fp contract(off)
+    constexpr int P = HELM ? 2 : 1, RU = NJ <= 2 ? 4 : 2;      // planes; rows loaded ahead of their use
+    extern __shared__ double acasm[];               // a and b (r entries each), then the waves' partial results
+    const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, nw = nt >> 6;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = r1 * r1 * r1, n = r * r;
+    double *sa = acasm, *sb = sa + P * r, *ssum = sb + P * r, *smax = ssum + 16;
+    __shared__ int spiv;
+    double *R = Rall + (size_t)blockIdx.x * n * P;
+    auto sq = [&](const double (&v)[P]) { return HELM ? v[0] * v[0] + v[P - 1] * v[P - 1] : v[0] * v[0]; };
+    auto get = [&](int e, double (&v)[P]) {
+        if (HELM) {
+            const double2 w = reinterpret_cast<const double2 *>(R)[e];
+            v[0] = w.x;
+            v[P - 1] = w.y;
+        } else {
+            v[0] = R[e];
+        }
+    };
+    auto put = [&](int e, const double (&v)[P]) {
+        if (HELM) reinterpret_cast<double2 *>(R)[e] = make_double2(v[0], v[P - 1]);
+        else R[e] = v[0];
+    };
+    for (int c = blockIdx.x; c < ncls; c += gridDim.x) {
+        Largest big;
+        double sum = 0.0;
+        double nj[NJ][3];                            // the columns' node coordinates
+#pragma unroll
+        for (int h = 0; h < NJ; ++h) {
+            const int j = min(64 * h + lane, r - 1);
+            nj[h][0] = nodes[j / (r1 * r1)];
+            nj[h][1] = nodes[(j / r1) % r1];
+            nj[h][2] = nodes[j % r1];
+        }
+        for (int i = wv; i < r; i += nw) {
+            const double ni[3] = {nodes[i / (r1 * r1)], nodes[(i / r1) % r1], nodes[i % r1]};
+            double rowmax = 0.0;
+#pragma unroll
+            for (int h = 0; h < NJ; ++h) {
+                const int j = 64 * h + lane;
+                double dd[3];
+                for (int d = 0; d < 3; ++d) dd[d] = r0[3 * c + d] + 0.5 * dl * (ni[d] - nj[h][d]);
+                const double rr = sqrt(dd[0] * dd[0] + dd[1] * dd[1] + dd[2] * dd[2]);
+                const double inv = 1.0 / (4.0 * M_PI * rr);
+                double v[P];
+                v[0] = inv;
+                if (HELM) {
+                    double sn, cs;
+                    sincos(k * rr, &sn, &cs);
+                    v[0] = cs * inv;
+                    v[P - 1] = sn * inv;
+                }
+                if (j < r) {
+                    put(i * r + j, v);
+                    const double q = sq(v);
+                    sum += q;
+                    rowmax = fmax(rowmax, q);
+                }
+            }
+            big.add(rowmax, i);
+        }
+        double t2 = 0.0;
+        int rank = 0;
+        for (;;) {
+            // |R|_F^2 and the largest squared modulus over the block
+            double bs = sum, bm = big.mx;
+            for (int o = 32; o; o >>= 1) {
+                bs += __shfl_xor(bs, o, 64);
+                bm = fmax(bm, __shfl_xor(bm, o, 64));
+            }
+            __syncthreads();                         // (the last step's readers of the partial results are done)
+            if (lane == 0) {
+                ssum[wv] = bs;
+                smax[wv] = bm;
+            }
+            if (tid == 0) spiv = n;
+            __syncthreads();
+            bs = bm = 0.0;
+            for (int w = 0; w < nw; ++w) {
+                bs += ssum[w];
+                bm = fmax(bm, smax[w]);
+            }
+            if (rank == 0) t2 = bs;
+            if (rank >= r || bs <= tol * tol * t2 || bm == 0.0) break;
+            const double thr = (1.0 - 2e-9) * bm;
+            if (big.mx >= thr) {
+                // this lane holds a candidate: its first row within reach (all its rows where that is unsure)
+                const bool sure = big.qf >= thr && !big.unsure;
+                for (int i = sure ? big.row : wv; i < r; i += nw) {
+                    int at = n;
+#pragma unroll
+                    for (int h = NJ - 1; h >= 0; --h) {
+                        const int j = 64 * h + lane;
+                        if (j < r) {
+                            double v[P];
+                            get(i * r + j, v);
+                            if (sq(v) >= thr) at = i * r + j;
+                        }
+                    }
+                    if (at < n) atomicMin(&spiv, at);
+                    if (sure || at < n) break;
+                }
+            }
+            __syncthreads();
+            const int piv = spiv, pi = piv / r, pj = piv - pi * r;
+            for (int q = tid; q < r; q += nt) {
+                const size_t f = (((size_t)c * cap + rank) * r + q) * P;
+                double x[P], y[P], pv[P];
+                get(q * r + pj, x);
+                get(pi * r + q, y);
+                get(piv, pv);
+                if (HELM) {
+                    const double pn = pv[0] * pv[0] + pv[P - 1] * pv[P - 1];
+                    const double re = (y[0] * pv[0] + y[P - 1] * pv[P - 1]) / pn, im = (y[P - 1] * pv[0] - y[0] * pv[P - 1]) / pn;
+                    y[0] = re;
+                    y[P - 1] = im;
+                } else {
+                    y[0] = y[0] / pv[0];
+                }
+                for (int p = 0; p < P; ++p) {
+                    sa[P * q + p] = x[p];
+                    sb[P * q + p] = y[p];
+                    if (rank < cap) {
+                        FA[f + p] = (float)x[p];
+                        FB[f + p] = (float)y[p];
+                    }
+                }
+            }
+            __syncthreads();
+            double b[NJ][P];
+#pragma unroll
+            for (int h = 0; h < NJ; ++h)
+                for (int p = 0; p < P; ++p) b[h][p] = sb[P * min(64 * h + lane, r - 1) + p];
+            sum = 0.0;
+            big = Largest();
+            for (int i0 = wv; i0 < r; i0 += RU * nw) {
+                double v[RU][NJ][P];
+#pragma unroll
+                for (int q = 0; q < RU; ++q)
+#pragma unroll
+                    for (int h = 0; h < NJ; ++h) get(min(i0 + q * nw, r - 1) * r + min(64 * h + lane, r - 1), v[q][h]);
+#pragma unroll
+                for (int q = 0; q < RU; ++q) {
+                    const int i = i0 + q * nw;
+                    if (i >= r) break;
+                    const double ax = sa[P * i], ay = sa[P * i + P - 1];
+                    double rowmax = 0.0;
+#pragma unroll
+                    for (int h = 0; h < NJ; ++h) {
+                        double w[P];
+                        if (HELM) {
+                            w[0] = v[q][h][0] - (ax * b[h][0] - ay * b[h][P - 1]);
+                            w[P - 1] = v[q][h][P - 1] - (ax * b[h][P - 1] + ay * b[h][0]);
+                        } else {
+                            w[0] = v[q][h][0] - ax * b[h][0];
+                        }
+                        if (64 * h + lane < r) {
+                            put(i * r + 64 * h + lane, w);
+                            const double m = sq(w);
+                            sum += m;
+                            rowmax = fmax(rowmax, m);
+                        }
+                    }
+                    big.add(rowmax, i);
+                }
+            }
+            ++rank;
+        }
+        if (tid == 0) ranks[c] = rank;
+    }
+}
+
+typedef void (*AcaFn)(int, const double *, const double *, int, double, double, double, int, double *, float *, float *,
+                      int32_t *);
+AcaFn aca_kernel(bool helm, int r1) {
+    if (r1 <= 4) return helm ? k_aca<true, 1> : k_aca<false, 1>;
+    if (r1 == 5) return helm ? k_aca<true, 2> : k_aca<false, 2>;
+    if (r1 == 6) return helm ? k_aca<true, 4> : k_aca<false, 4>;
+    if (r1 == 7) return helm ? k_aca<true, 6> : k_aca<false, 6>;
+    return helm ? k_aca<true, 8> : k_aca<false, 8>;
+}
+
+// The factors in the fragment orders of the transfer kernels (LDesc::acaA, acaB), zero beyond each class's rank and
+// beyond r: rank q = 16 kb + 4 u + g sits at position 4 g + u of its tile.  Both arrays are [.][64 lanes][4], one
+// thread per element of either; A: row i % 16 and g from the lane, u the step; B^T: the position and the node's
+// step group from the lane, i % 4 the step.
+template <bool HELM>
+__global__ void __launch_bounds__(kThreads)
+k_aca_pack(int ncls, int r, int kt, int nrt, int nb, int cap, float sA, const float *FA, const float *FB, const int32_t *ranks,
+           float *A, float *B) {
+    constexpr int P = HELM ? 2 : 1;
+    const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    const int u = (int)(t & 3), lane = (int)(t >> 2) & 63;
+    const int64_t blk = t >> 8;
+    if (blk < (int64_t)ncls * kt * nrt * P) {          // A [class][kb][row tile][plane]
+        const int pl = (int)(blk % P), rt = (int)(blk / P % nrt), kb = (int)(blk / P / nrt % kt);
+        const int c = (int)(blk / P / nrt / kt);
+        const int q = 16 * kb + 4 * u + (lane >> 4), i = 16 * rt + (lane & 15);
+        A[t] = q < ranks[c] && i < r ? sA * FA[(((size_t)c * cap + q) * r + i) * P + pl] : 0.f;
+    }
+    if (blk < (int64_t)ncls * P * kt * nb) {           // B [class][plane][kb][jb]
+        const int jb = (int)(blk % nb), kb = (int)(blk / nb % kt), pl = (int)(blk / nb / kt % P);
+        const int c = (int)(blk / nb / kt / P);
+        const int pos = lane & 15, q = 16 * kb + 4 * (pos & 3) + (pos >> 2), i = 16 * jb + 4 * (lane >> 4) + u;
+        B[t] = q < ranks[c] && i < r ? FB[(((size_t)c * cap + q) * r + i) * P + pl] : 0.f;
+    }
+}
+
 // The classes that occur in a target group (G boxes) of k_lag_expand, ascending, with each target's far pair of the
 // class: a table in LDS, then its non-empty rows in order (one wave, by lane scans).
 template <int G>
@@ -1011,74 +1256,6 @@ void hankel_host(int L, double z, std::vector<std::complex<double>> &h) {
     if (L >= 1) h[1] = -e * (z + I) / (z * z);
     for (int p = 1; p < L; ++p) h[p + 1] = (2.0 * p + 1.0) / z * h[p] - h[p - 1];
 }
-
-// ---- ACA of the transfer matrices of a Lagrange level (Sec. 2.2.2, eq. ffmACAmatvec): T_c ~ A_c B_c^T by cross
-// approximation with complete pivoting (Bebendorf), in FP64 on the host.  Step k takes the largest entry (i, j)
-// of the residual R = T - sum of the terms so far, a_k = R(:, j), b_k = R(i, :) / R(i, j), and the rank is the
-// first k with |R|_F <= tol |T|_F, so every class meets the tolerance exactly.  The pivot is the first entry in
-// row-major order whose squared modulus is within a relative 2e-9 of the largest, so that entries equal up to
-// rounding (the tensor grid is symmetric) pick the same pivot on every machine.
-namespace {
-typedef std::complex<double> cd;
-
-cd transfer_entry(const double *r0, const double *nodes, double dl, int r1, int helm, double k, int i, int j) {
-#pragma clang fp contract(off)
-    const int ia[3] = {i / (r1 * r1), (i / r1) % r1, i % r1};
-    const int ja[3] = {j / (r1 * r1), (j / r1) % r1, j % r1};
-    double dd[3];
-    for (int d = 0; d < 3; ++d) dd[d] = r0[d] + 0.5 * dl * (nodes[ia[d]] - nodes[ja[d]]);
-    const double rr = std::sqrt(dd[0] * dd[0] + dd[1] * dd[1] + dd[2] * dd[2]);
-    if (!helm) return cd(1.0 / (4.0 * M_PI * rr), 0.0);
-    return cd(std::cos(k * rr) / (4.0 * M_PI * rr), std::sin(k * rr) / (4.0 * M_PI * rr));
-}
-
-// Columns of A and B (r entries each, column after column); returns the rank.
-int aca_class(const double *r0, const double *nodes, double dl, int r1, int helm, double k, double tol,
-              std::vector<cd> &A, std::vector<cd> &B) {
-#pragma clang fp contract(off)
-    const int r = r1 * r1 * r1;
-    const size_t rr = (size_t)r * r;
-    A.clear();
-    B.clear();
-    std::vector<cd> R(rr);
-    double T2 = 0.0;
-    for (int i = 0; i < r; ++i)
-        for (int j = 0; j < r; ++j) {
-            const cd t = transfer_entry(r0, nodes, dl, r1, helm, k, i, j);
-            R[(size_t)i * r + j] = t;
-            T2 += t.real() * t.real() + t.imag() * t.imag();
-        }
-    int rank = 0;
-    while (rank < r) {
-        double R2 = 0.0, m = 0.0;
-        for (size_t e = 0; e < rr; ++e) {
-            const double q = R[e].real() * R[e].real() + R[e].imag() * R[e].imag();
-            R2 += q;
-            m = std::max(m, q);
-        }
-        if (R2 <= tol * tol * T2 || m == 0.0) break;
-        size_t piv = 0;
-        for (size_t e = 0; e < rr; ++e)
-            if (R[e].real() * R[e].real() + R[e].imag() * R[e].imag() >= (1.0 - 2e-9) * m) {
-                piv = e;
-                break;
-            }
-        const int pi = (int)(piv / r), pj = (int)(piv % r);
-        const cd pv = R[piv];
-        const size_t a0 = A.size();
-        for (int q = 0; q < r; ++q) {
-            A.push_back(R[(size_t)q * r + pj]);
-            B.push_back(R[(size_t)pi * r + q] / pv);
-        }
-        for (int i = 0; i < r; ++i) {
-            const cd ai = A[a0 + i];
-            for (int j = 0; j < r; ++j) R[(size_t)i * r + j] -= ai * B[a0 + j];
-        }
-        ++rank;
-    }
-    return rank;
-}
-}  // namespace
 
 int lagrange_r1(int kernel, double k, double dl, double eps, int override_r1) {
     if (override_r1 > 0) return override_r1;
@@ -1619,6 +1796,12 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
     }
     // --- compression form and tables per level (Sec. 2.2.2, 2.2.3)
     size_t ws_src = 0, ws_tgt = 0, ws_z = 0, ws_part = 0, ws_gG = 0, ws_gH = 0;
+    struct {                               // the last level's ACA factors (k_aca)
+        int level = 0, r1 = 0;
+        DevBuf<float> FA, FB;
+        DevBuf<int32_t> rank;
+        int32_t *rank_h = nullptr;
+    } aca;
     for (int l = 1; l <= P.leaf; ++l) {
         Level &LV = P.lev[l];
         if (LV.nfar == 0) continue;
@@ -1850,6 +2033,34 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
             DevBuf<int32_t> cnt(nbin), cursor(nbin);
             FFM_HIP(hipMemsetAsync(cnt.p, 0, sizeof(int32_t) * nbin, st));
             FFM_LAUNCH(k_count_cls, nblocks(LV.nfar), kThreads, 0, st, LV.far_cls.p, LV.nfar, per_reg, LV.ncls, cnt.p);
+            // ACA of the transfer matrices (eq. ffmACAmatvec, relative tolerance eps / 4) where it saves MFMA work: a pair
+            // costs 2 rp kp multiply-adds, kp its class's rank in whole 32-row tiles (at most one per four waves of 32
+            // rows: ranks up to aca_cap), instead of rp^2.  Not at FP16 levels (FP16 runs 16x the FP32 rate on full
+            // matrices) nor below r1 = 5 (r = 64: one 32-row tile already costs as much as T).  The factorisation runs
+            // while the class counts come back
+            const bool force_aca = (P.opt.flags & FFM_FLAG_ACA) != 0;
+            const bool try_aca = !LV.fp16 && !(P.opt.flags & FFM_FLAG_NO_ACA) && (LV.r1 >= 5 || force_aca);
+            const int aca_cap = 32 * std::min(4, LV.rp / 32);
+            // (Laplace levels of trees with one corner: T_c scales with 1 / d_l, a power of two, so a level with the
+            // last factored level's classes and nodes takes its factors, A times that power: the same numbers)
+            const bool reuse = try_aca && !helm && P.aligned && aca.level > 0 && aca.r1 == LV.r1 &&
+                               P.lev[aca.level].cls_off == LV.cls_off;
+            DevBuf<double> aca_R;
+            if (try_aca && !reuse) {
+                const size_t planes = helm ? 2 : 1, per_blk = (size_t)LV.r * LV.r * planes;
+                const int nblk = (int)std::min<size_t>(LV.ncls, std::max<size_t>(1, kAcaBytes / (per_blk * sizeof(double))));
+                aca_R.alloc(nblk * per_blk);
+                aca.FA.alloc((size_t)LV.ncls * aca_cap * LV.r * planes);
+                aca.FB.alloc((size_t)LV.ncls * aca_cap * LV.r * planes);
+                aca.rank.alloc(LV.ncls);
+                aca.rank_h = SC.pin<int32_t>(LV.ncls);
+                aca.level = l;
+                aca.r1 = LV.r1;
+                FFM_LAUNCH(aca_kernel(helm, LV.r1), nblk, kAcaThreads, (2 * planes * LV.r + 32) * sizeof(double), st,
+                           LV.ncls, dr0.p, dnodes.p, LV.r1, dl, P.k, P.eps / 4.0, aca_cap, aca_R.p, aca.FA.p, aca.FB.p,
+                           aca.rank.p);
+                FFM_HIP(hipMemcpyAsync(aca.rank_h, aca.rank.p, sizeof(int32_t) * LV.ncls, hipMemcpyDeviceToHost, st));
+            }
             std::vector<int32_t> hb(nbin), hc(LV.ncls, 0), gstart(nbin), gcls;
             FFM_HIP(hipMemcpyAsync(hb.data(), cnt.p, sizeof(int32_t) * nbin, hipMemcpyDeviceToHost, st));
             FFM_HIP(hipStreamSynchronize(st));
@@ -1862,70 +2073,31 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
                 g += ng;
             }
             LV.ngrp = g;
-            // ACA of the transfer matrices (eq. ffmACAmatvec, relative tolerance eps / 4) where it saves MFMA work:
-            // each class's rank padded to whole 32-row tiles, at most one tile per wave of the transfer block; a
-            // pair then costs 2 rp kp instead of rp^2 multiply-adds.  Not at FP16 levels (FP16 runs 16x the FP32
-            // rate on full matrices) nor below r1 = 5 (r = 64: one 32-row tile already costs as much as T).
             LV.aca = false;
             const int32_t *exp_cnt = nullptr;
-            const int nwv = std::min(4, LV.rp / 32);
-            const bool force_aca = (P.opt.flags & FFM_FLAG_ACA) != 0;
-            if (!LV.fp16 && !(P.opt.flags & FFM_FLAG_NO_ACA) && (LV.r1 >= 5 || force_aca)) {
-                const double tol = P.eps / 4.0;
-                std::vector<std::vector<cd>> Af(LV.ncls), Bf(LV.ncls);
-                std::vector<int> rank(LV.ncls, 0);
-                std::atomic<int> next{0};
-                auto worker = [&] {
-                    for (int c = next++; c < LV.ncls; c = next++)
-                        rank[c] = aca_class(&r0[3 * (size_t)c], nodes.data(), dl, LV.r1, helm, P.k, tol, Af[c], Bf[c]);
-                };
-                const int nth = (int)std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
-                std::vector<std::thread> pool;
-                for (int t = 1; t < nth; ++t) pool.emplace_back(worker);
-                worker();
-                for (auto &t : pool) t.join();
-                int kpm = 32;
+            const int32_t *rank_h = aca.rank_h;
+            if (try_aca) {
+                int rmax = 1;
                 double cost_t = 0.0, cost_a = 0.0, rank_sum = 0.0;
-                std::vector<int32_t> kp(LV.ncls);
                 for (int c = 0; c < LV.ncls; ++c) {
-                    kp[c] = std::max(32, (rank[c] + 31) / 32 * 32);
-                    kpm = std::max(kpm, kp[c]);
                     const double ng = (hc[c] + 15) / 16;
+                    rmax = std::max(rmax, rank_h[c]);
                     cost_t += ng * (double)per;
-                    cost_a += ng * 2.0 * LV.rp * kp[c];
-                    rank_sum += rank[c];
+                    cost_a += ng * 2.0 * LV.rp * std::max(32, (rank_h[c] + 31) / 32 * 32);
+                    rank_sum += rank_h[c];
                 }
-                LV.aca = kpm <= 32 * nwv && (force_aca || cost_a <= 0.75 * cost_t);
+                LV.aca = rmax <= aca_cap && (force_aca || cost_a <= 0.75 * cost_t);
                 LV.aca_rank = LV.ncls ? rank_sum / LV.ncls : 0.0;
                 if (LV.aca) {
-                    const int r = LV.r, planes = helm ? 2 : 1;
-                    const int rmax = *std::max_element(rank.begin(), rank.end());
-                    const int kt = LV.aca_kt = std::max(1, (rmax + 15) / 16), nrt = (r + 15) / 16;
-                    const int nb = LV.aca_nb = LV.rp / 16;
-                    LV.aca_ranks.assign(rank.begin(), rank.end());
-                    std::vector<float> ha((size_t)LV.ncls * kt * nrt * planes * 256, 0.f);
-                    std::vector<float> hf((size_t)LV.ncls * planes * kt * nb * 256, 0.f);
-                    for (int c = 0; c < LV.ncls; ++c)
-                        for (int q = 0; q < rank[c]; ++q)
-                            for (int i = 0; i < r; ++i) {
-                                const cd a = Af[c][(size_t)q * r + i], b = Bf[c][(size_t)q * r + i];
-                                // rank q = 16 kb + 4 u + g at position 4 g + u of its tile.  A: row i % 16, lane
-                                // group g, step u; B^T: the position as row, node i as lane group and step
-                                const int kb = q / 16, u = (q % 16) / 4, g = q % 4, pos = 4 * g + u;
-                                const size_t ia = (((size_t)c * kt + kb) * nrt + i / 16) * planes * 256 +
-                                                  (i % 16 + 16 * g) * 4 + u;
-                                const size_t ib = (((size_t)c * planes * kt + kb) * nb + i / 16) * 256 +
-                                                  (pos + 16 * ((i % 16) / 4)) * 4 + i % 4;
-                                ha[ia] = (float)a.real();
-                                hf[ib] = (float)b.real();
-                                if (helm) {
-                                    ha[ia + 256] = (float)a.imag();
-                                    hf[ib + (size_t)kt * nb * 256] = (float)b.imag();
-                                }
-                            }
-                    upload(LV.acaA, ha, st, SC);
-                    upload(LV.acaB, hf, st, SC);
+                    const int r = LV.r, planes = helm ? 2 : 1, nrt = (r + 15) / 16;
+                    const int kt = LV.aca_kt = (rmax + 15) / 16, nb = LV.aca_nb = LV.rp / 16;
+                    LV.aca_ranks.assign(rank_h, rank_h + LV.ncls);
+                    LV.acaA.alloc((size_t)LV.ncls * kt * nrt * planes * 256);
+                    LV.acaB.alloc((size_t)LV.ncls * planes * kt * nb * 256);
                     upload(LV.acaKp, LV.aca_ranks, st, SC);
+                    FFM_LAUNCH((helm ? k_aca_pack<true> : k_aca_pack<false>), (int)std::max(LV.acaA.n, LV.acaB.n) / kThreads,
+                               kThreads, 0, st, LV.ncls, r, kt, nrt, nb, aca_cap, (float)std::ldexp(1.0, l - aca.level), aca.FA.p, aca.FB.p,
+                               LV.acaKp.p, LV.acaA.p, LV.acaB.p);
                     exp_cnt = expand_lists(LV, helm ? 16 : 8, st, SC);
                 }
             }
