@@ -2903,7 +2903,12 @@ k_lag_interp_dn(const LDesc *__restrict__ descs, const IoEntry *__restrict__, co
 }
 
 // ------------------------------------------------------------------ near field (leaf)
-// v_i += sum_{s in near(t)} sum_{j in s, r_ij > 0} G(r_ij) u_j.  One 64-lane block per target box.  Source points
+// v_i += sum_{s in near(t)} sum_{j in s, r_ij > 0} G(r_ij) u_j.  One block per target box, of one wave or, where boxes
+// are too few to fill the chip, of two to eight, which share the box's source chunks (plan.hip, near_waves).  A chunk
+// whose list entry, range and points were fetched one after the other cost three memory latencies, more than its
+// evaluation: with the list in LDS and the next chunk's points loaded ahead, and the waves, 26 -> 14 us for 4096 points
+// (Laplace, 260 boxes), 150 -> 55 for 50,000 (1295 boxes), 237 -> 171 for 262,000 (4636), 536 -> 469 for 1M (18,354,
+// one wave each), 4.4 -> 3.1 ms for 10M (Helmholtz, symmetric pass).  Source points
 // are staged through LDS in chunks of 64, in FP64 relative to the target centre, and every pair's difference is
 // formed in FP64 and rounded once to FP32, so close pairs keep the full FP32 relative accuracy of r.  Helmholtz
 // coordinates are scaled by k / 2 pi when staged (r then reads in revolutions, the phase of e^{ikr}), and the
@@ -2963,22 +2968,119 @@ struct NearSmem {
     float2 sp[kNearSlots];                                 // source-side sums of a chunk (symmetric pairs)
 };
 
-// Stage the chunk's sources c0 ... c0 + cnt - 1 (relative to the target centre, scaled) for R lane rows of
-// `steps` sources each: source jj at slot (jj / steps) * so + jj % steps, zero sources in the slots of
-// cnt <= jj < R * steps (at most 127).  d.two_over_dl is 2 / d_l of the descriptor's level.  With snm, the
-// source normals nsrc[j] times nsign go to snm[slot] (the double layer stages the negated source normals:
-// n_y . grad_y G(x - y) = (-n_y) . grad_x G(x - y)).
-__device__ __forceinline__ void near_stage_chunk(const LDesc &d, NearSmem &sm, int c0, int cnt, int R, int steps,
+// The chunks of a box's near list, numbered in list order, every chunk at most 64 sources of one box.  A wave reads
+// the list's entries at once, one per lane, into its LDS, so finding a chunk's box and range takes no memory access,
+// and a chunk's sources are loaded into registers while the chunk before is evaluated; the waves of a block take
+// every nw-th chunk.
+struct NearChunk {
+    int s, c0, cnt, rel;          // source box, first source, sources, first source's position in its box
+    int64_t off;                  // symmetric lists: the entry's near_off
+};
+
+struct NearRegs {                 // one source per lane
+    double x, y, z;
+    float2 u;
+    float4 n;
+};
+
+struct NearList {                 // one entry per lane, in the wave's LDS
+    int64_t off[64];
+    int s[64], j0[64], j1[64], incl[64];      // incl: chunks up to and including the entry's
+};
+
+// SYM: lower neighbours with a reverse entry are left out (their own block evaluates the pair of boxes).  Returns the
+// number of chunks.
+template <bool SYM>
+__device__ __forceinline__ int near_list(const LDesc &d, NearList &w, int t, int64_t e, int64_t e1) {
+    const int lane = threadIdx.x & 63;
+    const bool on = e + lane < e1;
+    const int64_t el = on ? e + lane : e;
+    const int s = d.near_src[el];
+    const int64_t off = SYM ? d.near_off[el] : -1;
+    const int j0 = d.sstart[s], j1 = d.sstart[s + 1];
+    int n = !on || (SYM && s < t && off >= 0) ? 0 : (j1 - j0 + 63) >> 6;
+    for (int k = 1; k < 64; k <<= 1) {
+        const int v = __shfl_up(n, k, 64);
+        if (lane >= k) n += v;
+    }
+    wave_lds_fence();
+    w.s[lane] = s;
+    w.j0[lane] = j0;
+    w.j1[lane] = j1;
+    w.incl[lane] = n;
+    if (SYM) w.off[lane] = off;
+    wave_lds_fence();
+    return __builtin_amdgcn_readlane(n, 63);
+}
+
+template <bool SYM>
+__device__ __forceinline__ NearChunk near_chunk(const NearList &w, int q) {
+    const int e = __popcll(__ballot(w.incl[threadIdx.x & 63] <= q));
+    NearChunk c;
+    c.s = __builtin_amdgcn_readfirstlane(w.s[e]);
+    c.rel = 64 * (q - (e ? __builtin_amdgcn_readfirstlane(w.incl[e - 1]) : 0));
+    c.c0 = __builtin_amdgcn_readfirstlane(w.j0[e]) + c.rel;
+    c.cnt = min(64, __builtin_amdgcn_readfirstlane(w.j1[e]) - c.c0);
+    c.off = -1;
+    if (SYM) {
+        const int64_t o = w.off[e];
+        c.off = ((int64_t)__builtin_amdgcn_readfirstlane((int)(o >> 32)) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane((int)o);
+    }
+    return c;
+}
+
+template <bool NRM>
+__device__ __forceinline__ void near_load(const LDesc &d, const NearChunk &c, const float4 *nsrc, NearRegs &r) {
+    const int j = c.c0 + min((int)(threadIdx.x & 63), c.cnt - 1);
+    r.x = d.sxs[j];
+    r.y = d.sys[j];
+    r.z = d.szs[j];
+    r.u = d.u[j];
+    if (NRM) r.n = nsrc[j];
+}
+
+// Walk this wave's chunks of box t's near list: stage(chunk, registers), then compute(chunk).
+template <bool SYM, bool NRM, class Stage, class Compute>
+__device__ __forceinline__ void near_walk(const LDesc &d, NearList &w, int t, const float4 *nsrc, Stage &&stage,
+                                          Compute &&compute) {
+    const int nw = blockDim.x >> 6;
+    const int64_t e1 = d.near_ptr[t + 1];
+    for (int64_t e = d.near_ptr[t]; e < e1; e += 64) {
+        const int total = near_list<SYM>(d, w, t, e, e1);
+        int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        if (q >= total) continue;
+        NearChunk cur = near_chunk<SYM>(w, q);
+        NearRegs r;
+        near_load<NRM>(d, cur, nsrc, r);
+        for (;;) {
+            const NearChunk c = cur;
+            stage(c, r);
+            q += nw;
+            const bool more = q < total;
+            if (more) {
+                cur = near_chunk<SYM>(w, q);
+                near_load<NRM>(d, cur, nsrc, r);
+            }
+            compute(c);
+            if (!more) break;
+        }
+    }
+}
+
+// Stage a chunk's sources (relative to the target centre, scaled) for R lane rows of `steps` sources each: source jj
+// at slot (jj / steps) * so + jj % steps, zero sources in the slots of cnt <= jj < R * steps (at most 127).
+// d.two_over_dl is 2 / d_l of the descriptor's level.  With snm, the source normals times nsign go to snm[slot] (the
+// double layer stages the negated source normals: n_y . grad_y G(x - y) = (-n_y) . grad_x G(x - y)).
+__device__ __forceinline__ void near_stage_chunk(const LDesc &d, NearSmem &sm, const NearRegs &r, int cnt, int R, int steps,
                                                  int so, double cx, double cy, double cz, double scale,
-                                                 float uscale, float4 *snm, const float4 *nsrc = nullptr,
-                                                 float nsign = -1.f) {
-    const int lane = threadIdx.x;
+                                                 float uscale, float4 *snm, float nsign = -1.f) {
+    const int lane = threadIdx.x & 63;
     // zero sources sit at (2, 2, 2) d_l from the target centre: no target is there (each lies within d_l / 2 of
     // its centre on every axis), so every pair with them has r > 0 and adds exactly zero, and their phases stay
     // within the bound of the level's near pairs
     const double pad = 4.0 / d.two_over_dl * scale;
     const uint32_t mul = (65536u + (uint32_t)steps - 1u) / (uint32_t)steps;   // jj / steps for jj < 128
-    __syncthreads();
+    wave_lds_fence();
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const int jj = lane + 64 * h;
@@ -2986,21 +3088,61 @@ __device__ __forceinline__ void near_stage_chunk(const LDesc &d, NearSmem &sm, i
             const int qd = (int)(((uint32_t)jj * mul) >> 16);
             const int slot = qd * so + (jj - qd * steps);
             if (jj < cnt) {
-                const int j = c0 + jj;
-                sm.x[slot] = (d.sxs[j] - cx) * scale;
-                sm.y[slot] = (d.sys[j] - cy) * scale;
-                sm.z[slot] = (d.szs[j] - cz) * scale;
-                const float2 uu = d.u[j];
-                sm.u[slot] = make_float2(uu.x * uscale, uu.y * uscale);
-                if (snm) {
-                    const float4 n = nsrc[j];
-                    snm[slot] = make_float4(nsign * n.x, nsign * n.y, nsign * n.z, 0.f);
-                }
+                sm.x[slot] = (r.x - cx) * scale;
+                sm.y[slot] = (r.y - cy) * scale;
+                sm.z[slot] = (r.z - cz) * scale;
+                sm.u[slot] = make_float2(r.u.x * uscale, r.u.y * uscale);
+                if (snm) snm[slot] = make_float4(nsign * r.n.x, nsign * r.n.y, nsign * r.n.z, 0.f);
             } else {
                 sm.x[slot] = sm.y[slot] = sm.z[slot] = pad;   // padding: zero sources
                 sm.u[slot] = make_float2(0.f, 0.f);
                 if (snm) snm[slot] = make_float4(0.f, 0.f, 0.f, 0.f);
             }
+        }
+    }
+    wave_lds_fence();
+}
+
+// A wave's LDS of the near-field kernels: the staged chunk, with normals (NRM 1, 2 of the kernels that stage them) or
+// the source-side sums of a gradient's other two components.
+template <int NRM, bool SYM>
+struct NearWave {
+    NearSmem sm;
+    NearList list;
+    float4 snm[(SYM ? NRM == 1 || NRM == 2 : NRM == 2) ? kNearSlots : 1];
+    float2 sp12[SYM && NRM == 3 ? 2 : 1][SYM && NRM == 3 ? kNearSlots : 1];
+};
+extern __shared__ __align__(16) char near_raw[];
+
+// Add a pass's sums to the output: every wave's partial sums a[k] of its lanes go to its LDS, and the first wave adds,
+// per target, the waves' R partial sums each in order.
+template <class W, int T>
+__device__ __forceinline__ void near_reduce(W *waves, const float (&are)[T], const float (&aim)[T], int g, int R, int nt,
+                                            float2 *out) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    float2 *part = reinterpret_cast<float2 *>(waves[wv].sm.x);   // [T][64], over x, y, z and u (T <= 5)
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < T; ++k) part[k * 64 + lane] = make_float2(are[k], aim[k]);
+    __syncthreads();
+    if (wv == 0 && lane < g) {
+#pragma unroll
+        for (int k = 0; k < T; ++k) {
+            const int ti = lane + g * k;
+            if (ti >= nt) break;
+            float2 a = make_float2(0.f, 0.f);
+            for (int w = 0; w < nw; ++w) {
+                const float2 *pw = reinterpret_cast<const float2 *>(waves[w].sm.x) + k * 64 + lane;
+                for (int rr = 0; rr < R; ++rr) {
+                    const float2 b = pw[rr * g];
+                    a.x += b.x;
+                    a.y += b.y;
+                }
+            }
+            float2 o = out[ti];
+            o.x += a.x;
+            o.y += a.y;
+            out[ti] = o;
         }
     }
     __syncthreads();
@@ -3080,9 +3222,11 @@ __device__ __forceinline__ void near_range(const NearSmem &sm, const float4 *snm
 
 // One pass: targets i0 ... i0 + nt - 1 of box t, T per lane.
 template <bool HELM, int NRM, bool BIG, int T>
-__device__ __forceinline__ void near_pass(const LDesc &d, NearSmem &sm, float4 *snm, int t, int i0, int nt,
+__device__ __forceinline__ void near_pass(const LDesc &d, NearWave<NRM, false> *waves, int t, int i0, int nt,
                                           double scale, float uscale) {
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    NearSmem &sm = waves[threadIdx.x >> 6].sm;
+    float4 *snm = waves[threadIdx.x >> 6].snm;
     const int g = __builtin_amdgcn_readfirstlane((nt + T - 1) / T), R = __builtin_amdgcn_readfirstlane(64 / g);
     const int r = lane / g, gi = lane - r * g;
     const bool valid = r < R;
@@ -3108,52 +3252,27 @@ __device__ __forceinline__ void near_pass(const LDesc &d, NearSmem &sm, float4 *
             }
         }
     }
-    const int64_t e0 = d.near_ptr[t], e1 = d.near_ptr[t + 1];
     const bool same = d.same != 0;
-    for (int64_t e = e0; e < e1; ++e) {
-        const int s = __builtin_amdgcn_readfirstlane(d.near_src[e]);
-        const int j0 = __builtin_amdgcn_readfirstlane(d.sstart[s]), j1 = __builtin_amdgcn_readfirstlane(d.sstart[s + 1]);
-        const bool chk = !same || s == t;
-        for (int c0 = j0; c0 < j1; c0 += 64) {
-            const int cnt = min(64, j1 - c0);
-            const int steps = __builtin_amdgcn_readfirstlane((cnt + R - 1) / R), so = steps | 1;
-            near_stage_chunk(d, sm, c0, cnt, R, steps, so, cx, cy, cz, scale, uscale, NRM == 2 ? snm : nullptr, d.sn);
-            const int base = valid ? r * so : 0;     // idle lanes read staged slots and discard their sums
-            if (chk)
+    near_walk<false, NRM == 2>(
+        d, waves[threadIdx.x >> 6].list, t, d.sn,
+        [&](const NearChunk &c, const NearRegs &rg) {
+            const int steps = (c.cnt + R - 1) / R;
+            near_stage_chunk(d, sm, rg, c.cnt, R, steps, steps | 1, cx, cy, cz, scale, uscale, NRM == 2 ? snm : nullptr);
+        },
+        [&](const NearChunk &c) {
+            const int steps = (c.cnt + R - 1) / R;
+            const int base = valid ? r * (steps | 1) : 0;     // idle lanes read staged slots and discard their sums
+            if (!same || c.s == t)
                 near_range<HELM, NRM, BIG, true, T>(sm, snm, base, steps, x, y, z, nx, ny, nz, are, aim);
             else
                 near_range<HELM, NRM, BIG, false, T>(sm, snm, base, steps, x, y, z, nx, ny, nz, are, aim);
-        }
-    }
-    // the R partial sums of each target, added in order of r
-    float2 *part = reinterpret_cast<float2 *>(sm.x);   // [T][64], over x and y
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < T; ++k) part[k * 64 + lane] = make_float2(are[k], aim[k]);
-    __syncthreads();
-    if (lane < g) {
-#pragma unroll
-        for (int k = 0; k < T; ++k) {
-            const int ti = lane + g * k;
-            if (ti >= nt) break;
-            float2 a = part[k * 64 + lane];
-            for (int rr = 1; rr < R; ++rr) {
-                const float2 b = part[k * 64 + lane + rr * g];
-                a.x += b.x;
-                a.y += b.y;
-            }
-            float2 o = d.v[i0 + ti];
-            o.x += a.x;
-            o.y += a.y;
-            d.v[i0 + ti] = o;
-        }
-    }
+        });
+    near_reduce(waves, are, aim, g, R, nt, d.v + i0);
 }
 
 template <bool HELM, int NRM, bool BIG>
 __device__ __forceinline__ void near_body(const LDesc &d, const int4 wk) {
-    __shared__ NearSmem sm;
-    __shared__ float4 snm[NRM == 2 ? kNearSlots : 1];   // staged source normals (double layer)
+    NearWave<NRM, false> *waves = reinterpret_cast<NearWave<NRM, false> *>(near_raw);
     const int t = wk.y;
     const int ta = d.tstart[t], tz = d.tstart[t + 1];
     // Helmholtz: coordinates in units of 2 pi / k; 1/r = (k / 2 pi) / r', 1/r^3 = (k / 2 pi)^3 / r'^3 and
@@ -3164,17 +3283,17 @@ __device__ __forceinline__ void near_body(const LDesc &d, const int4 wk) {
     for (int i0 = ta; i0 < tz;) {
         const NearPass ps = near_next_pass(tz - i0);
         if (ps.T == 1)
-            near_pass<HELM, NRM, BIG, 1>(d, sm, snm, t, i0, ps.nt, scale, uscale);
+            near_pass<HELM, NRM, BIG, 1>(d, waves, t, i0, ps.nt, scale, uscale);
         else if (ps.T == 2)
-            near_pass<HELM, NRM, BIG, 2>(d, sm, snm, t, i0, ps.nt, scale, uscale);
+            near_pass<HELM, NRM, BIG, 2>(d, waves, t, i0, ps.nt, scale, uscale);
         else
-            near_pass<HELM, NRM, BIG, 4>(d, sm, snm, t, i0, ps.nt, scale, uscale);
+            near_pass<HELM, NRM, BIG, 4>(d, waves, t, i0, ps.nt, scale, uscale);
         i0 += ps.nt;
     }
 }
 
 template <bool HELM, bool BIG>
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(512, 4)
 k_near(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const int4 *__restrict__ work) {
     const int4 wk = work[blockIdx.x];
     near_body<HELM, 0, BIG>(descs[wk.x], wk);
@@ -3182,7 +3301,7 @@ k_near(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const int4 
 
 // The normal derivative at the target (the adjoint double-layer kernel), same blocks and lanes.
 template <bool HELM, bool BIG>
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(512, 4)
 k_near_dn(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const int4 *__restrict__ work) {
     const int4 wk = work[blockIdx.x];
     near_body<HELM, 1, BIG>(descs[wk.x], wk);
@@ -3190,7 +3309,7 @@ k_near_dn(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const in
 
 // The normal derivative at the source (the double-layer kernel), same blocks and lanes.
 template <bool HELM, bool BIG>
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(512, 4)
 k_near_dl(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const int4 *__restrict__ work) {
     const int4 wk = work[blockIdx.x];
     near_body<HELM, 2, BIG>(descs[wk.x], wk);
@@ -3255,9 +3374,10 @@ __device__ __forceinline__ void near_range_grad(const NearSmem &sm, int base, in
 // One pass of the gradient near field: the lanes and sources of near_pass; component c of target i is added
 // to output plane c (d.v + c n_x).
 template <bool HELM, bool BIG, int T>
-__device__ __forceinline__ void near_pass_grad(const LDesc &d, NearSmem &sm, int t, int i0, int nt, double scale,
-                                               float uscale) {
-    const int lane = threadIdx.x;
+__device__ __forceinline__ void near_pass_grad(const LDesc &d, NearWave<3, false> *waves, int t, int i0, int nt,
+                                               double scale, float uscale) {
+    const int lane = threadIdx.x & 63;
+    NearSmem &sm = waves[threadIdx.x >> 6].sm;
     const int g = __builtin_amdgcn_readfirstlane((nt + T - 1) / T), R = __builtin_amdgcn_readfirstlane(64 / g);
     const int r = lane / g, gi = lane - r * g;
     const bool valid = r < R;
@@ -3277,59 +3397,32 @@ __device__ __forceinline__ void near_pass_grad(const LDesc &d, NearSmem &sm, int
             z[k] = (d.tzs[i] - cz) * scale;
         }
     }
-    const int64_t e0 = d.near_ptr[t], e1 = d.near_ptr[t + 1];
     const bool same = d.same != 0;
-    for (int64_t e = e0; e < e1; ++e) {
-        const int s = __builtin_amdgcn_readfirstlane(d.near_src[e]);
-        const int j0 = __builtin_amdgcn_readfirstlane(d.sstart[s]), j1 = __builtin_amdgcn_readfirstlane(d.sstart[s + 1]);
-        const bool chk = !same || s == t;
-        for (int c0 = j0; c0 < j1; c0 += 64) {
-            const int cnt = min(64, j1 - c0);
-            const int steps = __builtin_amdgcn_readfirstlane((cnt + R - 1) / R), so = steps | 1;
-            near_stage_chunk(d, sm, c0, cnt, R, steps, so, cx, cy, cz, scale, uscale, nullptr);
-            const int base = valid ? r * so : 0;     // idle lanes read staged slots and discard their sums
-            if (chk)
+    near_walk<false, false>(
+        d, waves[threadIdx.x >> 6].list, t, nullptr,
+        [&](const NearChunk &c, const NearRegs &rg) {
+            const int steps = (c.cnt + R - 1) / R;
+            near_stage_chunk(d, sm, rg, c.cnt, R, steps, steps | 1, cx, cy, cz, scale, uscale, nullptr);
+        },
+        [&](const NearChunk &c) {
+            const int steps = (c.cnt + R - 1) / R;
+            const int base = valid ? r * (steps | 1) : 0;     // idle lanes read staged slots and discard their sums
+            if (!same || c.s == t)
                 near_range_grad<HELM, BIG, true, T>(sm, base, steps, x, y, z, ar, ai);
             else
                 near_range_grad<HELM, BIG, false, T>(sm, base, steps, x, y, z, ar, ai);
-        }
-    }
-    // per component: the R partial sums of each target, added in order of r
-    float2 *part = reinterpret_cast<float2 *>(sm.x);   // [T][64], over x and y
+        });
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < T; ++k) part[k * 64 + lane] = make_float2(ar[c][k], ai[c][k]);
-        __syncthreads();
-        if (lane < g) {
-            float2 *vc = d.v + (int64_t)c * d.nx;
-#pragma unroll
-            for (int k = 0; k < T; ++k) {
-                const int ti = lane + g * k;
-                if (ti >= nt) break;
-                float2 a = part[k * 64 + lane];
-                for (int rr = 1; rr < R; ++rr) {
-                    const float2 b = part[k * 64 + lane + rr * g];
-                    a.x += b.x;
-                    a.y += b.y;
-                }
-                float2 o = vc[i0 + ti];
-                o.x += a.x;
-                o.y += a.y;
-                vc[i0 + ti] = o;
-            }
-        }
-    }
+    for (int c = 0; c < 3; ++c) near_reduce(waves, ar[c], ai[c], g, R, nt, d.v + (int64_t)c * d.nx + i0);
 }
 
 // The gradient at the targets, all three components in one pass over the near pairs.  Item (desc, target box).
 template <bool HELM, bool BIG>
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(512, 4)
 k_near_grad(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const int4 *__restrict__ work) {
     const int4 wk = work[blockIdx.x];
     const LDesc &d = descs[wk.x];
-    __shared__ NearSmem sm;
+    NearWave<3, false> *waves = reinterpret_cast<NearWave<3, false> *>(near_raw);
     const int t = wk.y;
     const int ta = d.tstart[t], tz = d.tstart[t + 1];
     const double kr = (double)d.k_rev;
@@ -3338,11 +3431,11 @@ k_near_grad(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const 
     for (int i0 = ta; i0 < tz;) {
         const NearPass ps = near_next_pass(tz - i0);
         if (ps.T == 1)
-            near_pass_grad<HELM, BIG, 1>(d, sm, t, i0, ps.nt, scale, uscale);
+            near_pass_grad<HELM, BIG, 1>(d, waves, t, i0, ps.nt, scale, uscale);
         else if (ps.T == 2)
-            near_pass_grad<HELM, BIG, 2>(d, sm, t, i0, ps.nt, scale, uscale);
+            near_pass_grad<HELM, BIG, 2>(d, waves, t, i0, ps.nt, scale, uscale);
         else
-            near_pass_grad<HELM, BIG, 4>(d, sm, t, i0, ps.nt, scale, uscale);
+            near_pass_grad<HELM, BIG, 4>(d, waves, t, i0, ps.nt, scale, uscale);
         i0 += ps.nt;
     }
 }
@@ -3399,10 +3492,11 @@ __device__ __forceinline__ void near_pair_sym(double x, double y, double z, floa
 }
 
 template <bool HELM, bool BIG, int T>
-__device__ __forceinline__ void near_pass_sym(const LDesc &d, NearSmem &sm, int t, int i0, int nt, bool first,
+__device__ __forceinline__ void near_pass_sym(const LDesc &d, NearWave<0, true> *waves, int t, int i0, int nt, bool first,
                                               double scale, float uscale) {
     constexpr int g = 16, R = 4;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    NearSmem &sm = waves[threadIdx.x >> 6].sm;
     const int r = lane >> 4, gi = lane & 15;
     const bool last = gi == g - 1;
     const double cx = d.tctr[3 * t], cy = d.tctr[3 * t + 1], cz = d.tctr[3 * t + 2];
@@ -3423,20 +3517,17 @@ __device__ __forceinline__ void near_pass_sym(const LDesc &d, NearSmem &sm, int 
         ut[k] = ti < nt ? make_float2(uu.x * uscale, uu.y * uscale) : make_float2(0.f, 0.f);
         nty[k] = -ut[k].y;
     }
-    const int64_t e0 = d.near_ptr[t], e1 = d.near_ptr[t + 1];
-    for (int64_t e = e0; e < e1; ++e) {
-        const int s = __builtin_amdgcn_readfirstlane(d.near_src[e]);
-        const int64_t off = d.near_off[e];
-        if (s < t && off >= 0) continue;          // the block of box s evaluates this pair of boxes
-        const int j0 = __builtin_amdgcn_readfirstlane(d.sstart[s]), j1 = __builtin_amdgcn_readfirstlane(d.sstart[s + 1]);
-        for (int c0 = j0; c0 < j1; c0 += 64) {
-            const int cnt = min(64, j1 - c0);
-            const int steps = __builtin_amdgcn_readfirstlane((cnt + R - 1) / R), so = steps | 1;
-            near_stage_chunk(d, sm, c0, cnt, R, steps, so, cx, cy, cz, scale, uscale, nullptr);
-            const int base = r * so;
-            if (s == t) {
+    near_walk<true, false>(
+        d, waves[threadIdx.x >> 6].list, t, nullptr,
+        [&](const NearChunk &c, const NearRegs &rg) {
+            const int steps = (c.cnt + R - 1) / R;
+            near_stage_chunk(d, sm, rg, c.cnt, R, steps, steps | 1, cx, cy, cz, scale, uscale, nullptr);
+        },
+        [&](const NearChunk &c) {
+            const int steps = (c.cnt + R - 1) / R, base = r * (steps | 1);
+            if (c.s == t) {
                 near_range<HELM, 0, BIG, true, T>(sm, nullptr, base, steps, x, y, z, nx, ny, nz, are, aim);
-            } else if (s < t) {
+            } else if (c.s < t) {
                 near_range<HELM, 0, BIG, false, T>(sm, nullptr, base, steps, x, y, z, nx, ny, nz, are, aim);
             } else {
                 const int jb = r * steps;
@@ -3454,9 +3545,10 @@ __device__ __forceinline__ void near_pass_sym(const LDesc &d, NearSmem &sm, int 
                     sim = row_sum16(sim);
                     if (last) sm.sp[jb + q] = make_float2(sre, sim);   // slots past cnt are never read
                 }
-                __syncthreads();
-                if (lane < cnt) {
-                    float2 *o = d.nsym + off + (c0 - j0) + lane;
+                wave_lds_fence();
+                if (lane < c.cnt) {
+                    // (the same wave takes this chunk in every pass)
+                    float2 *o = d.nsym + c.off + c.rel + lane;
                     float2 a = sm.sp[lane];
                     if (!first) {
                         const float2 b = *o;
@@ -3466,38 +3558,15 @@ __device__ __forceinline__ void near_pass_sym(const LDesc &d, NearSmem &sm, int 
                     *o = a;
                 }
             }
-        }
-    }
-    float2 *part = reinterpret_cast<float2 *>(sm.x);   // [T][64] over x, y, z and u (T <= 5)
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < T; ++k) part[k * 64 + lane] = make_float2(are[k], aim[k]);
-    __syncthreads();
-    if (lane < g) {
-#pragma unroll
-        for (int k = 0; k < T; ++k) {
-            const int ti = lane + g * k;
-            if (ti >= nt) break;
-            float2 a = part[k * 64 + lane];
-#pragma unroll
-            for (int rr = 1; rr < R; ++rr) {
-                const float2 b = part[k * 64 + lane + rr * g];
-                a.x += b.x;
-                a.y += b.y;
-            }
-            float2 o = d.v[i0 + ti];
-            o.x += a.x;
-            o.y += a.y;
-            d.v[i0 + ti] = o;
-        }
-    }
+        });
+    near_reduce(waves, are, aim, g, R, nt, d.v + i0);
 }
 
 template <bool HELM, bool BIG>
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(512, 4)
 k_near_sym(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const int4 *__restrict__ work) {
-    __shared__ NearSmem sm;
-    static_assert(sizeof(NearSmem) >= 5 * 64 * sizeof(float2) + sizeof(float2) * kNearSlots, "part[] must fit");
+    NearWave<0, true> *waves = reinterpret_cast<NearWave<0, true> *>(near_raw);
+    static_assert(offsetof(NearSmem, sp) >= 5 * 64 * sizeof(float2), "the partial sums must fit");
     const int4 wk = work[blockIdx.x];
     const LDesc &d = descs[wk.x];
     const int t = wk.y;
@@ -3510,11 +3579,11 @@ k_near_sym(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const i
         const int T = (nt + 15) >> 4;
         const bool first = i0 == ta;
         switch (T) {
-            case 1: near_pass_sym<HELM, BIG, 1>(d, sm, t, i0, nt, first, scale, uscale); break;
-            case 2: near_pass_sym<HELM, BIG, 2>(d, sm, t, i0, nt, first, scale, uscale); break;
-            case 3: near_pass_sym<HELM, BIG, 3>(d, sm, t, i0, nt, first, scale, uscale); break;
-            case 4: near_pass_sym<HELM, BIG, 4>(d, sm, t, i0, nt, first, scale, uscale); break;
-            default: near_pass_sym<HELM, BIG, 5>(d, sm, t, i0, nt, first, scale, uscale); break;
+            case 1: near_pass_sym<HELM, BIG, 1>(d, waves, t, i0, nt, first, scale, uscale); break;
+            case 2: near_pass_sym<HELM, BIG, 2>(d, waves, t, i0, nt, first, scale, uscale); break;
+            case 3: near_pass_sym<HELM, BIG, 3>(d, waves, t, i0, nt, first, scale, uscale); break;
+            case 4: near_pass_sym<HELM, BIG, 4>(d, waves, t, i0, nt, first, scale, uscale); break;
+            default: near_pass_sym<HELM, BIG, 5>(d, waves, t, i0, nt, first, scale, uscale); break;
         }
         i0 += nt;
     }
@@ -3587,10 +3656,13 @@ __device__ __forceinline__ void near_pair_symd(double x, double y, double z, flo
 // sources' normals are staged beside them (NRM 1: n_j, NRM 2: -n_j), and a gradient's three components have
 // their own accumulators, source-side sums, buffer planes (nsym + c nsymn) and output planes (v + c n_x).
 template <bool HELM, bool BIG, int NRM, int T>
-__device__ __forceinline__ void near_pass_symd(const LDesc &d, NearSmem &sm, float4 *snm, float2 (*sp12)[kNearSlots],
-                                               int t, int i0, int nt, bool first, double scale, float uscale) {
+__device__ __forceinline__ void near_pass_symd(const LDesc &d, NearWave<NRM, true> *waves, int t, int i0, int nt,
+                                               bool first, double scale, float uscale) {
     constexpr int g = 16, R = 4, NC = NRM == 3 ? 3 : 1;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    NearSmem &sm = waves[threadIdx.x >> 6].sm;
+    float4 *snm = waves[threadIdx.x >> 6].snm;
+    auto &sp12 = waves[threadIdx.x >> 6].sp12;
     const int r = lane >> 4, gi = lane & 15;
     const bool last = gi == g - 1;
     const double cx = d.tctr[3 * t], cy = d.tctr[3 * t + 1], cz = d.tctr[3 * t + 2];
@@ -3619,27 +3691,24 @@ __device__ __forceinline__ void near_pass_symd(const LDesc &d, NearSmem &sm, flo
         const float2 uu = d.u[i];
         ut[k] = ti < nt ? make_float2(uu.x * uscale, uu.y * uscale) : make_float2(0.f, 0.f);
     }
-    const int64_t e0 = d.near_ptr[t], e1 = d.near_ptr[t + 1];
-    for (int64_t e = e0; e < e1; ++e) {
-        const int s = __builtin_amdgcn_readfirstlane(d.near_src[e]);
-        const int64_t off = d.near_off[e];
-        if (s < t && off >= 0) continue;          // the block of box s evaluates this pair of boxes
-        const int j0 = __builtin_amdgcn_readfirstlane(d.sstart[s]), j1 = __builtin_amdgcn_readfirstlane(d.sstart[s + 1]);
-        for (int c0 = j0; c0 < j1; c0 += 64) {
-            const int cnt = min(64, j1 - c0);
-            const int steps = __builtin_amdgcn_readfirstlane((cnt + R - 1) / R), so = steps | 1;
-            near_stage_chunk(d, sm, c0, cnt, R, steps, so, cx, cy, cz, scale, uscale, NRM == 3 ? nullptr : snm,
-                             nrm, NRM == 1 ? 1.f : -1.f);
-            const int base = r * so;
-            if (s <= t) {
+    near_walk<true, NRM != 3>(
+        d, waves[threadIdx.x >> 6].list, t, nrm,
+        [&](const NearChunk &c, const NearRegs &rg) {
+            const int steps = (c.cnt + R - 1) / R;
+            near_stage_chunk(d, sm, rg, c.cnt, R, steps, steps | 1, cx, cy, cz, scale, uscale, NRM == 3 ? nullptr : snm,
+                             NRM == 1 ? 1.f : -1.f);
+        },
+        [&](const NearChunk &c) {
+            const int steps = (c.cnt + R - 1) / R, base = r * (steps | 1);
+            if (c.s <= t) {
                 // the box itself (r > 0 test) and lower neighbours without a reverse entry: ordered pairs
                 if constexpr (NRM == 3) {
-                    if (s == t)
+                    if (c.s == t)
                         near_range_grad<HELM, BIG, true, T>(sm, base, steps, x, y, z, are, aim);
                     else
                         near_range_grad<HELM, BIG, false, T>(sm, base, steps, x, y, z, are, aim);
                 } else {
-                    if (s == t)
+                    if (c.s == t)
                         near_range<HELM, NRM, BIG, true, T>(sm, snm, base, steps, x, y, z, nx, ny, nz, are[0], aim[0]);
                     else
                         near_range<HELM, NRM, BIG, false, T>(sm, snm, base, steps, x, y, z, nx, ny, nz, are[0], aim[0]);
@@ -3653,35 +3722,35 @@ __device__ __forceinline__ void near_pass_symd(const LDesc &d, NearSmem &sm, flo
                     const float4 sn = NRM == 3 ? make_float4(0.f, 0.f, 0.f, 0.f) : snm[sl];
                     float sre[NC], sim[NC];
 #pragma unroll
-                    for (int c = 0; c < NC; ++c) sre[c] = sim[c] = 0.f;
+                    for (int m = 0; m < NC; ++m) sre[m] = sim[m] = 0.f;
 #pragma unroll
                     for (int k = 0; k < T; ++k) {
                         float ar[NC], ai[NC];
 #pragma unroll
-                        for (int c = 0; c < NC; ++c) {
-                            ar[c] = are[c][k];
-                            ai[c] = aim[c][k];
+                        for (int m = 0; m < NC; ++m) {
+                            ar[m] = are[m][k];
+                            ai[m] = aim[m][k];
                         }
                         near_pair_symd<HELM, BIG, NRM, NC>(x[k], y[k], z[k], nx[k], ny[k], nz[k], ut[k], sx, sy, sz,
                                                            sn, us, ar, ai, sre, sim);
 #pragma unroll
-                        for (int c = 0; c < NC; ++c) {
-                            are[c][k] = ar[c];
-                            aim[c][k] = ai[c];
+                        for (int m = 0; m < NC; ++m) {
+                            are[m][k] = ar[m];
+                            aim[m][k] = ai[m];
                         }
                     }
 #pragma unroll
-                    for (int c = 0; c < NC; ++c) {
-                        const float a = row_sum16(sre[c]), b = row_sum16(sim[c]);
-                        if (last) (c == 0 ? sm.sp : sp12[c - 1])[jb + q] = make_float2(a, b);
+                    for (int m = 0; m < NC; ++m) {
+                        const float a = row_sum16(sre[m]), b = row_sum16(sim[m]);
+                        if (last) (m == 0 ? sm.sp : sp12[m - 1])[jb + q] = make_float2(a, b);
                     }
                 }
-                __syncthreads();
-                if (lane < cnt) {
+                wave_lds_fence();
+                if (lane < c.cnt) {
 #pragma unroll
-                    for (int c = 0; c < NC; ++c) {
-                        float2 *o = d.nsym + (int64_t)c * d.nsymn + off + (c0 - j0) + lane;
-                        float2 a = (c == 0 ? sm.sp : sp12[c - 1])[lane];
+                    for (int m = 0; m < NC; ++m) {
+                        float2 *o = d.nsym + (int64_t)m * d.nsymn + c.off + c.rel + lane;
+                        float2 a = (m == 0 ? sm.sp : sp12[m - 1])[lane];
                         if (!first) {
                             const float2 b = *o;
                             a.x += b.x;
@@ -3691,43 +3760,15 @@ __device__ __forceinline__ void near_pass_symd(const LDesc &d, NearSmem &sm, flo
                     }
                 }
             }
-        }
-    }
-    float2 *part = reinterpret_cast<float2 *>(sm.x);   // [T][64] over x, y, z and u (T <= 5)
+        });
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < T; ++k) part[k * 64 + lane] = make_float2(are[c][k], aim[c][k]);
-        __syncthreads();
-        if (lane < g) {
-            float2 *vc = d.v + (int64_t)c * d.nx;
-#pragma unroll
-            for (int k = 0; k < T; ++k) {
-                const int ti = lane + g * k;
-                if (ti >= nt) break;
-                float2 a = part[k * 64 + lane];
-#pragma unroll
-                for (int rr = 1; rr < R; ++rr) {
-                    const float2 b = part[k * 64 + lane + rr * g];
-                    a.x += b.x;
-                    a.y += b.y;
-                }
-                float2 o = vc[i0 + ti];
-                o.x += a.x;
-                o.y += a.y;
-                vc[i0 + ti] = o;
-            }
-        }
-    }
+    for (int c = 0; c < NC; ++c) near_reduce(waves, are[c], aim[c], g, R, nt, d.v + (int64_t)c * d.nx + i0);
 }
 
 template <bool HELM, bool BIG, int NRM>
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(512, 3)
 k_near_sym_d(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const int4 *__restrict__ work) {
-    __shared__ NearSmem sm;
-    __shared__ float4 snm[NRM == 3 ? 1 : kNearSlots];
-    __shared__ float2 sp12[NRM == 3 ? 2 : 1][kNearSlots];
+    NearWave<NRM, true> *waves = reinterpret_cast<NearWave<NRM, true> *>(near_raw);
     const int4 wk = work[blockIdx.x];
     const LDesc &d = descs[wk.x];
     const int t = wk.y;
@@ -3740,11 +3781,11 @@ k_near_sym_d(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const
         const int T = (nt + 15) >> 4;
         const bool first = i0 == ta;
         switch (T) {
-            case 1: near_pass_symd<HELM, BIG, NRM, 1>(d, sm, snm, sp12, t, i0, nt, first, scale, uscale); break;
-            case 2: near_pass_symd<HELM, BIG, NRM, 2>(d, sm, snm, sp12, t, i0, nt, first, scale, uscale); break;
-            case 3: near_pass_symd<HELM, BIG, NRM, 3>(d, sm, snm, sp12, t, i0, nt, first, scale, uscale); break;
-            case 4: near_pass_symd<HELM, BIG, NRM, 4>(d, sm, snm, sp12, t, i0, nt, first, scale, uscale); break;
-            default: near_pass_symd<HELM, BIG, NRM, 5>(d, sm, snm, sp12, t, i0, nt, first, scale, uscale); break;
+            case 1: near_pass_symd<HELM, BIG, NRM, 1>(d, waves, t, i0, nt, first, scale, uscale); break;
+            case 2: near_pass_symd<HELM, BIG, NRM, 2>(d, waves, t, i0, nt, first, scale, uscale); break;
+            case 3: near_pass_symd<HELM, BIG, NRM, 3>(d, waves, t, i0, nt, first, scale, uscale); break;
+            case 4: near_pass_symd<HELM, BIG, NRM, 4>(d, waves, t, i0, nt, first, scale, uscale); break;
+            default: near_pass_symd<HELM, BIG, NRM, 5>(d, waves, t, i0, nt, first, scale, uscale); break;
         }
         i0 += nt;
     }
@@ -3759,24 +3800,43 @@ k_near_gather(const LDesc *__restrict__ descs, const IoEntry *__restrict__, cons
     const int b = wk.y;
     const int ta = d.tstart[b], tz = d.tstart[b + 1];
     const int64_t e0 = d.near_ptr[b], e1 = d.near_ptr[b + 1];
-    for (int c = 0; c < d.ncomp; ++c) {
-        const float2 *ns = d.nsym + (int64_t)c * d.nsymn;
-        float2 *vc = d.v + (int64_t)c * d.nx;
-        for (int i = ta + (int)threadIdx.x; i < tz; i += 64) {
-            float2 a = make_float2(0.f, 0.f);
-            for (int64_t e = e0; e < e1; ++e) {
-                const int s = __builtin_amdgcn_readfirstlane(d.near_src[e]);
-                const int64_t off = d.near_off[e];
-                if (s < b && off >= 0) {
-                    const float2 w = ns[off + (i - ta)];
-                    a.x += w.x;
-                    a.y += w.y;
+    const int lane = threadIdx.x;
+    for (int64_t eb = e0; eb < e1; eb += 64) {
+        // the entries in the lanes; those with sums for this box in list order, four loads at a time
+        int64_t off = -1;
+        if (eb + lane < e1 && d.near_src[eb + lane] < b) off = d.near_off[eb + lane];
+        const unsigned long long has = __ballot(off >= 0);
+        for (int c = 0; c < d.ncomp; ++c) {
+            const float2 *ns = d.nsym + (int64_t)c * d.nsymn - ta;
+            float2 *vc = d.v + (int64_t)c * d.nx;
+            for (int i = ta + lane; i - lane < tz; i += 64) {
+                float2 a = make_float2(0.f, 0.f);
+                unsigned long long m = has;
+                while (m) {
+                    float2 w[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        w[u] = make_float2(0.f, 0.f);
+                        if (!m) continue;
+                        const int e = __builtin_ctzll(m);
+                        m &= m - 1;
+                        const int64_t o = ((int64_t)__builtin_amdgcn_readlane((int)(off >> 32), e) << 32) |
+                                          (uint32_t)__builtin_amdgcn_readlane((int)off, e);
+                        if (i < tz) w[u] = ns[o + i];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        a.x += w[u].x;
+                        a.y += w[u].y;
+                    }
+                }
+                if (i < tz) {
+                    float2 o = vc[i];
+                    o.x += a.x;
+                    o.y += a.y;
+                    vc[i] = o;
                 }
             }
-            float2 o = vc[i];
-            o.x += a.x;
-            o.y += a.y;
-            vc[i] = o;
         }
     }
 }
@@ -3856,12 +3916,14 @@ KernelFn kernel_of(const Stage &S, int &threads) {
             if (S.a < 200) return S.b ? k_lag_expand<true, 1> : k_lag_expand<false, 1>;
             return S.b ? k_lag_expand<true, 4> : k_lag_expand<false, 4>;
         case K_INTERP: threads = 64 * std::max(1, S.a); return k_lag_interp;
-        case K_NEAR: threads = 64; return S.b ? (S.a ? k_near<true, true> : k_near<true, false>) : k_near<false, false>;
+        // near-field kernels: a = BIG (symmetric ones BIG + 2 NRM) + 16 log2(waves per block)
+        case K_NEAR:
+            threads = 64 << (S.a >> 4);
+            return S.b ? ((S.a & 1) ? k_near<true, true> : k_near<true, false>) : k_near<false, false>;
         case K_NEAR_SYM:
-            // a = BIG + 2 NRM (NRM 0: the kernel itself, 1: normal derivative at the targets, 2: at the sources,
-            // 3: the gradient)
-            threads = 64;
-            switch (S.a >> 1) {
+            // NRM 0: the kernel itself, 1: normal derivative at the targets, 2: at the sources, 3: the gradient
+            threads = 64 << (S.a >> 4);
+            switch ((S.a & 15) >> 1) {
                 case 1:
                     return S.b ? ((S.a & 1) ? k_near_sym_d<true, true, 1> : k_near_sym_d<true, false, 1>)
                                : k_near_sym_d<false, false, 1>;
@@ -3876,14 +3938,14 @@ KernelFn kernel_of(const Stage &S, int &threads) {
             }
         case K_NEAR_GATHER: threads = 64; return k_near_gather;
         case K_NEAR_DL:
-            threads = 64;
-            return S.b ? (S.a ? k_near_dl<true, true> : k_near_dl<true, false>) : k_near_dl<false, false>;
+            threads = 64 << (S.a >> 4);
+            return S.b ? ((S.a & 1) ? k_near_dl<true, true> : k_near_dl<true, false>) : k_near_dl<false, false>;
         case K_NEAR_DN:
-            threads = 64;
-            return S.b ? (S.a ? k_near_dn<true, true> : k_near_dn<true, false>) : k_near_dn<false, false>;
+            threads = 64 << (S.a >> 4);
+            return S.b ? ((S.a & 1) ? k_near_dn<true, true> : k_near_dn<true, false>) : k_near_dn<false, false>;
         case K_NEAR_GRAD:
-            threads = 64;
-            return S.b ? (S.a ? k_near_grad<true, true> : k_near_grad<true, false>) : k_near_grad<false, false>;
+            threads = 64 << (S.a >> 4);
+            return S.b ? ((S.a & 1) ? k_near_grad<true, true> : k_near_grad<true, false>) : k_near_grad<false, false>;
         case K_INTERP_DN: threads = 64 * std::max(1, S.a); return k_lag_interp_dn;
         case K_BWD_PAIR_DN:
             if (S.a == 100) {
@@ -3931,6 +3993,23 @@ KernelFn kernel_of(const Stage &S, int &threads) {
 }
 
 }  // namespace
+
+size_t near_shmem(int kern, int a) {
+    const size_t nw = (size_t)1 << (a >> 4);
+    switch (kern) {
+        case K_NEAR: return nw * sizeof(NearWave<0, false>);
+        case K_NEAR_DN: return nw * sizeof(NearWave<1, false>);
+        case K_NEAR_DL: return nw * sizeof(NearWave<2, false>);
+        case K_NEAR_GRAD: return nw * sizeof(NearWave<3, false>);
+        default: break;
+    }
+    switch ((a & 15) >> 1) {
+        case 0: return nw * sizeof(NearWave<0, true>);
+        case 1: return nw * sizeof(NearWave<1, true>);
+        case 2: return nw * sizeof(NearWave<2, true>);
+        default: return nw * sizeof(NearWave<3, true>);
+    }
+}
 
 int stage_blocks_per_cu(int kern, int a, int b) {
     // a property of the compiled kernel and the device: queried once per (device, variant)
@@ -4074,15 +4153,15 @@ std::string kernel_name(int kern, int a, int b) {
         case K_ACA: return "k_lag_project<" + tf(b) + ">";
         case K_EXPAND: return "k_lag_expand<" + tf(b) + (a < 200 ? ", 1>" : ", 4>");
         case K_INTERP: return "k_lag_interp";
-        case K_NEAR: return "k_near<" + tf(b) + ", " + tf(b && a) + ">";
+        case K_NEAR: return "k_near<" + tf(b) + ", " + tf(b && (a & 1)) + ">";
         case K_NEAR_SYM:
-            if (a >> 1)
-                return "k_near_sym_d<" + tf(b) + ", " + tf(b && (a & 1)) + ", " + std::to_string(a >> 1) + ">";
-            return "k_near_sym<" + tf(b) + ", " + tf(b && a) + ">";
+            if ((a & 15) >> 1)
+                return "k_near_sym_d<" + tf(b) + ", " + tf(b && (a & 1)) + ", " + std::to_string((a & 15) >> 1) + ">";
+            return "k_near_sym<" + tf(b) + ", " + tf(b && (a & 1)) + ">";
         case K_NEAR_GATHER: return "k_near_gather";
-        case K_NEAR_DN: return "k_near_dn<" + tf(b) + ", " + tf(b && a) + ">";
-        case K_NEAR_GRAD: return "k_near_grad<" + tf(b) + ", " + tf(b && a) + ">";
-        case K_NEAR_DL: return "k_near_dl<" + tf(b) + ", " + tf(b && a) + ">";
+        case K_NEAR_DN: return "k_near_dn<" + tf(b) + ", " + tf(b && (a & 1)) + ">";
+        case K_NEAR_GRAD: return "k_near_grad<" + tf(b) + ", " + tf(b && (a & 1)) + ">";
+        case K_NEAR_DL: return "k_near_dl<" + tf(b) + ", " + tf(b && (a & 1)) + ">";
         case K_INTERP_DN: return "k_lag_interp_dn";
         case K_BWD_PAIR_DN: return "k_pw_backward_dn<" + std::to_string(a == 100 ? 64 : 256) + ", " + tf(b) + ">";
         case K_ZERO_OUT: return "k_zero_io";

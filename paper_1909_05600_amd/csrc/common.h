@@ -519,6 +519,8 @@ void plan_static_setup(Plan &P, hipStream_t st);
 int implicit_batch_drop(const Plan *P, bool wait);
 // concurrent blocks per CU of a kernel variant (occupancy) and the device's CU count
 int stage_blocks_per_cu(int kern, int a, int b);
+// dynamic LDS of a near-field kernel variant (a: see kernel_of)
+size_t near_shmem(int kern, int a);
 std::string kernel_name(int kern, int a, int b);
 int device_cus();
 LDesc make_desc(const Plan &P, int l, int inst, float2 *u, float2 *v, float *amax, const LevelWork &w);

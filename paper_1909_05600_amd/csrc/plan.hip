@@ -2360,6 +2360,15 @@ size_t anterp_shmem(int nw, int r1, bool dl) {
     return (size_t)nw * 64 * (dl ? 8 : 4) * (r1 <= 6 ? 6 : 8) * sizeof(float);
 }
 
+// log2 of the waves per box of a near-field launch over `boxes` boxes of `chunks` source chunks each on average (about
+// one per near pair; the symmetric pass visits half of them): enough waves for two rounds of the chip, at most eight,
+// and at most four for every three chunks (early lists have few).
+int near_waves(size_t boxes, double chunks) {
+    int lg = 0;
+    while (lg < 3 && (boxes << lg) < 8192 && (double)(2 << lg) * 0.75 <= chunks) ++lg;
+    return lg;
+}
+
 // The transfer stage of a Gegenbauer level: class tables in LDS where boxes have many direction pairs
 // (measured faster from n_pair ~ 4096 on), one target per block otherwise.
 // Gradient plans: v~ of the three components of a Gegenbauer level (k_dir_scale), over the level's target boxes.
@@ -2700,15 +2709,19 @@ void plan_stages(Plan &P, const Tune &tu, hipStream_t st, Scratch *keep) {
             if (P.lev[l].h_early.empty()) continue;
             std::vector<int4> er;
             for (int32_t t : P.lev[l].h_early) er.push_back(make_int4(l, t, 0, 0));
-            P.post.push_back(make_stage(near_kern, big(l), nhelm, -1, l, 0, std::move(er), st, SC));
+            const int a = big(l) + 16 * near_waves(er.size(), (double)P.lev[l].nearly / (double)er.size());
+            P.post.push_back(make_stage(near_kern, a, nhelm, -1, l, near_shmem(near_kern, a), std::move(er), st, SC));
         }
+        const double per_box = (double)P.lev[P.leaf].nnear / (double)std::max<size_t>(1, nr.size());
         if (P.near_sym) {
             std::vector<int4> ga = nr;
             const int nrm = P.grad ? 3 : (P.dn ? 1 : (P.dl ? 2 : 0));
-            P.post.push_back(make_stage(K_NEAR_SYM, big(P.leaf) + 2 * nrm, nhelm, -1, P.leaf, 0, std::move(nr), st, SC));
+            const int a = big(P.leaf) + 2 * nrm + 16 * near_waves(nr.size(), 0.5 * per_box);
+            P.post.push_back(make_stage(K_NEAR_SYM, a, nhelm, -1, P.leaf, near_shmem(K_NEAR_SYM, a), std::move(nr), st, SC));
             P.post.push_back(make_stage(K_NEAR_GATHER, 0, 0, 61, P.leaf, 0, std::move(ga), st, SC));
         } else {
-            P.post.push_back(make_stage(near_kern, big(P.leaf), nhelm, 61, P.leaf, 0, std::move(nr), st, SC));
+            const int a = big(P.leaf) + 16 * near_waves(nr.size(), per_box);
+            P.post.push_back(make_stage(near_kern, a, nhelm, 61, P.leaf, near_shmem(near_kern, a), std::move(nr), st, SC));
         }
         P.post.push_back(make_stage(K_PERM_OUT, 0, 0, 62, 0, 0, std::move(po), st, SC));
     }
