@@ -756,10 +756,10 @@ def launch_work(name, level, st):
         return (8.0 * nq * (nbf + st["nclass"][level] + nbt), "hbm",
                 "unique bytes: u~ of every source box, the class tables D and v~ of every target box, 8 per "
                 "direction each (the far-pair gathers re-read them from the caches)")
-    if name in ("k_lag_mfma", "k_lag_mfma16"):
+    if name.startswith("k_lag_mfma"):
         r = L ** 3
         return ((8.0 if st.get("_helm") else 4.0) * r * r * st["nfar"][level],
-                "mfma16" if name == "k_lag_mfma16" else "mfma",
+                "mfma16" if name.startswith("k_lag_mfma16") else "mfma",
                 "flops of T u~ per far pair, r = r1^3: 8 r^2 (complex T) or 4 r^2 (real T, complex u~); MFMA")
     if name in ("k_lag_anterp", "k_lag_interp"):
         r = L ** 3

@@ -2298,110 +2298,6 @@ k_lag_anterp_dl(const LDesc *__restrict__ descs, const IoEntry *__restrict__, co
     lag_anterp_body<true>(descs[wk.x], wk);
 }
 
-// U[k][2m + part] = part of u~_{s_m}[k] for the 16 pairs m of a class group (zero where the slot is empty): both
-// parts of an entry come from one 8-byte load, and each thread issues eight loads before it writes them to LDS.
-__device__ __forceinline__ void stage_group_sources(const float2 *ut2, const int *ps, int rp, float *U) {
-    const int nel = rp * 16, nth = blockDim.x, tid = threadIdx.x;
-    const gc2 src = gl(ut2);
-    for (int base = 0; base < nel; base += 8 * nth) {
-        v2f w[8];
-        int sm[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) sm[u] = ps[(base + u * nth + tid) & 15];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int idx = base + u * nth + tid, k = idx >> 4;
-            w[u] = v2f{0.f, 0.f};
-            if (idx < nel && sm[u] >= 0) w[u] = src[(int64_t)sm[u] * rp + k];
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int idx = base + u * nth + tid;
-            if (idx < nel) {
-                U[2 * idx] = w[u].x;
-                U[2 * idx + 1] = w[u].y;
-            }
-        }
-    }
-}
-
-// Transfer products of one class group on MFMA: Z_e = T_c u~_{s(e)} for up to 16 pairs e.
-// C (rp x 32) = T_c (rp x rp) x U (rp x 32), U[k][2m + part] = part of u~_{s(e_m)}[k].
-// v_mfma_f32_32x32x2f32 operands: A[i][k] from lane i + 32 k, B[k][j] from lane j + 32 k,
-// D[i][j] in lane j + 32 ((i / 4) % 2), register (i % 4) + 4 (i / 8).  Item (desc, group).
-__global__ void __launch_bounds__(256)
-k_lag_mfma(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const int4 *__restrict__ work) {
-    extern __shared__ float U[];   // [rp][32]
-    const int4 wk = work[blockIdx.x];
-    const LDesc &d = descs[wk.x];
-    const int g = wk.y;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nwv = blockDim.x >> 6;
-    const int rp = d.rp, helm = d.helm;
-    const int c = d.grp_cls[g];
-    __shared__ int pe[16], ps[16];
-    if (tid < 16) {
-        const int e = d.grp_pair[(int64_t)g * 16 + tid];
-        pe[tid] = e;
-        ps[tid] = e >= 0 ? d.far_src[e] : -1;
-    }
-    __syncthreads();
-    stage_group_sources(d.ut2, ps, rp, U);
-    __syncthreads();
-    const int64_t per = (int64_t)rp * rp;
-    const float *Tre = d.T + (int64_t)c * (helm ? 2 : 1) * per;
-    const float *Tim = Tre + per;
-    const int col = lane & 31, kh = lane >> 5;
-    const int e = pe[col >> 1];
-    for (int mt = wv; mt < rp / 32; mt += nwv) {   // the waves share the staged sources, one row tile each
-        floatx16 acc1, acc2;
-        for (int v = 0; v < 16; ++v) {
-            acc1[v] = 0.f;
-            acc2[v] = 0.f;
-        }
-        // groups of four steps (rp / 2 is a multiple of 16): the group's operands are loaded before its
-        // products, through global-address-space views of T
-        const gcf TreG = gfl(Tre) + mt * 32 + col, TimG = gfl(Tim) + mt * 32 + col;
-        // groups of four steps, double-buffered: the next group's T loads are issued before this group's
-        // products (rp / 2 is a multiple of 16)
-        float a1n[4], a2n[4];
-        auto load = [&](int kk0) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int k = 2 * (kk0 + u) + kh;
-                a1n[u] = TreG[(int64_t)k * rp];
-                a2n[u] = 0.f;
-                if (helm) a2n[u] = TimG[(int64_t)k * rp];   // Laplace tables have no imaginary part
-            }
-        };
-        load(0);
-        for (int kk0 = 0; kk0 < rp / 2; kk0 += 4) {
-            float bv[4], a1[4], a2[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                bv[u] = U[(2 * (kk0 + u) + kh) * 32 + col];
-                a1[u] = a1n[u];
-                a2[u] = a2n[u];
-            }
-            if (kk0 + 4 < rp / 2) load(kk0 + 4);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[u], bv[u], acc1, 0, 0, 0);
-                if (helm) acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(a2[u], bv[u], acc2, 0, 0, 0);
-            }
-        }
-        for (int v = 0; v < 16; ++v) {
-            const int i = mt * 32 + 8 * (v >> 2) + 4 * kh + (v & 3);
-            float val = acc1[v];
-            if (helm) {
-                const float sw = __shfl_xor(acc2[v], 1, 64);
-                val = (col & 1) ? val + sw : val - sw;
-            }
-            if (e >= 0) reinterpret_cast<float *>(d.Z + (int64_t)e * rp + i)[col & 1] = val;
-        }
-    }
-}
-
 // Transfers through the ACA factors of the classes (Sec. 2.2.2, eq. ffmACAmatvec: T_c ~ A_c B_c^T) in two kernels:
 // k_lag_project forms Y_e = B_c^T u~_{s(e)} for every far pair e, by class groups; k_lag_expand forms v~_t = sum_e
 // A_c(e) Y_e by target groups, so that only the rank's worth of values per pair goes through memory (128 B per 16
@@ -2642,115 +2538,332 @@ k_lag_expand(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const
     }
 }
 
-// Mixed precision: the same class-group products on FP16 MFMA (v_mfma_f32_32x32x16_f16, K = 16 per
-// instruction) with FP32 accumulation.  A[i][k] comes from lane i + 32 (k / 8) (element k % 8 of a half8),
-// B[k][j] from lane j + 32 (k / 8); D as for the FP32 instruction.  T16 = T * sT (plan time); the sources are scaled by a
-// power of two s_u derived on the device from max |u| so that |u~ s_u| < 6e4; Z = C / (sT s_u).
+// FP16 levels: the same u~ with every node's sum in the order of the points, one FMA per point.  u~ is rounded to FP16
+// for the transfers, where a last-bit difference of a sum can move a value by a half unit of FP16, a thousand times
+// more; in this order u~ does not depend on how the work is split.  v_mfma_f32_16x16x4f32 adds its four products
+// as FMAs one after the other (checked on the device), so rows of nodes by two columns (re, im) give just that chain:
+// l_a l_b l_c of the row's node is the A operand, formed from the chunk's bases in LDS, and every wave takes its own
+// rows.  Bases are evaluated one chunk of 64 points ahead, an axis per wave.  Item (desc, source box, first row tile,
+// waves of row tiles if four more stage, or 0: at least four waves that do both).  The serial chain (16 products
+// of 32 cycles a chunk) and the barrier bound boxes of many points, LDS reads (four per 64 nodes and points) the rest.
+// Ellipsoid, 137k points, r1 = 4, levels 2 to 6: 121, 55, 25, 13, 17 us.
+template <int R1>
+__device__ __forceinline__ void lag_anterp_ord_r1(const LDesc &d, const int4 wk, float (*e)[64 * 3 * kMaxR1],
+                                                  float (*us)[128]) {
+    constexpr int r = R1 * R1 * R1, NRT = (r + 15) / 16, W = 3 * R1;
+    constexpr int MT = NRT > 16 ? 2 : 1;                           // row tiles per wave
+    const int b = wk.y, tid = threadIdx.x, lane = tid & 63, nw = blockDim.x >> 6;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), li = lane & 15, lk = lane >> 4;
+    const double two_over_dl = d.two_over_dl;
+    float nodes[R1], den[R1];
+#pragma unroll
+    for (int a = 0; a < R1; ++a) {
+        nodes[a] = d.lnodes[a];
+        den[a] = d.lden[a];
+    }
+    const int xs = wv - wk.w;                                      // what the wave stages
+    const int nc = wk.w ? wk.w : nw, t0 = wk.z + wv;                                      // first row tile of the wave
+    int ia[MT], ib[MT], ic[MT];
+    floatx4 acc[MT];
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+        const int i = min(16 * (t0 + t * nc) + li, r - 1);
+        ia[t] = i / (R1 * R1);
+        ib[t] = R1 + (i / R1) % R1;
+        ic[t] = 2 * R1 + i % R1;
+        acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    const int i0 = d.sstart[b], i1 = d.sstart[b + 1];
+    // wave wk.w + x, x < 3, evaluates axis x of a chunk and the next one lays down its inputs; the values are loaded a chunk earlier
+    // (in every wave, whatever its part: a load under a condition would be waited for at once)
+    const double *p = xs == 0 ? d.sxs : (xs == 1 ? d.sys : d.szs);
+    const double ctr = d.sctr[3 * b + min(max(xs, 0), 2)];
+    double pn = 0.0;
+    float2 un{0.f, 0.f};
+    auto fetch = [&](int s0) {
+        const int j = min(s0 + lane, i1 - 1);
+        pn = p[j];
+        un = d.u[j];
+    };
+    auto stage = [&](int s0, int buf) {
+        if (xs >= 0 && xs < 3) {
+            float l[R1];
+            lagrange_1d((float)((pn - ctr) * two_over_dl), R1, nodes, den, l);
+#pragma unroll
+            for (int a = 0; a < R1; ++a) e[buf][lane * W + xs * R1 + a] = l[a];
+        } else if (xs == 3) {
+            us[buf][2 * lane] = s0 + lane < i1 ? un.x : 0.f;
+            us[buf][2 * lane + 1] = s0 + lane < i1 ? un.y : 0.f;
+        }
+    };
+    fetch(i0);
+    stage(i0, 0);
+    fetch(i0 + 64);
+    __syncthreads();
+    for (int s0 = i0, buf = 0; s0 < i1; s0 += 64, buf ^= 1) {
+        const int cnt = min(64, i1 - s0);
+        if (s0 + 64 < i1) {
+            stage(s0 + 64, buf ^ 1);
+            fetch(s0 + 128);
+        }
+        // four steps per round (points past the last have u = 0 and leave every sum as it is)
+        if (wv < nc) {
+            for (int p0 = 0; p0 < cnt; p0 += 16) {
+                float a[4][MT], bv[4];
+#pragma unroll
+                for (int h = 0; h < 4; ++h) {
+                    const int pt = p0 + 4 * h + lk;
+                    const float *q = e[buf] + pt * W;
+                    bv[h] = us[buf][2 * pt + (li & 1)];
+#pragma unroll
+                    for (int t = 0; t < MT; ++t) a[h][t] = q[ia[t]] * q[ib[t]] * q[ic[t]];
+                }
+#pragma unroll
+                for (int h = 0; h < 4; ++h)
+#pragma unroll
+                    for (int t = 0; t < MT; ++t)
+                        if (t == 0 || t0 + t * nc < NRT) acc[t] = mfma16(a[h][t], bv[h], acc[t]);
+            }
+        }
+        __syncthreads();
+    }
+    float *ut = reinterpret_cast<float *>(d.ut2 + (int64_t)b * d.rp);
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int i = 16 * (t0 + t * nc) + 4 * lk + v;
+            if (li < 2 && i < r && wv < nc) ut[2 * i + li] = acc[t][v];
+        }
+    if (wk.z == 0)
+        for (int x = 2 * r + tid; x < 2 * d.rp; x += blockDim.x) ut[x] = 0.f;
+}
+
+__global__ void __launch_bounds__(1024)
+k_lag_anterp_ord(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const int4 *__restrict__ work) {
+    __shared__ float e[2][64 * 3 * kMaxR1], us[2][128];
+    const int4 wk = work[blockIdx.x];
+    const LDesc &d = descs[wk.x];
+    switch (d.r1) {
+        case 1: lag_anterp_ord_r1<1>(d, wk, e, us); break;
+        case 2: lag_anterp_ord_r1<2>(d, wk, e, us); break;
+        case 3: lag_anterp_ord_r1<3>(d, wk, e, us); break;
+        case 4: lag_anterp_ord_r1<4>(d, wk, e, us); break;
+        case 5: lag_anterp_ord_r1<5>(d, wk, e, us); break;
+        case 6: lag_anterp_ord_r1<6>(d, wk, e, us); break;
+        case 7: lag_anterp_ord_r1<7>(d, wk, e, us); break;
+        default: lag_anterp_ord_r1<8>(d, wk, e, us); break;
+    }
+}
+
+// Full transfer matrices: Z_e = T_c(e) u~_{s(e)} for every far pair, by class groups of 16 pairs (the columns, real and
+// imaginary parts in two products), four groups of one class per block, one per wave.  T_c is stored in fragment
+// order (rows and nodes of a product in one 16-byte load per lane) and goes through LDS once per block, two
+// buffers, a barrier per step: at one group per load T_c is what the L2s deliver (16 KB per group at r1 = 4; 200 KB in
+// FP16 and complex at r1 = 6) and the products waited for it.  The sources go through the wave's own LDS as in
+// k_lag_project.  What the L2s deliver bounds it still: T_c once per 64 pairs, and the sources' u~.  FP32, r1 = 4: 137k
+// points on an ellipsoid, level 6, 111 -> 63 us; 129k in a cube, 584k pairs, 155 us now.  32 problems of 2k to 137k
+// points in one batch, against a wave per group and operands straight from memory: 9203 -> 4916 us FP32 with the
+// kernels before and after it, FP16 8596 -> 5038 us.
+struct GroupPairs {              // this lane's pair and its sources, one class group per wave
+    int e = -1;
+    gc4 U[4];
+};
+
+__device__ __forceinline__ void group_pairs(const LDesc &d, int grp, bool on, int *srcs, int lane, GroupPairs &p) {
+    p.e = on ? d.grp_pair[(int64_t)grp * 16 + (lane & 15)] : -1;
+    if (lane < 16) srcs[lane] = d.far_src[max(p.e, 0)];
+    wave_lds_fence();
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        p.U[i] = (gc4)(const v4f *)(d.ut2 + (int64_t)srcs[(lane >> 4) + 4 * i] * d.rp) + (lane & 15);
+}
+
+// k_lag_mfma, FP32: v_mfma_f32_16x16x4f32, four row tiles at a time and 32 nodes per step.  T: [class][plane][row
+// tile][block of 16 nodes][64 lanes][4 steps].  Item (desc, first group, groups, 0).
+template <bool HELM>
+__global__ void __launch_bounds__(256)
+k_lag_mfma(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const int4 *__restrict__ work) {
+    constexpr int P = HELM ? 2 : 1, RT = 4;
+    __shared__ v4f sa[2][RT * 2 * P][64];
+    __shared__ float st[4][16 * kProjRow];
+    __shared__ int srcs[4][16];
+    const int4 wk = work[blockIdx.x];
+    const LDesc &d = descs[wk.x];
+    const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, m = lane & 15;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool on = wv < wk.z;
+    const int c = __builtin_amdgcn_readfirstlane(d.grp_cls[wk.y]);
+    const int rp = d.rp, nb = rp >> 4, nrt = (d.r1 * d.r1 * d.r1 + 15) >> 4;
+    GroupPairs gp;
+    group_pairs(d, wk.y + wv, on, srcs[wv], lane, gp);
+    float *sw = st[wv] + g * kProjRow + 4 * m;
+    const float *sr = st[wv] + m * kProjRow + 8 * g;
+    const gc4 T = (gc4)(const v4f *)d.T + (int64_t)c * P * nrt * nb * 64 + lane;
+    for (int rt0 = 0; rt0 < nrt; rt0 += RT) {
+        floatx4 zr[RT], zi[RT];
+#pragma unroll
+        for (int t = 0; t < RT; ++t) zr[t] = zi[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+        v4f u[4], a[2 * P];
+        auto load = [&](int jb) {
+            if (on) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) u[i] = gp.U[i][8 * jb];
+            }
+            // this wave's share of the fragments: row tile wv, both blocks, both planes (tiles past the last repeat it)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int p = 0; p < P; ++p)
+                    a[h * P + p] = T[((int64_t)(p * nrt + min(rt0 + wv, nrt - 1)) * nb + jb + h) * 64];
+        };
+        load(0);
+        for (int jb = 0; jb < nb; jb += 2) {
+            const int buf = (jb >> 1) & 1;
+#pragma unroll
+            for (int q = 0; q < 2 * P; ++q) sa[buf][wv * 2 * P + q][lane] = a[q];
+            if (on) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) *reinterpret_cast<v4f *>(sw + 4 * i * kProjRow) = u[i];
+            }
+            __syncthreads();
+            if (jb + 2 < nb) load(jb + 2);
+            if (!on) continue;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const v4f c0 = *reinterpret_cast<const v4f *>(sr + 32 * h), c1 = *reinterpret_cast<const v4f *>(sr + 32 * h + 4);
+                const float ur[4] = {c0.x, c0.z, c1.x, c1.z}, ui[4] = {c0.y, c0.w, c1.y, c1.w};
+                v4f tr[RT], ti[RT];
+#pragma unroll
+                for (int t = 0; t < RT; ++t) {
+                    tr[t] = sa[buf][t * 2 * P + h * P][lane];
+                    if (HELM) ti[t] = sa[buf][t * 2 * P + h * P + P - 1][lane];
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int t = 0; t < RT; ++t) {
+                        zr[t] = mfma16(tr[t][q], ur[q], zr[t]);
+                        zi[t] = mfma16(tr[t][q], ui[q], zi[t]);
+                        if (HELM) {
+                            zr[t] = mfma16(-ti[t][q], ui[q], zr[t]);
+                            zi[t] = mfma16(ti[t][q], ur[q], zi[t]);
+                        }
+                    }
+            }
+        }
+        // lane (pair m, g) holds rows 4 g .. 4 g + 3 of each tile
+        if (gp.e >= 0) {
+#pragma unroll
+            for (int t = 0; t < RT; ++t)
+                if (rt0 + t < nrt) {
+                    const gm4 Z = (gm4)(v4f *)(d.Z + (int64_t)gp.e * rp + 16 * (rt0 + t) + 4 * g);
+                    Z[0] = v4f{zr[t][0], zi[t][0], zr[t][1], zi[t][1]};
+                    Z[1] = v4f{zr[t][2], zi[t][2], zr[t][3], zi[t][3]};
+                }
+        }
+        __syncthreads();                     // the next tiles' first fragments go over buffers still being read
+    }
+}
+
+// Mixed precision: the same products on FP16 MFMA (v_mfma_f32_16x16x32_f16: 16 rows, 32 nodes) with FP32
+// accumulation.  T16 = T * sT (plan time); the sources are scaled by a power of two s_u derived on the device from
+// max |u| so that |u~ s_u| < 6e4; Z = C / (sT s_u).
 __device__ __forceinline__ float u_scale(float amax, int maxpts) {
     // |u~| <= (Lebesgue constant of the tensor grid, <= 8) * points * max|u|
     const float bound = 8.f * (float)maxpts * fmaxf(amax, 1e-30f);
     return exp2f(floorf(log2f(6.0e4f / bound)));
 }
 
+// k_lag_mfma16: the group's sources stay in registers as operands of all KB = rp / 32 blocks of 32 nodes, and T16 goes
+// by RT row tiles per step, [class][row tile][block][plane][64 lanes][8 nodes].  Item (desc, first group, groups, 0).
+template <bool HELM, int KB>
 __global__ void __launch_bounds__(256)
 k_lag_mfma16(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const int4 *__restrict__ work) {
-    extern __shared__ _Float16 U16[];   // [32][rp]: column-major tile, k contiguous
+    constexpr int P = HELM ? 2 : 1, RT = KB == 1 ? 2 : (KB == 2 ? 4 : (KB == 4 ? 2 : 1)), NF = RT * KB * P;
+    constexpr int NL = (NF + 3) / 4;         // fragments (1 KB each) a wave moves per step
+    __shared__ half8_t sa[2][NF][64];
+    __shared__ float st[4][16 * kProjRow];
+    __shared__ int srcs[4][16];
     const int4 wk = work[blockIdx.x];
     const LDesc &d = descs[wk.x];
-    const int g = wk.y;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nwv = blockDim.x >> 6;
-    const int rp = d.rp, helm = d.helm;
-    const int c = d.grp_cls[g];
-    const float su = u_scale(*d.amax, d.maxpts);
-    __shared__ int pe[16], ps[16];
-    if (tid < 16) {
-        const int e = d.grp_pair[(int64_t)g * 16 + tid];
-        pe[tid] = e;
-        ps[tid] = e >= 0 ? d.far_src[e] : -1;
+    const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, m = lane & 15;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool on = wv < wk.z;
+    const int c = __builtin_amdgcn_readfirstlane(d.grp_cls[wk.y]);
+    const int rp = d.rp, nrt = (d.r1 * d.r1 * d.r1 + 15) >> 4;
+    const float su = u_scale(*d.amax, d.maxpts), inv = 1.f / (d.sT * su);
+    const gch8 T = (gch8)(const half8_t *)d.T16 + (int64_t)c * nrt * KB * P * 64 + lane;
+    half8_t a[NL];
+    auto load = [&](int rt0) {
+        // (fragments past the last row tile's repeat the last fragment)
+#pragma unroll
+        for (int q = 0; q < NL; ++q)
+            a[q] = T[(int64_t)min(rt0 * KB * P + min(wv + 4 * q, NF - 1), nrt * KB * P - 1) * 64];
+    };
+    load(0);
+    GroupPairs gp;
+    group_pairs(d, wk.y + wv, on, srcs[wv], lane, gp);
+    half8_t ur[KB], ui[KB];
+    if (on) {
+        float *sw = st[wv] + g * kProjRow + 4 * m;
+        const float *sr = st[wv] + m * kProjRow + 16 * g;
+        v4f u[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) u[i] = gp.U[i][0];
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) *reinterpret_cast<v4f *>(sw + 4 * i * kProjRow) = u[i];
+            wave_lds_fence();
+            if (kb + 1 < KB) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) u[i] = gp.U[i][16 * (kb + 1)];
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const v4f w = *reinterpret_cast<const v4f *>(sr + 4 * q);
+                ur[kb][2 * q] = (_Float16)(w.x * su);
+                ui[kb][2 * q] = (_Float16)(w.y * su);
+                ur[kb][2 * q + 1] = (_Float16)(w.z * su);
+                ui[kb][2 * q + 1] = (_Float16)(w.w * su);
+            }
+            wave_lds_fence();
+        }
     }
-    __syncthreads();
-    {
-        // entry (m, k): both parts of u~_{s_m}[k] from one 8-byte load (consecutive threads, consecutive k), eight
-        // loads in flight per thread before the LDS writes
-        const int nel = rp * 16, nth = blockDim.x;
-        const gc2 src = gl(d.ut2);
-        for (int base = 0; base < nel; base += 8 * nth) {
-            v2f w[8];
-            int sm[8];
+    for (int rt0 = 0, step = 0; rt0 < nrt; rt0 += RT, ++step) {
+        const int buf = step & 1;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int idx = base + u * nth + tid;
-                sm[u] = idx < nel ? ps[idx / rp] : -1;
-            }
+        for (int q = 0; q < NL; ++q)
+            if (wv + 4 * q < NF) sa[buf][wv + 4 * q][lane] = a[q];
+        __syncthreads();
+        if (rt0 + RT < nrt) load(rt0 + RT);
+        if (!on) continue;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int idx = base + u * nth + tid, m = idx / rp, k = idx - m * rp;
-                w[u] = v2f{0.f, 0.f};
-                if (sm[u] >= 0) w[u] = src[(int64_t)sm[u] * rp + k];
-            }
+        for (int t = 0; t < RT; ++t) {
+            floatx4 zr = floatx4{0.f, 0.f, 0.f, 0.f}, zi = zr, wr = zr, wi = zr;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int idx = base + u * nth + tid, m = idx / rp, k = idx - m * rp;
-                if (idx < nel) {
-                    U16[(2 * m) * rp + k] = (_Float16)(w[u].x * su);
-                    U16[(2 * m + 1) * rp + k] = (_Float16)(w[u].y * su);
+            for (int kb = 0; kb < KB; ++kb) {
+                const half8_t tr = sa[buf][(t * KB + kb) * P][lane];
+                zr = __builtin_amdgcn_mfma_f32_16x16x32_f16(tr, ur[kb], zr, 0, 0, 0);
+                zi = __builtin_amdgcn_mfma_f32_16x16x32_f16(tr, ui[kb], zi, 0, 0, 0);
+                if (HELM) {
+                    const half8_t ti = sa[buf][(t * KB + kb) * P + P - 1][lane];
+                    wr = __builtin_amdgcn_mfma_f32_16x16x32_f16(ti, ui[kb], wr, 0, 0, 0);
+                    wi = __builtin_amdgcn_mfma_f32_16x16x32_f16(ti, ur[kb], wi, 0, 0, 0);
                 }
             }
-        }
-    }
-    __syncthreads();
-    const int64_t per = (int64_t)rp * rp;
-    const _Float16 *Tre = d.T16 + (int64_t)c * (helm ? 2 : 1) * per;
-    const _Float16 *Tim = Tre + per;
-    const int col = lane & 31, kh = lane >> 5;
-    const int e = pe[col >> 1];
-    const float inv = 1.f / (d.sT * su);
-    for (int mt = wv; mt < rp / 32; mt += nwv) {   // the waves share the staged sources, one row tile each
-        floatx16 acc1, acc2;
-        for (int v = 0; v < 16; ++v) {
-            acc1[v] = 0.f;
-            acc2[v] = 0.f;
-        }
-        const int i = mt * 32 + col;
-        // groups of two steps of 16 (rp is a multiple of 32), operands loaded before the group's products
-        const gch8 TreG = (gch8) reinterpret_cast<const half8_t *>(Tre + (int64_t)i * rp + 8 * kh);
-        const gch8 TimG = (gch8) reinterpret_cast<const half8_t *>(Tim + (int64_t)i * rp + 8 * kh);
-        // double-buffered as in the FP32 kernel
-        half8_t a1n[2], a2n[2];
-        auto load = [&](int k00) {
+            if (gp.e >= 0 && rt0 + t < nrt) {
+                float zx[4], zy[4];
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int k0 = k00 + 16 * u;
-                a1n[u] = TreG[k0 / 8];
-                a2n[u] = a1n[u];
-                if (helm) a2n[u] = TimG[k0 / 8];   // Laplace tables have no imaginary part
+                for (int v = 0; v < 4; ++v) {
+                    zx[v] = (HELM ? zr[v] - wr[v] : zr[v]) * inv;
+                    zy[v] = (HELM ? zi[v] + wi[v] : zi[v]) * inv;
+                }
+                const gm4 Z = (gm4)(v4f *)(d.Z + (int64_t)gp.e * rp + 16 * (rt0 + t) + 4 * g);
+                Z[0] = v4f{zx[0], zy[0], zx[1], zy[1]};
+                Z[1] = v4f{zx[2], zy[2], zx[3], zy[3]};
             }
-        };
-        load(0);
-        for (int k00 = 0; k00 < rp; k00 += 32) {
-            half8_t bv[2], a1[2], a2[2];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                bv[u] = *reinterpret_cast<const half8_t *>(U16 + col * rp + k00 + 16 * u + 8 * kh);
-                a1[u] = a1n[u];
-                a2[u] = a2n[u];
-            }
-            if (k00 + 32 < rp) load(k00 + 32);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1[u], bv[u], acc1, 0, 0, 0);
-                if (helm) acc2 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2[u], bv[u], acc2, 0, 0, 0);
-            }
-        }
-        for (int v = 0; v < 16; ++v) {
-            const int row = mt * 32 + 8 * (v >> 2) + 4 * kh + (v & 3);
-            float val = acc1[v];
-            if (helm) {
-                const float sw = __shfl_xor(acc2[v], 1, 64);
-                val = (col & 1) ? val + sw : val - sw;
-            }
-            if (e >= 0) reinterpret_cast<float *>(d.Z + (int64_t)e * rp + row)[col & 1] = val * inv;
         }
     }
 }
@@ -3901,14 +4014,23 @@ KernelFn kernel_of(const Stage &S, int &threads) {
             return S.b ? k_pw_backward_rings<1, 4, true> : k_pw_backward_rings<1, 4, false>;
         case K_BSUM: return k_sum_parts;
         // a = waves per block
-        case K_ANTERP: threads = 64 * std::max(1, S.a); return k_lag_anterp;
+        case K_ANTERP: threads = 64 * std::max(1, S.a); return S.b ? k_lag_anterp_ord : k_lag_anterp;
         case K_ANTERP_DL: threads = 64 * std::max(1, S.a); return k_lag_anterp_dl;
         case K_DIRSCALE: return k_dir_scale;
         case K_DNCOMBINE: return k_dn_combine;
         case K_DLCOMBINE: return k_dl_combine;
-        // a = waves per block (each takes its own 32-row tiles of T over the block's staged sources)
-        case K_MFMA32: threads = 64 * std::max(1, S.a); return k_lag_mfma;
-        case K_MFMA16: threads = 64 * std::max(1, S.a); return k_lag_mfma16;
+        case K_MFMA32: return S.b ? k_lag_mfma<true> : k_lag_mfma<false>;
+        case K_MFMA16:
+            // a = rp / 32
+            switch (S.a) {
+                case 1: return S.b ? k_lag_mfma16<true, 1> : k_lag_mfma16<false, 1>;
+                case 2: return S.b ? k_lag_mfma16<true, 2> : k_lag_mfma16<false, 2>;
+                case 4: return S.b ? k_lag_mfma16<true, 4> : k_lag_mfma16<false, 4>;
+                case 7: return S.b ? k_lag_mfma16<true, 7> : k_lag_mfma16<false, 7>;
+                case 11: return S.b ? k_lag_mfma16<true, 11> : k_lag_mfma16<false, 11>;
+                case 16: return S.b ? k_lag_mfma16<true, 16> : k_lag_mfma16<false, 16>;
+                default: throw Error(FFM_EINTERNAL, "unknown node count");
+            }
         case K_ACA: return S.b ? k_lag_project<true> : k_lag_project<false>;
         case K_EXPAND:
             // a = 100 (row tiles per wave) + waves
@@ -4143,13 +4265,13 @@ std::string kernel_name(int kern, int a, int b) {
             if (a == 102) return "k_pw_backward_rings<2, 2, " + tf(b) + ", 128>";
             return a == 2 ? "k_pw_backward_rings<2, 2, " + tf(b) + ", 256>" : "k_pw_backward_rings<1, 4, " + tf(b) + ", 256>";
         case K_BSUM: return "k_sum_parts";
-        case K_ANTERP: return "k_lag_anterp";
+        case K_ANTERP: return b ? "k_lag_anterp_ord" : "k_lag_anterp";
         case K_ANTERP_DL: return "k_lag_anterp_dl";
         case K_DIRSCALE: return "k_dir_scale";
         case K_DNCOMBINE: return "k_dn_combine";
         case K_DLCOMBINE: return "k_dl_combine";
-        case K_MFMA32: return "k_lag_mfma";
-        case K_MFMA16: return "k_lag_mfma16";
+        case K_MFMA32: return "k_lag_mfma<" + tf(b) + ">";
+        case K_MFMA16: return "k_lag_mfma16<" + tf(b) + ", " + std::to_string(a) + ">";
         case K_ACA: return "k_lag_project<" + tf(b) + ">";
         case K_EXPAND: return "k_lag_expand<" + tf(b) + (a < 200 ? ", 1>" : ", 4>");
         case K_INTERP: return "k_lag_interp";

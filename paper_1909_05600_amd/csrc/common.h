@@ -342,12 +342,13 @@ struct Level {
     int method = kNone;
     // Lagrange
     int r1 = 0, r = 0, rp = 0;           // nodes per axis, r1^3, r padded to a multiple of 32
-    DevBuf<float> T;                     // [ncls][rp][rp] (x2 planes re/im for Helmholtz)
+    DevBuf<float> T;                     // transfer matrices in fragment order (k_lag_mfma), FP32 levels without ACA
+    std::vector<int32_t> h_gcls;         // class of every group
     DevBuf<int32_t> grp_pair;            // [ngrp][16] far pair index (-1 = empty), grouped by class
     DevBuf<int32_t> grp_cls;             // [ngrp]
     int32_t ngrp = 0;
     bool fp16 = false;                   // transfer on FP16 MFMA (mixed precision)
-    DevBuf<_Float16> T16;                // [ncls][rp][rp] (x2 re/im), row-major by target index, times sT
+    DevBuf<_Float16> T16;                // the same times sT in FP16 (k_lag_mfma16), mixed precision
     float sT = 1.f;                      // power-of-two scale of T16
     // ACA factors of the transfer matrices (T is not kept): ranks, padded ranks, their maximum
     bool aca = false;

@@ -536,56 +536,58 @@ __global__ void __launch_bounds__(kThreads) k_remap(int32_t *cls, int64_t n, con
 }
 
 // ------------------------------------------------------------------ Lagrange tables
-// FP16 copy of the FP32 transfer tables, row-major by target index (k contiguous for the MFMA A
-// operand), times a power-of-two scale.
+// T_c[i][j] = G(|r0_c + (d_l / 2)(xi_i - xi_j)|), xi on the tensor Chebyshev grid, rounded to FP32 and, times a
+// power of two, to FP16 (F16); zero padding beyond r.  Stored in the fragment order of the transfer kernels, one
+// thread per lane's 16 bytes (of both planes): FP32 [class][plane][row tile][block of 16 nodes][lane][4 nodes], lane row
+// i % 16 + 16 (node group); FP16 [class][row tile][block of 32 nodes][plane][lane][8 nodes].
+template <bool HELM, bool F16>
 __global__ void __launch_bounds__(kThreads)
-k_to_half(const float *T, int64_t nplanes, int rp, float scale, _Float16 *T16) {
-    const int64_t per = (int64_t)rp * rp;
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= per * nplanes) return;
-    const int64_t pl = g / per, e = g % per;
-    const int i = (int)(e / rp), j = (int)(e % rp);   // element (i, j); T is stored as [j][i]
-    T16[g] = (_Float16)(T[pl * per + (int64_t)j * rp + i] * scale);
-}
-
-// T_c[i][j] = G(|r0_c + (d_l / 2)(xi_i - xi_j)|), xi on the tensor Chebyshev grid; stored transposed
-// (column j contiguous over i) for the MFMA A operand; zero padding beyond r.
-__global__ void __launch_bounds__(kThreads)
-k_lagrange_T(int ncls, const double *r0, int r1, int rp, const double *nodes, double half_dl, int helm, double k,
-             float *T) {
-    const int64_t per = (int64_t)rp * rp;
-    int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= per * ncls) return;
-    const int c = (int)(g / per);
-    const int64_t e = g % per;
-    const int j = (int)(e / rp), i = (int)(e % rp);   // element (i, j) at [c][j][i]
-    const int r = r1 * r1 * r1;
-    float re = 0.f, im = 0.f;
-    if (i < r && j < r) {
-        const int ia[3] = {i / (r1 * r1), (i / r1) % r1, i % r1};
-        const int ja[3] = {j / (r1 * r1), (j / r1) % r1, j % r1};
-        double d2 = 0.0;
-        for (int d = 0; d < 3; ++d) {
-            double dd = r0[3 * c + d] + half_dl * (nodes[ia[d]] - nodes[ja[d]]);
-            d2 += dd * dd;
-        }
-        const double rr = sqrt(d2);
-        const double inv = 1.0 / (4.0 * M_PI * rr);
-        if (helm) {
-            double sn, cs;
-            sincos(k * rr, &sn, &cs);
-            re = (float)(cs * inv);
-            im = (float)(sn * inv);
-        } else {
-            re = (float)inv;
+k_lagrange_T(int ncls, const double *r0, int r1, int nrt, int nb, const double *nodes, double half_dl, double k, float sT,
+             void *out) {
+    constexpr int P = HELM ? 2 : 1, N = F16 ? 8 : 4;
+    const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    const int lane = (int)(t & 63);
+    const int64_t blk = t >> 6;
+    if (blk >= (int64_t)ncls * nrt * nb) return;
+    const int jb = (int)(blk % nb), rt = (int)(blk / nb % nrt), c = (int)(blk / nb / nrt);
+    const int r = r1 * r1 * r1, i = 16 * rt + (lane & 15);
+    const int ia[3] = {i / (r1 * r1), (i / r1) % r1, i % r1};
+    float v[P][N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        const int j = 4 * N * jb + N * (lane >> 4) + u;
+        v[0][u] = v[P - 1][u] = 0.f;
+        if (i < r && j < r) {
+            const int ja[3] = {j / (r1 * r1), (j / r1) % r1, j % r1};
+            double d2 = 0.0;
+            for (int d = 0; d < 3; ++d) {
+                double dd = r0[3 * c + d] + half_dl * (nodes[ia[d]] - nodes[ja[d]]);
+                d2 += dd * dd;
+            }
+            const double rr = sqrt(d2);
+            const double inv = 1.0 / (4.0 * M_PI * rr);
+            if (HELM) {
+                double sn, cs;
+                sincos(k * rr, &sn, &cs);
+                v[0][u] = (float)(cs * inv);
+                v[P - 1][u] = (float)(sn * inv);
+            } else {
+                v[0][u] = (float)inv;
+            }
         }
     }
-    if (helm) {
-        T[(int64_t)c * 2 * per + e] = re;
-        T[(int64_t)c * 2 * per + per + e] = im;
-    } else {
-        T[(int64_t)c * per + e] = re;
-    }
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            if (F16) {
+                const int64_t o = ((((int64_t)c * nrt + rt) * nb + jb) * P + p) * 64 + lane;
+                static_cast<_Float16 *>(out)[o * N + u] = (_Float16)(v[p][u] * sT);
+            } else {
+                const int64_t o = ((((int64_t)c * P + p) * nrt + rt) * nb + jb) * 64 + lane;
+                static_cast<float *>(out)[o * N + u] = v[p][u];
+            }
+        }
 }
 
 // Class groups are formed per region, one of nreg equal ranges of the far pairs (the pairs are in target order, so a
@@ -2102,21 +2104,24 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
                 }
             }
             if (!LV.aca) {
-                LV.T.alloc((size_t)per * LV.ncls * (helm ? 2 : 1));
-                FFM_LAUNCH(k_lagrange_T, nblocks(per * LV.ncls), kThreads, 0, st, LV.ncls, dr0.p, LV.r1, LV.rp, dnodes.p,
-                           0.5 * dl, helm, P.k, LV.T.p);
-            }
-            if (LV.fp16) {
-                LV.sT = (float)std::ldexp(1.0, (int)std::floor(std::log2(4.0 * M_PI * dl)));
-                const int64_t planes = (int64_t)LV.ncls * (helm ? 2 : 1);
-                LV.T16.alloc((size_t)per * planes);
-                FFM_LAUNCH(k_to_half, nblocks(per * planes), kThreads, 0, st, LV.T.p, planes, LV.rp, LV.sT,
-                           LV.T16.p);
-                P.any_fp16 = true;
+                const int nrt = (LV.r + 15) / 16, nb = LV.fp16 ? LV.rp / 32 : LV.rp / 16, planes = helm ? 2 : 1;
+                const int64_t lanes = (int64_t)LV.ncls * nrt * nb * 64;
+                if (LV.fp16) {
+                    LV.sT = (float)std::ldexp(1.0, (int)std::floor(std::log2(4.0 * M_PI * dl)));
+                    LV.T16.alloc((size_t)lanes * planes * 8);
+                    P.any_fp16 = true;
+                } else {
+                    LV.T.alloc((size_t)lanes * planes * 4);
+                }
+                const auto kern = helm ? (LV.fp16 ? k_lagrange_T<true, true> : k_lagrange_T<true, false>)
+                                       : (LV.fp16 ? k_lagrange_T<false, true> : k_lagrange_T<false, false>);
+                FFM_LAUNCH(kern, nblocks(lanes), kThreads, 0, st, LV.ncls, dr0.p, LV.r1, nrt, nb, dnodes.p, 0.5 * dl, P.k,
+                           LV.sT, LV.fp16 ? (void *)LV.T16.p : (void *)LV.T.p);
             }
             DevBuf<int32_t> dgs;
             upload(dgs, gstart, st, SC);
             upload(LV.grp_cls, gcls, st, SC);
+            LV.h_gcls = gcls;
             LV.grp_pair.alloc((size_t)16 * std::max(g, 1));
             FFM_HIP(hipMemsetAsync(LV.grp_pair.p, 0xff, sizeof(int32_t) * 16 * std::max(g, 1), st));
             FFM_HIP(hipMemsetAsync(cursor.p, 0, sizeof(int32_t) * nbin, st));
@@ -2663,7 +2668,14 @@ void plan_stages(Plan &P, const Tune &tu, hipStream_t st, Scratch *keep) {
                     ex.push_back(make_int4(l, i / ex_chunks, i % ex_chunks * ex_rt, 0));
                 });
             } else {
-                xcd_deal(LV.ngrp, [&](int32_t g) { mf.push_back(make_int4(l, g, 0, 0)); });
+                // up to four groups of one class per block
+                std::vector<int32_t> run;
+                for (int32_t g = 0; g < LV.ngrp; ++g)
+                    if (run.empty() || g - run.back() == 4 || LV.h_gcls[(size_t)g] != LV.h_gcls[(size_t)run.back()]) run.push_back(g);
+                run.push_back(LV.ngrp);
+                xcd_deal((int32_t)run.size() - 1, [&](int32_t b) {
+                    mf.push_back(make_int4(l, run[(size_t)b], run[(size_t)b + 1] - run[(size_t)b], 0));
+                });
             }
             // target boxes with many points in ranges of whole 256-point steps, about kInterpBlocks blocks in all
             const double per_blk = LV.pts_tgt / kInterpBlocks;
@@ -2671,17 +2683,32 @@ void plan_stages(Plan &P, const Tune &tu, hipStream_t st, Scratch *keep) {
             for (int32_t t : LV.h_tgt)
                 for (int32_t i = sx[t]; i < sx[t + 1]; i += range)
                     ip.push_back(make_int4(l, t, i, std::min(i + range, sx[t + 1])));
-            const int nwa = anterp_waves(LV.pts_src / std::max<double>(1.0, (double)LV.h_fwd.size()), P.dl);
-            LV.stages.push_back(make_stage(P.dl ? K_ANTERP_DL : K_ANTERP, nwa, 0, s1, l, anterp_shmem(nwa, LV.r1, P.dl),
-                                           std::move(an), st, SC));
+            if (LV.fp16) {
+                // Every node's sum in point order; a wave takes one or two tiles of 16 nodes.  Boxes of many points are
+                // few: their tiles go to blocks of four waves, with four more that stage (8.6k points per box, r1 = 4: 159
+                // -> 121 us).  Up to 256 points are four chunks at most, and the first fetch bounds them.
+                const int tiles = (LV.r + 15) / 16, nwo = std::max(4, tiles <= 16 ? tiles : (tiles + 1) / 2);
+                if (LV.pts_src < 256.0 * LV.h_fwd.size()) {
+                    LV.stages.push_back(make_stage(K_ANTERP, nwo, 1, s1, l, 0, std::move(an), st, SC));
+                } else {
+                    std::vector<int4> sp;
+                    for (const int4 &w : an)
+                        for (int t = 0; t < tiles; t += tiles > 16 ? 8 : 4) sp.push_back({w.x, w.y, t, 4});
+                    LV.stages.push_back(make_stage(K_ANTERP, 8, 1, s1, l, 0, std::move(sp), st, SC));
+                }
+            } else {
+                const int nwa = anterp_waves(LV.pts_src / std::max<double>(1.0, (double)LV.h_fwd.size()), P.dl);
+                LV.stages.push_back(make_stage(P.dl ? K_ANTERP_DL : K_ANTERP, nwa, 0, s1, l, anterp_shmem(nwa, LV.r1, P.dl),
+                                               std::move(an), st, SC));
+            }
             if (LV.aca) {
                 LV.stages.push_back(make_stage(K_ACA, 0, P.kernel == FFM_HELMHOLTZ, -1, l, 0, std::move(mf), st, SC));
                 LV.stages.push_back(make_stage(K_EXPAND, 100 * ex_rt + ex_nw, P.kernel == FFM_HELMHOLTZ, s2, l,
                                                ex_shmem, std::move(ex), st, SC));
             }
             else
-                LV.stages.push_back(make_stage(LV.fp16 ? K_MFMA16 : K_MFMA32, LV.fp16 ? 1 : std::min(4, LV.rp / 32), 0,
-                                               s2, l, (size_t)LV.rp * 32 * (LV.fp16 ? 2 : 4), std::move(mf), st, SC));
+                LV.stages.push_back(make_stage(LV.fp16 ? K_MFMA16 : K_MFMA32, LV.fp16 ? LV.rp / 32 : 0,
+                                               P.kernel == FFM_HELMHOLTZ, s2, l, 0, std::move(mf), st, SC));
             // one wave per block where target boxes hold at most a wave's worth and v~ takes few rows to gather
             const bool one = (LV.aca || LV.r <= 64) && LV.pts_tgt <= 96.0 * (double)std::max<size_t>(1, LV.h_tgt.size());
             LV.stages.push_back(make_stage(P.dn || P.grad ? K_INTERP_DN : K_INTERP, one ? 1 : 4, 0, s3, l, sizeof(float2) * LV.r,

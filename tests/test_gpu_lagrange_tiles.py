@@ -72,3 +72,20 @@ def test_aca_tiles(orc, kernel, r1, eps, shift):
           % (kernel, r1, eps, shift, [round(st["aca_rank"][l], 1) for l in lev], rel(v, op.apply(wu))))
     assert rel(v, op.apply(wu)) < FP32_RTOL
     assert np.array_equal(v, gpu_apply(gp, wu))
+
+
+@pytest.mark.parametrize("kernel,r1", [(0, r1) for r1 in range(1, 9)] + [(1, 2), (1, 5), (1, 6)])
+def test_mixed_node_counts(orc, kernel, r1):
+    """FP16 levels: every count of 32-row slabs of r1^3 nodes, one and two row tiles per wave in the anterpolation, and
+    point counts per box on both sides of 256 (row tiles in blocks of their own above).  u~ and T are each rounded to
+    2^-11, twice for complex T: 2^-10 and 2^-9 of the output."""
+    rng = np.random.default_rng(20 + r1)
+    X = W.sphere_points(21001, rng)
+    wu = ((rng.standard_normal(21001) + 1j * rng.standard_normal(21001)) / 21001).astype(np.complex64)
+    k = 2.0 if kernel else 0.0
+    gp = gpu_plan(X, X, kernel, k, 1e-3, n_leaf=80, r1_override=r1, aca="off", precision=1)
+    g32 = gpu_plan(X, X, kernel, k, 1e-3, n_leaf=80, r1_override=r1, aca="off")
+    v, v32 = gpu_apply(gp, wu), gpu_apply(g32, wu)
+    print("kernel %d r1 %d: mixed vs fp32 %.3e" % (kernel, r1, rel(v, v32)))
+    assert any(gp.stats()["prec"]) and rel(v, v32) < (2.0 ** -9 if kernel else 2.0 ** -10)
+    assert np.array_equal(v, gpu_apply(gp, wu))
