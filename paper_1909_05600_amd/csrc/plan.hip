@@ -620,11 +620,11 @@ k_fill_groups(const int32_t *cls, int64_t n, int64_t per_reg, int ncls, const in
 // first k with |R|_F <= tol |T|_F, so every class meets the tolerance exactly.  The pivot is the first entry in
 // row-major order whose squared modulus is within a relative 2e-9 of the largest, so that entries equal up to
 // rounding (the tensor grid is symmetric) pick the same pivot on every machine.  R stays in global memory (746 KB at
-// r = 216, complex): each step is one read and write of it, in which the next step's sum and largest entry are
-// formed, with each lane's first candidate for the pivot.  The blocks' R together stay within
+// r = 216, complex): each step reads it once and every second one writes it, and forms the next step's sum and
+// largest entry with each lane's first candidate for the pivot.  The blocks' R together stay within
 // kAcaBytes, which the last-level cache holds.  The first `cap` columns of A and B go to FA and FB, [class][cap][r].
-// A 50,000-point Helmholtz plan with ACA at two levels (r = 216 and 125): 70 ms of 16 host threads -> 1.17 and 0.32 ms
-// here, bound by the traffic of R (6 TB/s).
+// A 50,000-point Helmholtz plan with ACA at two levels (r = 216 and 125): 70 ms of 16 host threads -> 0.95 and 0.26 ms
+// here (1.17 and 0.32 with a write in every step, 6 TB/s), bound by the traffic of R.
 constexpr size_t kAcaBytes = (size_t)256 << 20;
 constexpr int kAcaThreads = 512;
 
@@ -647,18 +647,23 @@ struct Largest {
     }
 };
 
+// Every aca_lag-th step writes R; up to aca_lag - 1 factors before it stay in LDS and are applied, in their order, to
+// what is read.  NJ 64-column pieces to a row: as many as the registers hold (r = 216, complex: 1.15 ms writing at every
+// step, 0.92 to 0.95 at every second, 0.99 at every third, which spills).
+constexpr __host__ __device__ int aca_lag(int nj) { return nj <= 1 ? 4 : (nj <= 4 ? 2 : 1); }
+
 // NJ: 64-column pieces of a row (r <= 64 NJ).  A wave walks every nw-th row, its lanes holding their columns' b.
 template <bool HELM, int NJ>
 __global__ void __launch_bounds__(kAcaThreads, 4)
 k_aca(int ncls, const double *r0, const double *nodes, int r1, double dl, double k, double tol, int cap, double *Rall,
       float *FA, float *FB, int32_t *ranks) {
 #pragma clang fp contract(off)
-    constexpr int P = HELM ? 2 : 1, RU = NJ <= 2 ? 4 : 2;      // planes; rows loaded ahead of their use
-    extern __shared__ double acasm[];               // a and b (r entries each), then the waves' partial results
+    constexpr int Q = aca_lag(NJ), P = HELM ? 2 : 1, RU = NJ <= 2 ? 4 : 2;      // planes; rows loaded ahead of their use
+    extern __shared__ double acasm[];               // Q pairs of a and b (r entries each), then the waves' partial results
     const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, nw = nt >> 6;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = r1 * r1 * r1, n = r * r;
-    double *sa = acasm, *sb = sa + P * r, *ssum = sb + P * r, *smax = ssum + 16;
+    double *sa = acasm, *sb = sa + Q * P * r, *ssum = sb + Q * P * r, *smax = ssum + 16;
     __shared__ int spiv;
     double *R = Rall + (size_t)blockIdx.x * n * P;
     auto sq = [&](const double (&v)[P]) { return HELM ? v[0] * v[0] + v[P - 1] * v[P - 1] : v[0] * v[0]; };
@@ -675,7 +680,26 @@ k_aca(int ncls, const double *r0, const double *nodes, int r1, double dl, double
         if (HELM) reinterpret_cast<double2 *>(R)[e] = make_double2(v[0], v[P - 1]);
         else R[e] = v[0];
     };
+    // v - a b
+    auto less = [&](double (&v)[P], double ax, double ay, const double (&b)[P]) {
+        if (HELM) {
+            v[0] = v[0] - (ax * b[0] - ay * b[P - 1]);
+            v[P - 1] = v[P - 1] - (ax * b[P - 1] + ay * b[0]);
+        } else {
+            v[0] = v[0] - ax * b[0];
+        }
+    };
+    int pend = 0;                                    // factors not yet in R
+    auto entry = [&](int i, int j, double (&v)[P]) {
+        get(i * r + j, v);
+        for (int s = 0; s < pend; ++s) {
+            double b[P];
+            for (int p = 0; p < P; ++p) b[p] = sb[P * (s * r + j) + p];
+            less(v, sa[P * (s * r + i)], sa[P * (s * r + i) + P - 1], b);
+        }
+    };
     for (int c = blockIdx.x; c < ncls; c += gridDim.x) {
+        pend = 0;
         Largest big;
         double sum = 0.0;
         double nj[NJ][3];                            // the columns' node coordinates
@@ -747,7 +771,7 @@ k_aca(int ncls, const double *r0, const double *nodes, int r1, double dl, double
                         const int j = 64 * h + lane;
                         if (j < r) {
                             double v[P];
-                            get(i * r + j, v);
+                            entry(i, j, v);
                             if (sq(v) >= thr) at = i * r + j;
                         }
                     }
@@ -760,9 +784,9 @@ k_aca(int ncls, const double *r0, const double *nodes, int r1, double dl, double
             for (int q = tid; q < r; q += nt) {
                 const size_t f = (((size_t)c * cap + rank) * r + q) * P;
                 double x[P], y[P], pv[P];
-                get(q * r + pj, x);
-                get(pi * r + q, y);
-                get(piv, pv);
+                entry(q, pj, x);
+                entry(pi, q, y);
+                entry(pi, pj, pv);
                 if (HELM) {
                     const double pn = pv[0] * pv[0] + pv[P - 1] * pv[P - 1];
                     const double re = (y[0] * pv[0] + y[P - 1] * pv[P - 1]) / pn, im = (y[P - 1] * pv[0] - y[0] * pv[P - 1]) / pn;
@@ -772,8 +796,8 @@ k_aca(int ncls, const double *r0, const double *nodes, int r1, double dl, double
                     y[0] = y[0] / pv[0];
                 }
                 for (int p = 0; p < P; ++p) {
-                    sa[P * q + p] = x[p];
-                    sb[P * q + p] = y[p];
+                    sa[P * (pend * r + q) + p] = x[p];
+                    sb[P * (pend * r + q) + p] = y[p];
                     if (rank < cap) {
                         FA[f + p] = (float)x[p];
                         FB[f + p] = (float)y[p];
@@ -781,43 +805,52 @@ k_aca(int ncls, const double *r0, const double *nodes, int r1, double dl, double
                 }
             }
             __syncthreads();
-            double b[NJ][P];
-#pragma unroll
-            for (int h = 0; h < NJ; ++h)
-                for (int p = 0; p < P; ++p) b[h][p] = sb[P * min(64 * h + lane, r - 1) + p];
             sum = 0.0;
             big = Largest();
-            for (int i0 = wv; i0 < r; i0 += RU * nw) {
-                double v[RU][NJ][P];
+            auto pass = [&](auto depth) {
+                constexpr int D = decltype(depth)::value;      // factors to apply; the last of Q writes
+                double b[D][NJ][P];
 #pragma unroll
-                for (int q = 0; q < RU; ++q)
+                for (int s = 0; s < D; ++s)
 #pragma unroll
-                    for (int h = 0; h < NJ; ++h) get(min(i0 + q * nw, r - 1) * r + min(64 * h + lane, r - 1), v[q][h]);
+                    for (int h = 0; h < NJ; ++h)
+                        for (int p = 0; p < P; ++p) b[s][h][p] = sb[P * (s * r + min(64 * h + lane, r - 1)) + p];
+                for (int i0 = wv; i0 < r; i0 += RU * nw) {
+                    double v[RU][NJ][P];
 #pragma unroll
-                for (int q = 0; q < RU; ++q) {
-                    const int i = i0 + q * nw;
-                    if (i >= r) break;
-                    const double ax = sa[P * i], ay = sa[P * i + P - 1];
-                    double rowmax = 0.0;
+                    for (int q = 0; q < RU; ++q)
 #pragma unroll
-                    for (int h = 0; h < NJ; ++h) {
-                        double w[P];
-                        if (HELM) {
-                            w[0] = v[q][h][0] - (ax * b[h][0] - ay * b[h][P - 1]);
-                            w[P - 1] = v[q][h][P - 1] - (ax * b[h][P - 1] + ay * b[h][0]);
-                        } else {
-                            w[0] = v[q][h][0] - ax * b[h][0];
+                        for (int h = 0; h < NJ; ++h) get(min(i0 + q * nw, r - 1) * r + min(64 * h + lane, r - 1), v[q][h]);
+#pragma unroll
+                    for (int q = 0; q < RU; ++q) {
+                        const int i = i0 + q * nw;
+                        if (i >= r) break;
+#pragma unroll
+                        for (int s = 0; s < D; ++s) {
+                            const double ax = sa[P * (s * r + i)], ay = sa[P * (s * r + i) + P - 1];
+#pragma unroll
+                            for (int h = 0; h < NJ; ++h) less(v[q][h], ax, ay, b[s][h]);
                         }
-                        if (64 * h + lane < r) {
-                            put(i * r + 64 * h + lane, w);
-                            const double m = sq(w);
-                            sum += m;
-                            rowmax = fmax(rowmax, m);
-                        }
+                        double rowmax = 0.0;
+#pragma unroll
+                        for (int h = 0; h < NJ; ++h)
+                            if (64 * h + lane < r) {
+                                if (D == Q) put(i * r + 64 * h + lane, v[q][h]);
+                                const double m = sq(v[q][h]);
+                                sum += m;
+                                rowmax = fmax(rowmax, m);
+                            }
+                        big.add(rowmax, i);
                     }
-                    big.add(rowmax, i);
                 }
+            };
+            switch (pend + 1) {
+                case 1: pass(std::integral_constant<int, 1>()); break;
+                case 2: pass(std::integral_constant<int, Q < 2 ? Q : 2>()); break;
+                case 3: pass(std::integral_constant<int, Q < 3 ? Q : 3>()); break;
+                default: pass(std::integral_constant<int, Q>()); break;
             }
+            pend = pend + 1 == Q ? 0 : pend + 1;
             ++rank;
         }
         if (tid == 0) ranks[c] = rank;
@@ -2058,7 +2091,8 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
                 aca.rank_h = SC.pin<int32_t>(LV.ncls);
                 aca.level = l;
                 aca.r1 = LV.r1;
-                FFM_LAUNCH(aca_kernel(helm, LV.r1), nblk, kAcaThreads, (2 * planes * LV.r + 32) * sizeof(double), st,
+                FFM_LAUNCH(aca_kernel(helm, LV.r1), nblk, kAcaThreads,
+                           (2 * planes * LV.r * aca_lag(LV.r1 <= 4 ? 1 : (LV.r1 <= 6 ? 4 : 8)) + 32) * sizeof(double), st,
                            LV.ncls, dr0.p, dnodes.p, LV.r1, dl, P.k, P.eps / 4.0, aca_cap, aca_R.p, aca.FA.p, aca.FB.p,
                            aca.rank.p);
                 FFM_HIP(hipMemcpyAsync(aca.rank_h, aca.rank.p, sizeof(int32_t) * LV.ncls, hipMemcpyDeviceToHost, st));
