@@ -711,7 +711,7 @@ k_pw_forward_rings(const LDesc *__restrict__ descs, const IoEntry *__restrict__,
     }
 }
 
-// Sum the point-segment partials of the forward transform in segment order.  Item (desc, source box).
+// Sum the point-segment partials of the forward transform, or of the anterpolation, in segment order.  Item (desc, source box).
 __global__ void __launch_bounds__(kThreads)
 k_sum_segments(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const int4 *__restrict__ work) {
     const int4 wk = work[blockIdx.x];
@@ -2132,7 +2132,7 @@ __device__ __forceinline__ void lagrange_1d_deriv(float t, int r1, const float *
 // u~_s = L_Y u_s: u~_s[(a r1 + b) r1 + c] = sum_j l_a(t_x) l_b(t_y) l_c(t_z) u_j, t = 2 (y - c_s) / d_l.
 // With DL (the normal derivative at the sources) the weight of node (a, b, c) is n_j . grad_y of its polynomial:
 // (2 / d_l) (n_x l'_a l_b l_c + n_y l_a l'_b l_c + n_z l_a l_b l'_c); the staged derivative tables carry the
-// factors (2 / d_l) n.  Item (desc, source box).
+// factors (2 / d_l) n.  Item (desc, source box, segment of its points).
 //
 // The sum over the points is a matrix product: rows (a, b), columns (c, part), one step of
 // v_mfma_f32_16x16x4f32 per four points and 16 rows, with l_a l_b as the A and l_c u as the B operand (DL: two
@@ -2142,7 +2142,7 @@ __device__ __forceinline__ void lagrange_1d_deriv(float t, int r1, const float *
 // block barriers; the waves' tiles are added in wave order at the end.  MFMA issue bounds it (96 cycles per
 // four points at r1 = 6 against about 50 for its LDS reads).  Sphere of 1M points, r1 = 6, levels 2 to 6: 974,
 // 282, 96, 72, 82 us with one 256-thread block per box and a thread per node (three LDS reads and four VALU
-// operations per point and node) -> 141, 46, 39, 38, 42 us.
+// operations per point and node) -> 141, 46, 39, 38, 42 us; level 2 in 14 segments per box 52 us and 8 for their sums.
 template <bool DL>
 __host__ __device__ constexpr int anterp_floats(int r1) { return (DL ? 8 : 4) * r1; }   // LDS floats per point
 
@@ -2170,7 +2170,9 @@ __device__ __forceinline__ void lag_anterp_r1(const LDesc &d, const int4 wk, flo
         den[a] = d.lden[a];
     }
     const double cx = d.sctr[3 * b], cy = d.sctr[3 * b + 1], cz = d.sctr[3 * b + 2];
-    const int i0 = d.sstart[b], i1 = d.sstart[b + 1];
+    // this block's segment of the box's points: whole rounds of the block
+    const int per = 64 * nw * ((d.sstart[b + 1] - d.sstart[b] + 64 * nw * d.nsplit - 1) / (64 * nw * d.nsplit));
+    const int i0 = d.sstart[b] + wk.z * per, i1 = min(d.sstart[b + 1], i0 + per);
     for (int s0 = i0 + wv * 64; s0 < i1; s0 += nw * 64) {
         const int cnt = min(64, i1 - s0);
         {
@@ -2242,7 +2244,7 @@ __device__ __forceinline__ void lag_anterp_r1(const LDesc &d, const int4 wk, flo
         wave_lds_fence();
     }
     // entry (row, j) of the product is float row W + j of u~: lane (j, g) holds rows 4 g + v of each tile
-    float *ut = reinterpret_cast<float *>(d.ut2 + (int64_t)b * d.rp);
+    float *ut = reinterpret_cast<float *>((d.nsplit > 1 ? d.part + wk.z * d.part_stride : d.ut) + (int64_t)b * d.npair);
     if (nw == 1) {
 #pragma unroll
         for (int t = 0; t < NT; ++t)

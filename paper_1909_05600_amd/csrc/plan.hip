@@ -2388,6 +2388,9 @@ static void pick_pair_tile(int64_t npair, int ppt_max, int &bs, int &ppt) {
 // CU; every block sums v~ of its box anew).
 constexpr double kInterpBlocks = 1024.0;
 
+// Blocks of a Lagrange level's anterpolation that boxes with many points are cut for.
+constexpr double kAnterpBlocks = 768.0;
+
 // Waves per block of the anterpolation for boxes of avg points on average: one wave serves a leaf box, and boxes
 // of coarse levels (thousands of points in a few tens of boxes) take sixteen, eight for the double layer, whose
 // points stage twice the LDS.
@@ -2731,9 +2734,30 @@ void plan_stages(Plan &P, const Tune &tu, hipStream_t st, Scratch *keep) {
                     LV.stages.push_back(make_stage(K_ANTERP, 8, 1, s1, l, 0, std::move(sp), st, SC));
                 }
             } else {
-                const int nwa = anterp_waves(LV.pts_src / std::max<double>(1.0, (double)LV.h_fwd.size()), P.dl);
-                LV.stages.push_back(make_stage(P.dl ? K_ANTERP_DL : K_ANTERP, nwa, 0, s1, l, anterp_shmem(nwa, LV.r1, P.dl),
-                                               std::move(an), st, SC));
+                const double avg = LV.pts_src / std::max<double>(1.0, (double)LV.h_fwd.size());
+                const int nwa = anterp_waves(avg, P.dl);
+                // Few boxes of many points: segments of at least a round of the block, about kAnterpBlocks blocks in all,
+                // their sums (in Z, which no transfer has written yet) added by k_sum_segments.  56 boxes of 18k points,
+                // r1 = 6: 141 -> 52 + 8 us in 14 segments; 272 boxes of 3.7k points 46 us either way and the launch 6:
+                // none below four segments.
+                const size_t per_seg = (size_t)P.ty->lev[l].nbox * LV.rp;
+                int split = (int)std::min({16.0, avg / (64.0 * nwa), std::ceil(kAnterpBlocks / (double)std::max<size_t>(1, LV.h_fwd.size())),
+                                           (double)(P.ws_z / std::max<size_t>(1, per_seg))});
+                if (split < 4) split = 1;
+                LV.qSplit = split;
+                if (split > 1) {
+                    std::vector<int4> sp, sm;
+                    for (const int4 &w : an) {
+                        for (int g = 0; g < split; ++g) sp.push_back({w.x, w.y, g, 0});
+                        sm.push_back(w);
+                    }
+                    LV.stages.push_back(make_stage(P.dl ? K_ANTERP_DL : K_ANTERP, nwa, 0, -1, l, anterp_shmem(nwa, LV.r1, P.dl),
+                                                   std::move(sp), st, SC));
+                    LV.stages.push_back(make_stage(K_SUM, 0, 0, s1, l, 0, std::move(sm), st, SC));
+                } else {
+                    LV.stages.push_back(make_stage(P.dl ? K_ANTERP_DL : K_ANTERP, nwa, 0, s1, l, anterp_shmem(nwa, LV.r1, P.dl),
+                                                   std::move(an), st, SC));
+                }
             }
             if (LV.aca) {
                 LV.stages.push_back(make_stage(K_ACA, 0, P.kernel == FFM_HELMHOLTZ, -1, l, 0, std::move(mf), st, SC));
@@ -2950,9 +2974,10 @@ LDesc make_desc(const Plan &P, int l, int inst, float2 *u, float2 *v, float *ama
     d.ucomp = w.ucomp;
     d.utx = w.utx;
     d.utstride = (int64_t)P.ws_src;
-    d.part = w.part;
-    d.npair = LV.npair;
-    d.part_stride = (int64_t)LY.nbox * LV.npair;
+    // (a Lagrange level's rp values of a box go as rp / 2 pairs)
+    d.part = LV.method == kGegenbauer ? w.part : reinterpret_cast<float4 *>(w.Z);
+    d.npair = LV.method == kGegenbauer ? LV.npair : LV.rp / 2;
+    d.part_stride = (int64_t)LY.nbox * d.npair;
     d.L = LV.L;
     d.nrp = LV.nrp;
     d.Tr = LV.Tr;

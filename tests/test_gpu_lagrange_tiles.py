@@ -51,6 +51,29 @@ def test_points_per_box(orc, n, dl):
         assert rel(gpu_apply(gt, w2), oracle_like(orc, gt, Y, X, 0, 0.0, 1e-3, **kw).apply(w2)) < FP32_RTOL
 
 
+@pytest.mark.parametrize("dl", [False, True])
+def test_point_segments(orc, dl):
+    """Level 2 with 16 boxes of 6250 points on average and boxes of a few hundred: segments (of whole rounds of a
+    block, the last ones empty in small boxes) whose sums are added after."""
+    import torch
+    import paper_1909_05600_amd as ffm
+    n = 100001
+    rng = np.random.default_rng(n)
+    Y = W.ellipsoid_points(n, rng)
+    X = W.sphere_points(500, rng) * 0.9
+    wu = ((rng.standard_normal(n) + 1j * rng.standard_normal(n)) / n).astype(np.complex64)
+    nrm = Y / np.linalg.norm(Y, axis=1, keepdims=True)
+    kw = {"source_normals": torch.from_numpy(nrm).cuda()} if dl else {}
+    kernel = 4 if dl else 0
+    gp = ffm.Plan(torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda(), kernel, 0.0, 1e-3, max_level=3, timing=True, **kw)
+    v = gpu_apply(gp, wu)
+    assert any(r["kernel"] == "k_sum_segments" for r in gp.launch_timing())
+    vo = oracle_like(orc, gp, X, Y, kernel, 0.0, 1e-3, max_level=3, **({"source_normals": nrm} if dl else {})).apply(wu)
+    print("dl %d: vs oracle %.3e" % (dl, rel(v, vo)))
+    assert rel(v, vo) < FP32_RTOL
+    assert np.array_equal(v, gpu_apply(gp, wu))
+
+
 @pytest.mark.parametrize("kernel,r1,eps,shift", [(0, 1, 1e-3, False), (0, 2, 1e-3, False), (0, 3, 1e-3, True),
                                                  (0, 4, 1e-3, False), (1, 3, 1e-3, False), (1, 5, 1e-3, True),
                                                  (0, 7, 1e-5, False), (1, 7, 1e-6, False)])
