@@ -2138,13 +2138,14 @@ __device__ __forceinline__ void lagrange_1d_deriv(float t, int r1, const float *
 // v_mfma_f32_16x16x4f32 per four points and 16 rows, with l_a l_b as the A and l_c u as the B operand (DL: two
 // steps, A = l'_a l_b + l_a l'_b with B = l_c u, then A = l_a l_b with B = l'_c u).  Each wave takes every
 // nw-th 64 points of the box: a lane evaluates one point's bases into the wave's own part of LDS, which the
-// wave then reads as operands (rows of 2 r1 floats: the four points of a step lie in distinct banks), without
+// wave then reads as operands (an odd number of floats per point: the lanes' writes lie in distinct banks), without
 // block barriers; the waves' tiles are added in wave order at the end.  MFMA issue bounds it (96 cycles per
 // four points at r1 = 6 against about 50 for its LDS reads).  Sphere of 1M points, r1 = 6, levels 2 to 6: 974,
 // 282, 96, 72, 82 us with one 256-thread block per box and a thread per node (three LDS reads and four VALU
-// operations per point and node) -> 141, 46, 39, 38, 42 us; level 2 in 14 segments per box 52 us and 8 for their sums.
+// operations per point and node) -> 141, 46, 39, 38, 42 us; level 2 in 14 segments
+// per box 52 us and 8 for their sums; with 25 floats per point instead of 24 43, 39, 32, 34, 34 us.
 template <bool DL>
-__host__ __device__ constexpr int anterp_floats(int r1) { return (DL ? 8 : 4) * r1; }   // LDS floats per point
+__host__ __device__ constexpr int anterp_floats(int r1) { return (DL ? 8 : 4) * r1 + 1; }   // LDS floats per point
 
 template <bool DL, int R1>
 __device__ __forceinline__ void lag_anterp_r1(const LDesc &d, const int4 wk, float *sm) {

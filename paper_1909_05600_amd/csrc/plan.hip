@@ -2399,7 +2399,7 @@ int anterp_waves(double avg, bool dl) { return avg <= 192.0 ? 1 : (avg <= 1024.0
 // Its dynamic LDS: 64 points per wave (the waves' tiles, r1^2 x 2 r1 floats each, fit in the same space), rounded
 // up to 6 or 8 nodes per axis so that a batch's instances of different r1 share launches.
 size_t anterp_shmem(int nw, int r1, bool dl) {
-    return (size_t)nw * 64 * (dl ? 8 : 4) * (r1 <= 6 ? 6 : 8) * sizeof(float);
+    return (size_t)nw * 64 * ((dl ? 8 : 4) * (r1 <= 6 ? 6 : 8) + 1) * sizeof(float);
 }
 
 // log2 of the waves per box of a near-field launch over `boxes` boxes of `chunks` source chunks each on average (about
@@ -2738,8 +2738,8 @@ void plan_stages(Plan &P, const Tune &tu, hipStream_t st, Scratch *keep) {
                 const int nwa = anterp_waves(avg, P.dl);
                 // Few boxes of many points: segments of at least a round of the block, about kAnterpBlocks blocks in all,
                 // their sums (in Z, which no transfer has written yet) added by k_sum_segments.  56 boxes of 18k points,
-                // r1 = 6: 141 -> 52 + 8 us in 14 segments; 272 boxes of 3.7k points 46 us either way and the launch 6:
-                // none below four segments.
+                // r1 = 6: 141 -> 52 + 8 us in 14 segments (43 + 8 since); 272 boxes of 3.7k points 46 us either way and
+                // the launch 6: none below four segments.
                 const size_t per_seg = (size_t)P.ty->lev[l].nbox * LV.rp;
                 int split = (int)std::min({16.0, avg / (64.0 * nwa), std::ceil(kAnterpBlocks / (double)std::max<size_t>(1, LV.h_fwd.size())),
                                            (double)(P.ws_z / std::max<size_t>(1, per_seg))});
