@@ -2404,10 +2404,12 @@ size_t anterp_shmem(int nw, int r1, bool dl) {
 
 // log2 of the waves per box of a near-field launch over `boxes` boxes of `chunks` source chunks each on average (about
 // one per near pair; the symmetric pass visits half of them): enough waves for two rounds of the chip, at most eight,
-// and at most four for every three chunks (early lists have few).
-int near_waves(size_t boxes, double chunks) {
+// and at most four for every three chunks (early lists have few).  Two at most in the ordered kernels, whose waves all
+// stage for the box's few targets: 488 boxes of 8 targets and 15 chunks of 20 sources, normal derivative, 44, 39, 53 and
+// 88 us with 1, 2, 4 and 8.
+int near_waves(size_t boxes, double chunks, int most) {
     int lg = 0;
-    while (lg < 3 && (boxes << lg) < 8192 && (double)(2 << lg) * 0.75 <= chunks) ++lg;
+    while (lg < most && (boxes << lg) < 8192 && (double)(2 << lg) * 0.75 <= chunks) ++lg;
     return lg;
 }
 
@@ -2794,18 +2796,18 @@ void plan_stages(Plan &P, const Tune &tu, hipStream_t st, Scratch *keep) {
             if (P.lev[l].h_early.empty()) continue;
             std::vector<int4> er;
             for (int32_t t : P.lev[l].h_early) er.push_back(make_int4(l, t, 0, 0));
-            const int a = big(l) + 16 * near_waves(er.size(), (double)P.lev[l].nearly / (double)er.size());
+            const int a = big(l) + 16 * near_waves(er.size(), (double)P.lev[l].nearly / (double)er.size(), 1);
             P.post.push_back(make_stage(near_kern, a, nhelm, -1, l, near_shmem(near_kern, a), std::move(er), st, SC));
         }
         const double per_box = (double)P.lev[P.leaf].nnear / (double)std::max<size_t>(1, nr.size());
         if (P.near_sym) {
             std::vector<int4> ga = nr;
             const int nrm = P.grad ? 3 : (P.dn ? 1 : (P.dl ? 2 : 0));
-            const int a = big(P.leaf) + 2 * nrm + 16 * near_waves(nr.size(), 0.5 * per_box);
+            const int a = big(P.leaf) + 2 * nrm + 16 * near_waves(nr.size(), 0.5 * per_box, 3);
             P.post.push_back(make_stage(K_NEAR_SYM, a, nhelm, -1, P.leaf, near_shmem(K_NEAR_SYM, a), std::move(nr), st, SC));
             P.post.push_back(make_stage(K_NEAR_GATHER, 0, 0, 61, P.leaf, 0, std::move(ga), st, SC));
         } else {
-            const int a = big(P.leaf) + 16 * near_waves(nr.size(), per_box);
+            const int a = big(P.leaf) + 16 * near_waves(nr.size(), per_box, 1);
             P.post.push_back(make_stage(near_kern, a, nhelm, 61, P.leaf, near_shmem(near_kern, a), std::move(nr), st, SC));
         }
         P.post.push_back(make_stage(K_PERM_OUT, 0, 0, 62, 0, 0, std::move(po), st, SC));
