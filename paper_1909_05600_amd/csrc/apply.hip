@@ -2413,9 +2413,9 @@ k_lag_project(const LDesc *__restrict__ descs, const IoEntry *__restrict__, cons
 // rows and 4 ranks per v_mfma_f32_16x16x4f32.  A wave keeps RT row tiles of the group (the last block of a group the
 // one or two that are left) in registers and walks its share of the group's units; A_c is stored in fragment order
 // ([class][rank tile][row tile][plane][lane][4 steps]), so a unit is RT + 1 loads of 16 bytes per lane (twice that
-// for the complex kernel), issued one or two units ahead (the unit list is staged in
-// LDS: read from memory unit by unit it put its misses into the chain, 335 -> 517 us at level 6).  A target without the class has a
-// zero column: half of them on a sphere (a quarter in a volume), which still costs less than FMAs on the VALU
+// for the complex kernel), issued one or two units ahead (the unit list is staged in LDS, kExpandUnits at a time: read
+// from memory unit by unit it put its misses into the chain, 335 -> 517 us at level 6).  A target without the class has
+// a zero column: half of them on a sphere (a quarter in a volume), which still costs less than FMAs on the VALU
 // with Y_e broadcast (LDS or scalar loads in a serial chain per pair).  The complex kernel, whose A_c is twice as
 // long, takes two tiles of eight targets per group for each load of A_c, and leaves a tile out where none of its
 // targets has the class.  The waves' tiles are added in wave order in LDS.  Item (desc, target group, first row tile).
@@ -2427,11 +2427,9 @@ __device__ __forceinline__ void lag_expand_body(const LDesc &d, const int grp, c
     const int col = lane & 15, g = lane >> 4, part = col & 1;
     const int r = d.r1 * d.r1 * d.r1, nrt = (r + 15) >> 4, kt = d.aca_kt;
     const int off = __builtin_amdgcn_readfirstlane(d.exp_ptr[grp]), n = __builtin_amdgcn_readfirstlane(d.exp_cnt[grp]);
-    // the group's units in LDS: addresses then depend on no load in flight
-    int *se = reinterpret_cast<int *>(sm), *sc = se + 8 * CT * n;      // [n][8 CT] pairs, [n] codes
-    for (int i = tid; i < 8 * CT * n; i += blockDim.x) se[i] = d.exp_e[(int64_t)off * (8 * CT) + i];
-    for (int i = tid; i < n; i += blockDim.x) sc[i] = d.exp_cls[off + i];
-    const int q0 = n * wv / nw, q1 = n * (wv + 1) / nw;
+    const int cap = min(n, kExpandUnits);                              // units staged at a time
+    int *se = reinterpret_cast<int *>(sm), *sc = se + 8 * CT * cap;    // [cap][8 CT] pairs, [cap] codes
+    int q1 = 0;                                                        // end of the wave's share
     const uint32_t ustride = (uint32_t)nrt * NP * 1024;        // bytes of A per (class, rank tile)
     const gcb A0 = (gcb)(d.acaA) + (uint32_t)rt0 * NP * 1024;
     const gcb Y0 = (gcb)(d.Z);
@@ -2449,7 +2447,6 @@ __device__ __forceinline__ void lag_expand_body(const LDesc &d, const int grp, c
     // operands in flight: two units ahead, one for the complex kernel's four tiles (registers)
     constexpr int NB = HELM && RT == 4 ? 2 : 3;
     Unit buf[NB];
-    __syncthreads();
     auto load = [&](int q, Unit &u) {
         q = min(q, q1 - 1);
         const uint32_t code = __builtin_amdgcn_readfirstlane(sc[q]), kb = (code >> 2) & 7;
@@ -2490,7 +2487,16 @@ __device__ __forceinline__ void lag_expand_body(const LDesc &d, const int grp, c
             }
         }
     };
-    if (q0 < q1) {
+    for (int p0 = 0; p0 < n; p0 += cap) {
+        // the units in LDS: addresses then depend on no load in flight
+        const int cnt = min(cap, n - p0);
+        if (p0) __syncthreads();
+        for (int i = tid; i < 8 * CT * cnt; i += blockDim.x) se[i] = d.exp_e[(int64_t)(off + p0) * (8 * CT) + i];
+        for (int i = tid; i < cnt; i += blockDim.x) sc[i] = d.exp_cls[off + p0 + i];
+        __syncthreads();
+        const int q0 = cnt * wv / nw;
+        q1 = cnt * (wv + 1) / nw;
+        if (q0 == q1) continue;
 #pragma unroll
         for (int i = 0; i < NB - 1; ++i) load(q0 + i, buf[i]);
         for (int q = q0; q < q1; q += NB) {

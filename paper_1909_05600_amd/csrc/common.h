@@ -157,6 +157,11 @@ constexpr int kMaxLev = 20;               // deepest level
 constexpr size_t kGridBatchBytes = (size_t)512 << 20;   // grid form: G and H of the boxes in flight at one level
 constexpr int kWin = 12;                  // translation window per axis
 constexpr int kWin3 = kWin * kWin * kWin; // window cells per level
+constexpr size_t kLdsBytes = (size_t)160 << 10;   // LDS of a CU, the most a block can ask for
+// k_lag_expand: units of a target group in LDS at a time, 36 bytes each (Helmholtz 68, 136 KB).  A group's own number
+// is not bounded by the LDS: 16 targets of two shifted sets meet up to 448 classes of up to 8 rank tiles.
+constexpr int kExpandUnits = 2048;
+static_assert(kExpandUnits * 68 <= kLdsBytes, "the units of a piece must fit");
 
 struct TreeLevel {
     int32_t nbox = 0;

@@ -1354,7 +1354,7 @@ const int32_t *expand_lists(Level &LV, int G, hipStream_t st, Scratch &SC) {
     LV.exp_cnt.alloc((size_t)ng);
     LV.exp_cls.alloc((size_t)off);
     LV.exp_e.alloc((size_t)off * G);
-    // (at most kWin^3 classes: 110 KB of LDS at G = 16, the most a launch asks for)
+    static_assert(sizeof(int32_t) * 16 * kWin3 <= kLdsBytes, "a group's table of all classes must fit");
     FFM_LAUNCH(G == 16 ? k_expand_fill<16> : k_expand_fill<8>, ng, kThreads, sizeof(int32_t) * G * LV.ncls, st, LV.exp_tgt.p,
                LV.far_ptr.p, LV.far_cls.p, LV.ncls, LV.acaKp.p, LV.exp_ptr.p, LV.exp_cnt.p, LV.exp_cls.p, LV.exp_e.p);
     int32_t *cnt = SC.pin<int32_t>((size_t)ng);
@@ -2276,6 +2276,7 @@ void plan_sync_ready(Plan &P) {
 namespace {
 Stage make_stage(int kern, int a, int b, int slot, int level, size_t shmem, std::vector<int4> &&items, hipStream_t st,
                  Scratch &SC) {
+    FFM_CHECK(shmem <= kLdsBytes, FFM_EINTERNAL, "ffm_plan: a stage's LDS request exceeds a CU's");
     Stage S;
     S.kern = kern;
     S.a = a;
@@ -2698,8 +2699,10 @@ void plan_stages(Plan &P, const Tune &tu, hipStream_t st, Scratch *keep) {
             const int ex_rt = LV.aca && (int64_t)LV.exp_cnt.n * ((nrt + 3) / 4) >= 192 ? 4 : 1;
             const int ex_chunks = (nrt + ex_rt - 1) / ex_rt;
             const int ex_nw = ex_rt == 1 ? 16 : ((int64_t)LV.exp_cnt.n * ex_chunks < 4096 ? 8 : 2);
-            // its LDS: a group's units (in steps of 64, so that a batch's levels share launches), or the waves' tiles
-            const size_t ex_shmem = std::max((size_t)((LV.exp_max + 63) / 64 * 64) * 4 * (P.kernel == FFM_HELMHOLTZ ? 17 : 9),
+            // its LDS: a group's units, kExpandUnits at most (in steps of 64, so that a batch's levels share launches), or
+            // the waves' tiles
+            const size_t ex_shmem = std::max((size_t)std::min((LV.exp_max + 63) / 64 * 64, kExpandUnits) * 4 *
+                                                 (P.kernel == FFM_HELMHOLTZ ? 17 : 9),
                                              (size_t)ex_nw * ex_rt * 256 * sizeof(float));
             if (LV.aca) {
                 xcd_deal((LV.ngrp + 3) / 4, [&](int32_t b) { mf.push_back(make_int4(l, 4 * b, LV.ngrp, 0)); });

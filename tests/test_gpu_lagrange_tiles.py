@@ -112,3 +112,36 @@ def test_mixed_node_counts(orc, kernel, r1):
     print("kernel %d r1 %d: mixed vs fp32 %.3e" % (kernel, r1, rel(v, v32)))
     assert any(gp.stats()["prec"]) and rel(v, v32) < (2.0 ** -9 if kernel else 2.0 ** -10)
     assert np.array_equal(v, gpu_apply(gp, wu))
+
+
+def test_aca_units_in_pieces():
+    """Two cubes half a leaf box apart, Helmholtz with eight nodes per axis at k d = 18: 448 classes per octant with
+    ranks up to 125, so a target group's unit list (68 bytes a unit) is longer than the LDS holds and is staged in
+    pieces.  Against the same product with the full matrices: the factors meet a relative 2.5e-8, so the two differ by
+    FP32 rounding."""
+    import paper_1909_05600_amd as ffm
+    rng = np.random.default_rng(8)
+    n, box = 12000, 1.0 / 8
+    X, Y = rng.random((n, 3)), rng.random((n, 3))
+    X[0], X[1], Y[0], Y[1] = 0.0, 1.0, 0.0, 1.0
+    Y += box / 2
+    wu = ((rng.standard_normal(n) + 1j * rng.standard_normal(n)) / n).astype(np.complex64)
+    kw = dict(n_leaf=4, max_level=3, r1_override=8, kd_switch=25.0)
+    gp = gpu_plan(X, Y, 1, 18.0 / box, 1e-7, **kw)
+    assert gp.stats()["aca"][3]
+    ranks = {tuple(int(x) for x in q[:3]): int(q[3]) for q in gp.export(ffm.FFM_EXPORT_ACA_RANK, 0, 3)}
+    assert max(ranks.values()) <= 128
+    # the target groups: 16 targets of one octant of their parents, in Morton order
+    ijk = gp.export(ffm.FFM_EXPORT_BOX_IJK, 0, 3)
+    far = gp.export(ffm.FFM_EXPORT_FAR, 0, 3)
+    units = 0
+    for octant in range(8):
+        ts = [t for t in np.unique(far[:, 0]) if tuple(ijk[t] & 1) == (octant >> 2, octant >> 1 & 1, octant & 1)]
+        for g in range(0, len(ts), 16):
+            cls = {tuple(int(x) for x in q) for q in far[np.isin(far[:, 0], ts[g:g + 16])][:, 2:5]}
+            units = max(units, sum((ranks[c] + 15) // 16 for c in cls))
+    v, full = gpu_apply(gp, wu), gpu_apply(gpu_plan(X, Y, 1, 18.0 / box, 1e-7, aca="off", **kw), wu)
+    print("ranks up to %d, %d units in the largest group: vs full matrices %.3e" % (max(ranks.values()), units, rel(v, full)))
+    assert 68 * units > 160 * 1024
+    assert rel(v, full) < FP32_RTOL
+    assert np.array_equal(v, gpu_apply(gp, wu))
