@@ -3026,7 +3026,8 @@ k_lag_interp_dn(const LDesc *__restrict__ descs, const IoEntry *__restrict__, co
 
 // ------------------------------------------------------------------ near field (leaf)
 // v_i += sum_{s in near(t)} sum_{j in s, r_ij > 0} G(r_ij) u_j.  One block per target box, of one wave or, where boxes
-// are too few to fill the chip, of two to eight, which share the box's source chunks (plan.hip, near_waves).  A chunk
+// are too few to fill the chip, of two (in the symmetric pass of one set up to eight), which share the box's source
+// chunks (plan.hip, near_waves).  A chunk
 // whose list entry, range and points were fetched one after the other cost three memory latencies, more than its
 // evaluation: with the list in LDS and the next chunk's points loaded ahead, and the waves, 26 -> 14 us for 4096 points
 // (Laplace, 260 boxes), 150 -> 55 for 50,000 (1295 boxes), 237 -> 171 for 262,000 (4636), 536 -> 469 for 1M (18,354,
@@ -3236,8 +3237,11 @@ struct NearWave {
 };
 extern __shared__ __align__(16) char near_raw[];
 
-// Add a pass's sums to the output: every wave's partial sums a[k] of its lanes go to its LDS, and the first wave adds,
-// per target, the waves' R partial sums each in order.
+// Add a pass's sums to the output: every wave's partial sums a[k] of its lanes go to its LDS, and one thread per target
+// adds the waves' R partial sums each in order, eight reads ahead of their sums.  (With the g lanes of the first wave
+// going through all T targets of a lane, read by read, this was the larger part of a block with few sources: two waves
+// per box then cost more than they gave, four of them 125 us for 64 boxes of 8 targets and 27 lists of 4 sources,
+// gradient, against 62 with one.)
 template <class W, int T>
 __device__ __forceinline__ void near_reduce(W *waves, const float (&are)[T], const float (&aim)[T], int g, int R, int nt,
                                             float2 *out) {
@@ -3247,25 +3251,26 @@ __device__ __forceinline__ void near_reduce(W *waves, const float (&are)[T], con
 #pragma unroll
     for (int k = 0; k < T; ++k) part[k * 64 + lane] = make_float2(are[k], aim[k]);
     __syncthreads();
-    if (wv == 0 && lane < g) {
+    for (int ti = threadIdx.x; ti < nt; ti += blockDim.x) {
+        const int k = ti / g, at = k * 64 + (ti - k * g);
+        float2 a = make_float2(0.f, 0.f), o = out[ti];
+        for (int w = 0; w < nw; ++w) {
+            const float2 *pw = reinterpret_cast<const float2 *>(waves[w].sm.x) + at;
+            for (int r0 = 0; r0 < R; r0 += 8) {
+                float2 b[8];
 #pragma unroll
-        for (int k = 0; k < T; ++k) {
-            const int ti = lane + g * k;
-            if (ti >= nt) break;
-            float2 a = make_float2(0.f, 0.f);
-            for (int w = 0; w < nw; ++w) {
-                const float2 *pw = reinterpret_cast<const float2 *>(waves[w].sm.x) + k * 64 + lane;
-                for (int rr = 0; rr < R; ++rr) {
-                    const float2 b = pw[rr * g];
-                    a.x += b.x;
-                    a.y += b.y;
-                }
+                for (int u = 0; u < 8; ++u) b[u] = pw[min(r0 + u, R - 1) * g];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (r0 + u < R) {
+                        a.x += b[u].x;
+                        a.y += b[u].y;
+                    }
             }
-            float2 o = out[ti];
-            o.x += a.x;
-            o.y += a.y;
-            out[ti] = o;
         }
+        o.x += a.x;
+        o.y += a.y;
+        out[ti] = o;
     }
     __syncthreads();
 }

@@ -2404,10 +2404,12 @@ size_t anterp_shmem(int nw, int r1, bool dl) {
 }
 
 // log2 of the waves per box of a near-field launch over `boxes` boxes of `chunks` source chunks each on average (about
-// one per near pair; the symmetric pass visits half of them): enough waves for two rounds of the chip, at most eight,
-// and at most four for every three chunks (early lists have few).  Two at most in the ordered kernels, whose waves all
-// stage for the box's few targets: 488 boxes of 8 targets and 15 chunks of 20 sources, normal derivative, 44, 39, 53 and
-// 88 us with 1, 2, 4 and 8.
+// one per near pair; the symmetric pass visits half of them): enough waves for two rounds of the chip, and at most four
+// for every three chunks (early lists have few).  At most `most`: eight waves in the symmetric kernels, two in the
+// ordered ones, whose best count depends on the points per box as well.  Helmholtz gradient with 1, 2 and 4 waves, us:
+// 512 boxes of a cube, 8 targets and 4 sources each 72, 57, 50, 64 and 64 606, 361, 210; 4600 boxes of a sphere 68, 76,
+// 116 and 810, 640, 637; 1150 boxes 40, 39, 49 and 466, 304, 224.  Two lose at most a sixth to one where boxes hold a
+// few points each, four up to 1.7 times.
 int near_waves(size_t boxes, double chunks, int most) {
     int lg = 0;
     while (lg < most && (boxes << lg) < 8192 && (double)(2 << lg) * 0.75 <= chunks) ++lg;
