@@ -2689,7 +2689,12 @@ __device__ __forceinline__ void group_pairs(const LDesc &d, int grp, bool on, in
 }
 
 // k_lag_mfma, FP32: v_mfma_f32_16x16x4f32, four row tiles at a time and 32 nodes per step.  T: [class][plane][row
-// tile][block of 16 nodes][64 lanes][4 steps].  Item (desc, first group, groups, 0).
+// tile][block of 16 nodes][64 lanes][4 steps].  Item (desc, first group, groups, first row tile):
+// a block takes four row tiles, for its few blocks are not enough to fill the chip where classes have few pairs, and its
+// sources pass through LDS once per four tiles in any case.  (Node counts above r1 = 4, all row tiles in one block ->
+// four, against one group per block and a row tile per wave: 4000 points on a sphere, Helmholtz, r1 = 6, 7, 8, the
+// product with both levels 322, 671, 1218 -> 211, 379, 638 against 248, 467, 767 us; 200,000 points 1769, 3753, 6895 ->
+// 1618, 3334, 6004 against 2371, 4558, 8168.)
 template <bool HELM>
 __global__ void __launch_bounds__(256)
 k_lag_mfma(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const int4 *__restrict__ work) {
@@ -2709,69 +2714,67 @@ k_lag_mfma(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const i
     float *sw = st[wv] + g * kProjRow + 4 * m;
     const float *sr = st[wv] + m * kProjRow + 8 * g;
     const gc4 T = (gc4)(const v4f *)d.T + (int64_t)c * P * nrt * nb * 64 + lane;
-    for (int rt0 = 0; rt0 < nrt; rt0 += RT) {
-        floatx4 zr[RT], zi[RT];
+    const int rt0 = wk.w;
+    floatx4 zr[RT], zi[RT];
 #pragma unroll
-        for (int t = 0; t < RT; ++t) zr[t] = zi[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-        v4f u[4], a[2 * P];
-        auto load = [&](int jb) {
-            if (on) {
+    for (int t = 0; t < RT; ++t) zr[t] = zi[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    v4f u[4], a[2 * P];
+    auto load = [&](int jb) {
+        if (on) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) u[i] = gp.U[i][8 * jb];
+            for (int i = 0; i < 4; ++i) u[i] = gp.U[i][8 * jb];
+        }
+        // this wave's share of the fragments: row tile wv, both blocks, both planes (tiles past the last repeat it)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                a[h * P + p] = T[((int64_t)(p * nrt + min(rt0 + wv, nrt - 1)) * nb + jb + h) * 64];
+    };
+    load(0);
+    for (int jb = 0; jb < nb; jb += 2) {
+        const int buf = (jb >> 1) & 1;
+#pragma unroll
+        for (int q = 0; q < 2 * P; ++q) sa[buf][wv * 2 * P + q][lane] = a[q];
+        if (on) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) *reinterpret_cast<v4f *>(sw + 4 * i * kProjRow) = u[i];
+        }
+        __syncthreads();
+        if (jb + 2 < nb) load(jb + 2);
+        if (!on) continue;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const v4f c0 = *reinterpret_cast<const v4f *>(sr + 32 * h), c1 = *reinterpret_cast<const v4f *>(sr + 32 * h + 4);
+            const float ur[4] = {c0.x, c0.z, c1.x, c1.z}, ui[4] = {c0.y, c0.w, c1.y, c1.w};
+            v4f tr[RT], ti[RT];
+#pragma unroll
+            for (int t = 0; t < RT; ++t) {
+                tr[t] = sa[buf][t * 2 * P + h * P][lane];
+                if (HELM) ti[t] = sa[buf][t * 2 * P + h * P + P - 1][lane];
             }
-            // this wave's share of the fragments: row tile wv, both blocks, both planes (tiles past the last repeat it)
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int p = 0; p < P; ++p)
-                    a[h * P + p] = T[((int64_t)(p * nrt + min(rt0 + wv, nrt - 1)) * nb + jb + h) * 64];
-        };
-        load(0);
-        for (int jb = 0; jb < nb; jb += 2) {
-            const int buf = (jb >> 1) & 1;
-#pragma unroll
-            for (int q = 0; q < 2 * P; ++q) sa[buf][wv * 2 * P + q][lane] = a[q];
-            if (on) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) *reinterpret_cast<v4f *>(sw + 4 * i * kProjRow) = u[i];
-            }
-            __syncthreads();
-            if (jb + 2 < nb) load(jb + 2);
-            if (!on) continue;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const v4f c0 = *reinterpret_cast<const v4f *>(sr + 32 * h), c1 = *reinterpret_cast<const v4f *>(sr + 32 * h + 4);
-                const float ur[4] = {c0.x, c0.z, c1.x, c1.z}, ui[4] = {c0.y, c0.w, c1.y, c1.w};
-                v4f tr[RT], ti[RT];
+            for (int q = 0; q < 4; ++q)
 #pragma unroll
                 for (int t = 0; t < RT; ++t) {
-                    tr[t] = sa[buf][t * 2 * P + h * P][lane];
-                    if (HELM) ti[t] = sa[buf][t * 2 * P + h * P + P - 1][lane];
-                }
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-#pragma unroll
-                    for (int t = 0; t < RT; ++t) {
-                        zr[t] = mfma16(tr[t][q], ur[q], zr[t]);
-                        zi[t] = mfma16(tr[t][q], ui[q], zi[t]);
-                        if (HELM) {
-                            zr[t] = mfma16(-ti[t][q], ui[q], zr[t]);
-                            zi[t] = mfma16(ti[t][q], ur[q], zi[t]);
-                        }
+                    zr[t] = mfma16(tr[t][q], ur[q], zr[t]);
+                    zi[t] = mfma16(tr[t][q], ui[q], zi[t]);
+                    if (HELM) {
+                        zr[t] = mfma16(-ti[t][q], ui[q], zr[t]);
+                        zi[t] = mfma16(ti[t][q], ur[q], zi[t]);
                     }
-            }
-        }
-        // lane (pair m, g) holds rows 4 g .. 4 g + 3 of each tile
-        if (gp.e >= 0) {
-#pragma unroll
-            for (int t = 0; t < RT; ++t)
-                if (rt0 + t < nrt) {
-                    const gm4 Z = (gm4)(v4f *)(d.Z + (int64_t)gp.e * rp + 16 * (rt0 + t) + 4 * g);
-                    Z[0] = v4f{zr[t][0], zi[t][0], zr[t][1], zi[t][1]};
-                    Z[1] = v4f{zr[t][2], zi[t][2], zr[t][3], zi[t][3]};
                 }
         }
-        __syncthreads();                     // the next tiles' first fragments go over buffers still being read
+    }
+    // lane (pair m, g) holds rows 4 g .. 4 g + 3 of each tile
+    if (gp.e >= 0) {
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+            if (rt0 + t < nrt) {
+                const gm4 Z = (gm4)(v4f *)(d.Z + (int64_t)gp.e * rp + 16 * (rt0 + t) + 4 * g);
+                Z[0] = v4f{zr[t][0], zi[t][0], zr[t][1], zi[t][1]};
+                Z[1] = v4f{zr[t][2], zi[t][2], zr[t][3], zi[t][3]};
+            }
     }
 }
 

@@ -2712,13 +2712,15 @@ void plan_stages(Plan &P, const Tune &tu, hipStream_t st, Scratch *keep) {
                     ex.push_back(make_int4(l, i / ex_chunks, i % ex_chunks * ex_rt, 0));
                 });
             } else {
-                // up to four groups of one class per block
+                // up to four groups of one class per block, and in FP32 four row tiles
                 std::vector<int32_t> run;
                 for (int32_t g = 0; g < LV.ngrp; ++g)
                     if (run.empty() || g - run.back() == 4 || LV.h_gcls[(size_t)g] != LV.h_gcls[(size_t)run.back()]) run.push_back(g);
                 run.push_back(LV.ngrp);
-                xcd_deal((int32_t)run.size() - 1, [&](int32_t b) {
-                    mf.push_back(make_int4(l, run[(size_t)b], run[(size_t)b + 1] - run[(size_t)b], 0));
+                const int chunks = LV.fp16 ? 1 : (nrt + 3) / 4;
+                xcd_deal(((int32_t)run.size() - 1) * chunks, [&](int32_t i) {
+                    const size_t b = (size_t)(i / chunks);
+                    mf.push_back(make_int4(l, run[b], run[b + 1] - run[b], i % chunks * 4));
                 });
             }
             // target boxes with many points in ranges of whole 256-point steps, about kInterpBlocks blocks in all
