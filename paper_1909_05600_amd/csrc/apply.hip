@@ -2737,6 +2737,7 @@ k_lag_mfma(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const i
 #pragma unroll
         for (int q = 0; q < 2 * P; ++q) sa[buf][wv * 2 * P + q][lane] = a[q];
         if (on) {
+            wave_lds_fence();                // (the step before has read its sources)
 #pragma unroll
             for (int i = 0; i < 4; ++i) *reinterpret_cast<v4f *>(sw + 4 * i * kProjRow) = u[i];
         }
