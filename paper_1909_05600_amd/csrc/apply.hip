@@ -2527,7 +2527,8 @@ __device__ __forceinline__ void lag_expand_body(const LDesc &d, const int grp, c
                 s.y += p[1];
             }
             // over u~, which k_lag_project has read for the last time
-            d.ut2[(int64_t)t * d.rp + rt0 * 16 + row] = s;
+            const int64_t at = d.exp_slot ? ((int64_t)grp * CT + h) * 8 + q : t;
+            d.ut2[at * d.rp + rt0 * 16 + row] = s;
         }
     }
 }
@@ -2895,7 +2896,7 @@ __device__ __forceinline__ void lag_interp_r1(const LDesc &d, const int4 wk, flo
     const gc2 Z = gl(d.Z);
     if (d.acaA) {
         // ACA levels: k_lag_expand has summed v~
-        const gc2 V = gl(d.ut2) + (int64_t)t * rp;
+        const gc2 V = gl(d.ut2) + (int64_t)(d.exp_slot ? d.exp_slot[t] : t) * rp;
         for (int i = tid; i < r; i += blockDim.x) {
             const v2f z = V[i];
             vt[i] = make_float2(z.x, z.y);

@@ -256,6 +256,7 @@ struct LDesc {
     const int32_t *exp_ptr, *exp_cnt;      // per group: first unit, units (one per class that occurs and rank tile)
     const int32_t *exp_cls;                // unit: 32 class + 4 rank tile + steps - 1
     const int32_t *exp_e;                  // unit: each target's far pair of the class (-1: none)
+    const int32_t *exp_slot;               // row of v~ of a target box (its place in exp_tgt), or null: its own number
     const int32_t *grp_pair, *grp_cls;
     float2 *ut2, *Z;
     double two_over_dl;
@@ -360,7 +361,7 @@ struct Level {
     double aca_rank = 0.0;               // mean rank over the classes (whenever ACA was evaluated)
     int aca_kt = 0, aca_nb = 0;          // rank tiles of 16, blocks of 16 nodes (LDesc)
     DevBuf<int32_t> exp_tgt, exp_ptr, exp_cnt;   // target groups of k_lag_expand and their classes (LDesc)
-    DevBuf<int32_t> exp_cls, exp_e;
+    DevBuf<int32_t> exp_cls, exp_e, exp_slot;
     int exp_max = 0;                     // most units of a group
     std::vector<int64_t> h_far_ptr;      // Lagrange levels: far list offsets of the target boxes
     std::vector<int32_t> h_ijk;          // Lagrange levels: integer coordinates of the target boxes

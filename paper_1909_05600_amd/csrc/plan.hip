@@ -1321,8 +1321,11 @@ T *keep(Scratch &SC, const std::vector<T> &h, hipStream_t st) {
 // Target groups of k_lag_expand: the level's targets in Morton order, octant of the parent by octant (targets of one
 // octant meet the same translation classes), G to a group, and each group's list of units (k_expand_fill;
 // room for as many as the group can have: its far pairs, or all classes, times the most rank tiles).
-// Returns the groups' unit counts in pinned memory, valid once the stream has passed.
-const int32_t *expand_lists(Level &LV, int G, hipStream_t st, Scratch &SC) {
+// v~ takes the place of u~, a row per target box by its number; with more target than source boxes (`slots`) by its
+// place in the groups, for most of them may have no far pair: 2000 sources beside a million targets would otherwise
+// need a row for every box of the targets.  Returns the groups' unit counts in pinned memory, valid once the
+// stream has passed.
+const int32_t *expand_lists(Level &LV, int G, bool slots, hipStream_t st, Scratch &SC) {
     std::vector<char> on(LV.h_ijk.size() / 3, 0);
     for (int32_t t : LV.h_tgt) on[(size_t)t] = 1;
     std::vector<int32_t> by_oct[8], tgt, ptr;
@@ -1351,6 +1354,12 @@ const int32_t *expand_lists(Level &LV, int G, hipStream_t st, Scratch &SC) {
     FFM_CHECK(off < ((int64_t)1 << 31), FFM_EINTERNAL, "ffm_plan: too many target group classes");
     upload(LV.exp_tgt, tgt, st, SC);
     upload(LV.exp_ptr, ptr, st, SC);
+    if (slots) {
+        std::vector<int32_t> slot(on.size(), 0);
+        for (size_t i = 0; i < tgt.size(); ++i)
+            if (tgt[i] >= 0) slot[(size_t)tgt[i]] = (int32_t)i;
+        upload(LV.exp_slot, slot, st, SC);
+    }
     LV.exp_cnt.alloc((size_t)ng);
     LV.exp_cls.alloc((size_t)off);
     LV.exp_e.alloc((size_t)off * G);
@@ -2134,7 +2143,7 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
                     FFM_LAUNCH((helm ? k_aca_pack<true> : k_aca_pack<false>), (int)std::max(LV.acaA.n, LV.acaB.n) / kThreads,
                                kThreads, 0, st, LV.ncls, r, kt, nrt, nb, aca_cap, (float)std::ldexp(1.0, l - aca.level), aca.FA.p, aca.FB.p,
                                LV.acaKp.p, LV.acaA.p, LV.acaB.p);
-                    exp_cnt = expand_lists(LV, helm ? 16 : 8, st, SC);
+                    exp_cnt = expand_lists(LV, helm ? 16 : 8, nbx > nby, st, SC);
                 }
             }
             if (!LV.aca) {
@@ -2164,7 +2173,8 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
             FFM_HIP(hipStreamSynchronize(st));
             LV.exp_max = exp_cnt ? *std::max_element(exp_cnt, exp_cnt + LV.exp_cnt.n) : 0;
             // u~ (and, at ACA levels, v~ in its place); per far pair Z, or Y of its rank tiles
-            ws_src = std::max(ws_src, ((size_t)(LV.aca ? std::max(nbx, nby) : nby) * LV.rp + 1) / 2);
+            const size_t rows = LV.aca ? std::max<size_t>(nby, nbx > nby ? LV.exp_tgt.n : 0) : nby;
+            ws_src = std::max(ws_src, (rows * LV.rp + 1) / 2);
             ws_z = std::max(ws_z, (size_t)LV.nfar * (LV.aca ? 16 * LV.aca_kt : LV.rp));
         }
     }
@@ -3013,6 +3023,7 @@ LDesc make_desc(const Plan &P, int l, int inst, float2 *u, float2 *v, float *ama
     d.exp_cnt = LV.exp_cnt.p;
     d.exp_cls = LV.exp_cls.p;
     d.exp_e = LV.exp_e.p;
+    d.exp_slot = LV.exp_slot.p;
     d.grp_pair = LV.grp_pair.p;
     d.grp_cls = LV.grp_cls.p;
     d.ut2 = w.ut2;
@@ -3111,7 +3122,7 @@ size_t plan_device_bytes(const Plan &P) {
              L.T.bytes() + L.grp_pair.bytes() + L.grp_cls.bytes() + L.dirs.bytes() + L.dirs64.bytes() + L.D.bytes() +
              L.lnodes.bytes() + L.lden.bytes() + L.rings.bytes() + L.phis.bytes() + L.T16.bytes() + L.acaA.bytes() +
              L.acaB.bytes() + L.acaKp.bytes() + L.exp_tgt.bytes() + L.exp_ptr.bytes() + L.exp_cnt.bytes() + L.exp_cls.bytes() +
-             L.exp_e.bytes() + L.Ez.bytes() +
+             L.exp_e.bytes() + L.exp_slot.bytes() + L.Ez.bytes() +
              L.Ex.bytes() + L.Ey.bytes() + L.ExT.bytes() + L.EyT.bytes() + L.gperm.bytes() + L.gzs.bytes() + L.gxyz.bytes() +
              L.tr_tgt.bytes() + L.gslot_s.bytes() + L.gslot_t.bytes() + L.near_off.bytes() + L.sib_tgt.bytes() + L.sib_src.bytes() + L.sib_cnt.bytes() +
              L.sib_cls.bytes();
