@@ -149,18 +149,19 @@ def test_aca_units_in_pieces():
 
 @pytest.mark.parametrize("kernel", [0, 1, 3])
 def test_aca_targets_without_far_pairs(orc, kernel):
-    """Few sources in a corner of many targets: the rows of v~ that a level keeps go by the targets that have far pairs
+    """Few sources within many targets: the rows of v~ that a level keeps go by the targets that have far pairs
     (every level's u~ of the source boxes and one product per far pair bound the workspace, as without ACA), and
     every target finds its own."""
     import torch
     import paper_1909_05600_amd as ffm
     n, k = 60000, 2.0 if kernel % 2 else 0.0
     rng = np.random.default_rng(5 + kernel)
-    X = W.sphere_points(n, rng)
+    X = W.cube_points(n, rng, (0, 0, 0), 2.0)
     Y = W.cube_points(801, rng, (0.6, 0.5, 0.4), 0.15)
+    N = W.sphere_points(n, rng)
     wu = ((rng.standard_normal(801) + 1j * rng.standard_normal(801)) / 801).astype(np.complex64)
-    kw = dict(n_leaf=16, r1_override=6)
-    nrm = {"normals": torch.from_numpy(X).cuda()} if kernel == 3 else {}
+    kw = dict(n_leaf=4, r1_override=6)
+    nrm = {"normals": torch.from_numpy(N).cuda()} if kernel == 3 else {}
     gp = ffm.Plan(torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda(), kernel, k, 1e-3, aca="on", **kw, **nrm)
     st = gp.stats()
     lev = [l for l in range(1, st["leaf"] + 1) if st["aca"][l] and st["nfar"][l]]
@@ -170,8 +171,8 @@ def test_aca_targets_without_far_pairs(orc, kernel):
     full = 8 * 224 * (max(st["nbox_y"][l] for l in lev) + max(st["nfar"][l] for l in lev)) + 8 * (n + 801) + 16 * 256
     assert gp.workspace_bytes() <= full
     v = gpu_apply(gp, wu)
-    on = {"normals": X} if kernel == 3 else {}
-    vo = oracle_like(orc, gp, X, Y, kernel, k, 1e-3, n_leaf=16, r1=6, **on).apply(wu)
+    on = {"normals": N} if kernel == 3 else {}
+    vo = oracle_like(orc, gp, X, Y, kernel, k, 1e-3, n_leaf=4, r1=6, **on).apply(wu)
     print("kernel %d: workspace %.1f of %.1f MB, vs oracle %.3e" % (kernel, gp.workspace_bytes() / 1e6, full / 1e6, rel(v, vo)))
     assert rel(v, vo) < FP32_RTOL
     assert np.array_equal(v, gpu_apply(gp, wu))
