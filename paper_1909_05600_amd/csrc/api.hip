@@ -24,6 +24,13 @@ long long fail_after() {
     }();
     return v;
 }
+long long fail_above() {
+    static long long v = [] {
+        const char *e = std::getenv("FFM_TEST_FAIL_ALLOC_ABOVE");
+        return e ? std::atoll(e) : -1LL;
+    }();
+    return v;
+}
 
 }  // namespace
 
@@ -65,6 +72,8 @@ void *dev_alloc(size_t bytes) {
     const long long n = g_alloc_count.fetch_add(1);
     const long long lim = fail_after();
     if (lim >= 0 && n == lim) throw Error(FFM_ENOMEM, "device allocation refused by FFM_TEST_FAIL_ALLOC_AFTER");
+    if (fail_above() >= 0 && bytes > (size_t)fail_above())
+        throw Error(FFM_ENOMEM, "device allocation refused by FFM_TEST_FAIL_ALLOC_ABOVE");
     const size_t sz = round_size(bytes);
     std::lock_guard<std::mutex> lk(g_mx);
     auto it = g_free.find(sz);

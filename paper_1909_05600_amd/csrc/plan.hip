@@ -622,11 +622,17 @@ k_fill_groups(const int32_t *cls, int64_t n, int64_t per_reg, int ncls, const in
 // rounding (the tensor grid is symmetric) pick the same pivot on every machine.  R stays in global memory (746 KB at
 // r = 216, complex): each step reads it once and every second one writes it, and forms the next step's sum and
 // largest entry with each lane's first candidate for the pivot.  The blocks' R together stay within
-// kAcaBytes, which the last-level cache holds.  The first `cap` columns of A and B go to FA and FB, [class][cap][r].
+// kAcaBytes, which the last-level cache holds; fewer blocks at a time are slower (a plan of 5000 points with
+// two such levels 2.1 ms, 2.3 with half of it, 2.9 with a quarter) and are what a plan falls back to on a full device.
+// The first `cap` columns of A and B go to FA and FB, [class][cap][r]: aca_cols of them at first, for 316 classes and
+// r = 216, complex, 70 MB; where a class takes more (ranks are below 64 up to r = 343 unless k d is far above the
+// default limit), all are factored once more with as many columns as they take: with 64 at r = 512 a plan of three
+// such levels took 114 ms instead of 84.
 // A 50,000-point Helmholtz plan with ACA at two levels (r = 216 and 125): 70 ms of 16 host threads -> 0.95 and 0.26 ms
 // here (1.17 and 0.32 with a write in every step, 6 TB/s), bound by the traffic of R.
 constexpr size_t kAcaBytes = (size_t)256 << 20;
 constexpr int kAcaThreads = 512;
+constexpr int aca_cols(int r1) { return r1 <= 7 ? 64 : 128; }
 
 // A lane's largest value so far over the rows it walks, and the first row within a relative 2e-9 of it; unsure where a
 // later rise may have left an earlier row within that distance.
@@ -1840,8 +1846,9 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
     }
     // --- compression form and tables per level (Sec. 2.2.2, 2.2.3)
     size_t ws_src = 0, ws_tgt = 0, ws_z = 0, ws_part = 0, ws_gG = 0, ws_gH = 0;
-    struct {                               // the last level's ACA factors (k_aca)
-        int level = 0, r1 = 0;
+    struct {                               // the last level's ACA factors (k_aca), their first `cap` columns, and scratch
+        int level = 0, r1 = 0, cap = 0;
+        DevBuf<double> R;
         DevBuf<float> FA, FB;
         DevBuf<int32_t> rank;
         int32_t *rank_h = nullptr;
@@ -2089,21 +2096,41 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
             // last factored level's classes and nodes takes its factors, A times that power: the same numbers)
             const bool reuse = try_aca && !helm && P.aligned && aca.level > 0 && aca.r1 == LV.r1 &&
                                P.lev[aca.level].cls_off == LV.cls_off;
-            DevBuf<double> aca_R;
-            if (try_aca && !reuse) {
+            // factor this level's classes, keeping `cap` columns, in the last level's buffers where they are large enough.
+            // On a full device by fewer blocks at a time; the first pass (`ranks`) also without columns, whose number
+            // is then known to the second
+            auto factor = [&](int cap, bool ranks) {
                 const size_t planes = helm ? 2 : 1, per_blk = (size_t)LV.r * LV.r * planes;
-                const int nblk = (int)std::min<size_t>(LV.ncls, std::max<size_t>(1, kAcaBytes / (per_blk * sizeof(double))));
-                aca_R.alloc(nblk * per_blk);
-                aca.FA.alloc((size_t)LV.ncls * aca_cap * LV.r * planes);
-                aca.FB.alloc((size_t)LV.ncls * aca_cap * LV.r * planes);
-                aca.rank.alloc(LV.ncls);
-                aca.rank_h = SC.pin<int32_t>(LV.ncls);
+                size_t nblk = std::min<size_t>(LV.ncls, std::max<size_t>(1, kAcaBytes / (per_blk * sizeof(double))));
+                while (!aca.R.p || aca.R.n < nblk * per_blk) {
+                    try {
+                        aca.R.alloc(nblk * per_blk);
+                    } catch (const Error &e) {
+                        if (e.code != FFM_ENOMEM || nblk == 1) throw;
+                        nblk = (nblk + 1) / 2;
+                    }
+                }
+                const size_t cols = (size_t)LV.ncls * cap * LV.r * planes;
+                try {
+                    if (!aca.FA.p || aca.FA.n < cols) aca.FA.alloc(cols);
+                    if (!aca.FB.p || aca.FB.n < cols) aca.FB.alloc(cols);
+                } catch (const Error &e) {
+                    if (e.code != FFM_ENOMEM || !ranks) throw;
+                    aca.FA.release();
+                    cap = 0;
+                }
                 aca.level = l;
                 aca.r1 = LV.r1;
-                FFM_LAUNCH(aca_kernel(helm, LV.r1), nblk, kAcaThreads,
+                aca.cap = cap;
+                FFM_LAUNCH(aca_kernel(helm, LV.r1), (int)nblk, kAcaThreads,
                            (2 * planes * LV.r * aca_lag(LV.r1 <= 4 ? 1 : (LV.r1 <= 6 ? 4 : 8)) + 32) * sizeof(double), st,
-                           LV.ncls, dr0.p, dnodes.p, LV.r1, dl, P.k, P.eps / 4.0, aca_cap, aca_R.p, aca.FA.p, aca.FB.p,
+                           LV.ncls, dr0.p, dnodes.p, LV.r1, dl, P.k, P.eps / 4.0, cap, aca.R.p, aca.FA.p, aca.FB.p,
                            aca.rank.p);
+            };
+            if (try_aca && !reuse) {
+                aca.rank.alloc(LV.ncls);
+                aca.rank_h = SC.pin<int32_t>(LV.ncls);
+                factor(std::min(aca_cap, aca_cols(LV.r1)), true);
                 FFM_HIP(hipMemcpyAsync(aca.rank_h, aca.rank.p, sizeof(int32_t) * LV.ncls, hipMemcpyDeviceToHost, st));
             }
             std::vector<int32_t> hb(nbin), hc(LV.ncls, 0), gstart(nbin), gcls;
@@ -2134,6 +2161,7 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
                 LV.aca = rmax <= aca_cap && (force_aca || cost_a <= 0.75 * cost_t);
                 LV.aca_rank = LV.ncls ? rank_sum / LV.ncls : 0.0;
                 if (LV.aca) {
+                    if (rmax > aca.cap) factor(rmax, false);
                     const int r = LV.r, planes = helm ? 2 : 1, nrt = (r + 15) / 16;
                     const int kt = LV.aca_kt = (rmax + 15) / 16, nb = LV.aca_nb = LV.rp / 16;
                     LV.aca_ranks.assign(rank_h, rank_h + LV.ncls);
@@ -2141,7 +2169,8 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
                     LV.acaB.alloc((size_t)LV.ncls * planes * kt * nb * 256);
                     upload(LV.acaKp, LV.aca_ranks, st, SC);
                     FFM_LAUNCH((helm ? k_aca_pack<true> : k_aca_pack<false>), (int)std::max(LV.acaA.n, LV.acaB.n) / kThreads,
-                               kThreads, 0, st, LV.ncls, r, kt, nrt, nb, aca_cap, (float)std::ldexp(1.0, l - aca.level), aca.FA.p, aca.FB.p,
+                               kThreads, 0, st, LV.ncls, r, kt, nrt, nb, aca.cap, (float)std::ldexp(1.0, l - aca.level),
+                               aca.FA.p, aca.FB.p,
                                LV.acaKp.p, LV.acaA.p, LV.acaB.p);
                     exp_cnt = expand_lists(LV, helm ? 16 : 8, nbx > nby, st, SC);
                 }

@@ -96,3 +96,51 @@ def test_aca_in_a_batch():
     for o, r in zip(outs, refs):
         assert np.array_equal(o.cpu().numpy().astype(np.complex128), r)
     b.destroy()
+
+
+CHILD = r"""
+import sys
+import numpy as np, torch
+sys.path.insert(0, %r)
+import ffm_workloads as W
+import paper_1909_05600_amd as ffm
+rng = np.random.default_rng(11)
+X = torch.from_numpy(W.sphere_points(5000, rng)).cuda()
+wu = torch.from_numpy(((rng.standard_normal(5000) + 1j * rng.standard_normal(5000)) / 5000).astype(np.complex64)).cuda()
+# the library is loaded, with the plan's kernels and the runtime's memory for them: sets of one class, one small set
+for r1 in (5, 6):
+    ffm.Plan(X[:100] * 0.05 + 2.0, X[-100:] * 0.05, 1, 5.0, 1e-3, n_leaf=8, r1_override=r1, aca="on").apply(wu[:100])
+ffm.Plan(X[:300].contiguous(), X[:300].contiguous(), 1, 5.0, 1e-3, max_level=1).apply(wu[:300])
+torch.cuda.synchronize()
+free = torch.cuda.mem_get_info()[0]
+p = ffm.Plan(X, X, 1, 5.0, 1e-3)
+assert any(p.stats()["aca"])
+np.save(sys.argv[1], p.apply(wu).cpu().numpy())
+print("HELD", free - torch.cuda.mem_get_info()[0], int(p.plan_bytes()), flush=True)
+"""
+
+
+def test_aca_on_a_full_device(tmp_path):
+    """The factorisation's scratch gives way: a plan of 5000 points (316 classes of r = 216 and 125) builds where no
+    allocation may exceed 24 MB (the residuals by fewer blocks at a time, the factors with as many columns as the ranks
+    found), with bitwise the same product.  With all memory at hand it takes the residuals of 316 blocks (236 MB) and 64
+    columns of both factors (70 MB) for its two levels together, beside what the plan itself holds (20 MB for the lists'
+    scratch and sizes rounded up to 2 MB)."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = []
+    for limit in (None, 24 << 20):
+        env = dict(os.environ)
+        if limit:
+            env["FFM_TEST_FAIL_ALLOC_ABOVE"] = str(limit)
+        f = str(tmp_path / ("%s.npy" % limit))
+        r = subprocess.run([sys.executable, "-c", CHILD % root, f], capture_output=True, text=True, env=env, timeout=300)
+        assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-3000:]
+        held, plan = [int(x) for x in [ln for ln in r.stdout.splitlines() if ln.startswith("HELD")][0].split()[1:]]
+        print("limit %s: %.1f MB taken, plan %.1f MB" % (limit, held / 1e6, plan / 1e6))
+        out.append((np.load(f), held - plan))
+    assert np.array_equal(out[0][0], out[1][0])
+    assert out[0][1] < (236 + 70 + 20) * 1e6
+    assert out[1][1] < out[0][1]
