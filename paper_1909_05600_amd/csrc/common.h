@@ -6,6 +6,7 @@
 #include <atomic>
 #include <cstdint>
 #include <cstring>
+#include <exception>
 #include <memory>
 #include <stdexcept>
 #include <string>
@@ -148,6 +149,19 @@ struct Scratch {
         pinned.push_back(p);
         if (!h.empty()) std::memcpy(p, h.data(), h.size() * sizeof(T));
         return static_cast<const T *>(p);
+    }
+};
+
+// Waits for the stream where an exception leaves its scope: device buffers of that scope and the ones around it are
+// freed then, to be handed to the next request, and kernels launched before the exception may still use them.
+struct Drain {
+    hipStream_t stream;
+    int depth = std::uncaught_exceptions();
+    explicit Drain(hipStream_t st) : stream(st) {}
+    Drain(const Drain &) = delete;
+    Drain &operator=(const Drain &) = delete;
+    ~Drain() {
+        if (std::uncaught_exceptions() > depth) (void)hipStreamSynchronize(stream);
     }
 };
 

@@ -2081,7 +2081,8 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
             while (nreg > 1 && LV.nfar < (int64_t)160 * LV.ncls * nreg) nreg /= 2;
             const int64_t per_reg = (LV.nfar + nreg - 1) / nreg;
             const int nbin = nreg * LV.ncls;
-            DevBuf<int32_t> cnt(nbin), cursor(nbin);
+            DevBuf<int32_t> cnt(nbin), cursor(nbin), dgs;
+            const Drain drain(st);
             FFM_HIP(hipMemsetAsync(cnt.p, 0, sizeof(int32_t) * nbin, st));
             FFM_LAUNCH(k_count_cls, nblocks(LV.nfar), kThreads, 0, st, LV.far_cls.p, LV.nfar, per_reg, LV.ncls, cnt.p);
             // ACA of the transfer matrices (eq. ffmACAmatvec, relative tolerance eps / 4) where it saves MFMA work: a pair
@@ -2190,7 +2191,6 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
                 FFM_LAUNCH(kern, nblocks(lanes), kThreads, 0, st, LV.ncls, dr0.p, LV.r1, nrt, nb, dnodes.p, 0.5 * dl, P.k,
                            LV.sT, LV.fp16 ? (void *)LV.T16.p : (void *)LV.T.p);
             }
-            DevBuf<int32_t> dgs;
             upload(dgs, gstart, st, SC);
             upload(LV.grp_cls, gcls, st, SC);
             LV.h_gcls = gcls;

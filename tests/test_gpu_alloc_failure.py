@@ -70,3 +70,21 @@ def test_allocation_failure_rolls_back_and_recovers():
         assert res["equal"] and res["finite"], res
         assert res["live_end"] == 0, res
     assert failed >= 3      # the refusals at 0, 4 and 25 fall inside the first plan's build
+
+
+@pytest.mark.parametrize("n", [45, 55, 65, 75])
+def test_allocation_failure_among_the_aca_tables(n):
+    """The same with a plan of three ACA levels: refusals while its factors are made and packed on the device (the
+    factorisation itself may go on with less)."""
+    env = dict(os.environ, FFM_TEST_FAIL_ALLOC_AFTER=str(n))
+    child = (CHILD % {"root": ROOT}).replace("w = W.helmholtz_sphere(20000, seed=3, k=40.0)",
+                                             "w = W.helmholtz_sphere(9000, seed=3, k=5.0)")
+    print("child with FFM_TEST_FAIL_ALLOC_AFTER=%d" % n, flush=True)
+    r = subprocess.run([sys.executable, "-c", child], capture_output=True, text=True, env=env, timeout=300)
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-3000:]
+    res = json.loads([ln for ln in r.stdout.splitlines() if ln.startswith("RESULT ")][-1][len("RESULT "):])
+    print(n, res)
+    assert res["live0"] == 0 and res["first"] in ("ok", "enomem"), res
+    if res["first"] == "enomem":
+        assert res["live_after"] == 0, res
+    assert res["equal"] and res["finite"] and res["live_end"] == 0, res
