@@ -370,15 +370,13 @@ struct Level {
     bool fp16 = false;                   // transfer on FP16 MFMA (mixed precision)
     DevBuf<_Float16> T16;                // the same times sT in FP16 (k_lag_mfma16), mixed precision
     float sT = 1.f;                      // power-of-two scale of T16
-    // ACA factors of the transfer matrices (T is not kept): ranks, padded ranks, their maximum
+    // ACA factors of the transfer matrices (T is not kept), in whole tiles of 16 ranks
     bool aca = false;
     double aca_rank = 0.0;               // mean rank over the classes (whenever ACA was evaluated)
     int aca_kt = 0, aca_nb = 0;          // rank tiles of 16, blocks of 16 nodes (LDesc)
     DevBuf<int32_t> exp_tgt, exp_ptr, exp_cnt;   // target groups of k_lag_expand and their classes (LDesc)
     DevBuf<int32_t> exp_cls, exp_e, exp_slot;
     int exp_max = 0;                     // most units of a group
-    std::vector<int64_t> h_far_ptr;      // Lagrange levels: far list offsets of the target boxes
-    std::vector<int32_t> h_ijk;          // Lagrange levels: integer coordinates of the target boxes
     std::vector<int32_t> aca_ranks;
     DevBuf<float> acaA, acaB;
     DevBuf<int32_t> acaKp;

@@ -1324,6 +1324,20 @@ T *keep(Scratch &SC, const std::vector<T> &h, hipStream_t st) {
     return p;
 }
 
+// What the work lists of a level need on the host (box ranges, the far or near pointer array, the marks of
+// the source boxes with far work, the near pair count), copied into pinned memory in stream order, so that the
+// lists of every level are read after one synchronisation.
+struct WorkFetch {
+    int32_t *par = nullptr;              // one tree, far levels: parent of every box
+    int32_t *ijk = nullptr;              // levels that may take ACA: integer coordinates of every target box
+    int32_t *sx = nullptr, *sy = nullptr;
+    int64_t *ptr = nullptr;
+    uint8_t *act = nullptr;
+    unsigned long long *near_pairs = nullptr;
+    int64_t *sym_tot = nullptr;          // symmetric leaf near field: length of the source-side buffer
+    int nbx = 0, nby = 0;
+};
+
 // Target groups of k_lag_expand: the level's targets in Morton order, octant of the parent by octant (targets of one
 // octant meet the same translation classes), G to a group, and each group's list of units (k_expand_fill;
 // room for as many as the group can have: its far pairs, or all classes, times the most rank tiles).
@@ -1331,13 +1345,13 @@ T *keep(Scratch &SC, const std::vector<T> &h, hipStream_t st) {
 // place in the groups, for most of them may have no far pair: 2000 sources beside a million targets would otherwise
 // need a row for every box of the targets.  Returns the groups' unit counts in pinned memory, valid once the
 // stream has passed.
-const int32_t *expand_lists(Level &LV, int G, bool slots, hipStream_t st, Scratch &SC) {
-    std::vector<char> on(LV.h_ijk.size() / 3, 0);
+const int32_t *expand_lists(Level &LV, const WorkFetch &F, int G, bool slots, hipStream_t st, Scratch &SC) {
+    std::vector<char> on((size_t)F.nbx, 0);
     for (int32_t t : LV.h_tgt) on[(size_t)t] = 1;
     std::vector<int32_t> by_oct[8], tgt, ptr;
     for (size_t t = 0; t < on.size(); ++t)
         if (on[t]) {
-            const int32_t *q = &LV.h_ijk[3 * t];
+            const int32_t *q = F.ijk + 3 * t;
             by_oct[(q[0] & 1) * 4 + (q[1] & 1) * 2 + (q[2] & 1)].push_back((int32_t)t);
         }
     for (auto &v : by_oct) {
@@ -1353,7 +1367,7 @@ const int32_t *expand_lists(Level &LV, int G, bool slots, hipStream_t st, Scratc
         int64_t np = 0;
         for (int q = 0; q < G; ++q) {
             const int32_t t = tgt[(size_t)G * g + q];
-            if (t >= 0) np += LV.h_far_ptr[(size_t)t + 1] - LV.h_far_ptr[(size_t)t];
+            if (t >= 0) np += F.ptr[t + 1] - F.ptr[t];
         }
         off += std::min<int64_t>(np, LV.ncls) * LV.aca_kt;
     }
@@ -1445,20 +1459,6 @@ void build_level(Tree &T, LevelScratch &S, int l, double d0, hipStream_t st) {
 
 // Work lists of a level, built on the host from the box sizes and list pointers: largest boxes
 // first so that the longest blocks start early.
-// What the work lists of a level need on the host (box ranges, the far or near pointer array, the marks of
-// the source boxes with far work, the near pair count), copied into pinned memory in stream order, so that the
-// lists of every level are read after one synchronisation.
-struct WorkFetch {
-    int32_t *par = nullptr;              // one tree, far levels: parent of every box
-    int32_t *ijk = nullptr;              // Lagrange levels: integer coordinates of every target box
-    int32_t *sx = nullptr, *sy = nullptr;
-    int64_t *ptr = nullptr;
-    uint8_t *act = nullptr;
-    unsigned long long *near_pairs = nullptr;
-    int64_t *sym_tot = nullptr;          // symmetric leaf near field: length of the source-side buffer
-    int nbx = 0, nby = 0;
-};
-
 void fetch_work_lists(Level &LV, const TreeLevel &LX, const TreeLevel &LY, bool near, hipStream_t st, Scratch &SC,
                       WorkFetch &F, bool sym = false, bool ijk = false) {
     F.nbx = LX.nbox;
@@ -1518,10 +1518,6 @@ void fetch_work_lists(Level &LV, const TreeLevel &LX, const TreeLevel &LY, bool 
 void build_work_lists(Plan &P, Level &LV, bool near, const WorkFetch &F) {
     std::vector<int32_t> sx(F.sx, F.sx + F.nbx + 1), sy(F.sy, F.sy + F.nby + 1);
     if (F.par) LV.h_par.assign(F.par, F.par + F.nbx);
-    if (F.ijk) {
-        LV.h_ijk.assign(F.ijk, F.ijk + 3 * (size_t)F.nbx);
-        LV.h_far_ptr.assign(F.ptr, F.ptr + F.nbx + 1);
-    }
     const int64_t *ptr = F.ptr;
     const uint8_t *act = F.act;
     const unsigned long long near_pairs = F.near_pairs ? *F.near_pairs : 0ull;
@@ -1814,9 +1810,18 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
     std::vector<WorkFetch> wf(P.leaf + 1);
     WorkFetch wf_near;
     std::vector<WorkFetch> wf_early(P.leaf + 1);
+    auto gegenbauer = [&](int l) { return P.kernel == FFM_HELMHOLTZ && P.k * std::ldexp(d0, -l) >= P.opt.kd_switch; };
+    // mixed precision: FP16 transfers where the FP16 rounding (2^-11 relative, twice that for the
+    // oscillatory complex kernel) stays within eps; |T| <= 1 / (4 pi d_l) is scaled to <= 1
+    // (the double layer's anterpolated u~ carries the factor 2 / d_l of the derivative, beyond the
+    // range the FP16 scaling of the sources provides for: its transfers stay FP32)
+    const bool fp16 = P.opt.precision == FFM_PREC_MIXED && !P.dl &&
+                      std::ldexp(1.0, -11) * (P.kernel == FFM_HELMHOLTZ ? 2.0 : 1.0) <= P.eps;
+    const bool force_aca = (P.opt.flags & FFM_FLAG_ACA) != 0;
+    auto may_aca = [&](int r1) { return !fp16 && !(P.opt.flags & FFM_FLAG_NO_ACA) && (r1 >= 5 || force_aca); };
     for (int l = 1; l <= P.leaf; ++l) {
-        const bool geg = P.kernel == FFM_HELMHOLTZ && P.k * std::ldexp(d0, -l) >= P.opt.kd_switch;
-        if (P.lev[l].nfar) fetch_work_lists(P.lev[l], TX.lev[l], TY.lev[l], false, st, SC, wf[l], P.same, !geg);
+        const bool ijk = !gegenbauer(l) && may_aca(lagrange_r1(P.kernel, P.k, std::ldexp(d0, -l), P.eps, P.opt.r1_override));
+        if (P.lev[l].nfar) fetch_work_lists(P.lev[l], TX.lev[l], TY.lev[l], false, st, SC, wf[l], P.same, ijk);
         if (l < P.leaf && P.lev[l].nearly) fetch_early_lists(P.lev[l], TX.lev[l], TY.lev[l], st, SC, wf_early[l]);
     }
     // one set: the leaf near field evaluates each unordered pair of distinct boxes once (G is symmetric; the
@@ -1863,7 +1868,7 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
                 r0[3 * c + d] = (corner[0][d] - corner[1][d]) + (double)LV.cls_off[3 * c + d] * dl;
         const int32_t nby = TY.lev[l].nbox, nbx = TX.lev[l].nbox;
         plog.mark("tab.start");
-        const bool geg = P.kernel == FFM_HELMHOLTZ && P.k * dl >= P.opt.kd_switch;
+        const bool geg = gegenbauer(l);
         if (geg) {
             LV.method = kGegenbauer;
             LV.L = gegenbauer_L(P.k, dl, P.eps);
@@ -2068,12 +2073,7 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
             upload(dr0, r0, st, SC);
             const int helm = P.kernel == FFM_HELMHOLTZ ? 1 : 0;
             const int64_t per = (int64_t)LV.rp * LV.rp;
-            // mixed precision: FP16 transfers where the FP16 rounding (2^-11 relative, twice that for the
-            // oscillatory complex kernel) stays within eps; |T| <= 1 / (4 pi d_l) is scaled to <= 1
-            const double cond = helm ? 2.0 : 1.0;
-            // (the double layer's anterpolated u~ carries the factor 2 / d_l of the derivative, beyond the
-            // range the FP16 scaling of the sources provides for: its transfers stay FP32)
-            LV.fp16 = P.opt.precision == FFM_PREC_MIXED && !P.dl && std::ldexp(1.0, -11) * cond <= P.eps;
+            LV.fp16 = fp16;
             // class groups of 16 pairs for the MFMA transfer, by region and class: the blocks of one XCD then gather
             // their sources from one part of the tree, which stays in its L2, where there are pairs enough for
             // eight regions of on average 160 pairs per class (half a group per bin is left empty, 5%)
@@ -2090,8 +2090,7 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
             // rows: ranks up to aca_cap), instead of rp^2.  Not at FP16 levels (FP16 runs 16x the FP32 rate on full
             // matrices) nor below r1 = 5 (r = 64: one 32-row tile already costs as much as T).  The factorisation runs
             // while the class counts come back
-            const bool force_aca = (P.opt.flags & FFM_FLAG_ACA) != 0;
-            const bool try_aca = !LV.fp16 && !(P.opt.flags & FFM_FLAG_NO_ACA) && (LV.r1 >= 5 || force_aca);
+            const bool try_aca = may_aca(LV.r1);
             const int aca_cap = 32 * std::min(4, LV.rp / 32);
             // (Laplace levels of trees with one corner: T_c scales with 1 / d_l, a power of two, so a level with the
             // last factored level's classes and nodes takes its factors, A times that power: the same numbers)
@@ -2173,7 +2172,7 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
                                kThreads, 0, st, LV.ncls, r, kt, nrt, nb, aca.cap, (float)std::ldexp(1.0, l - aca.level),
                                aca.FA.p, aca.FB.p,
                                LV.acaKp.p, LV.acaA.p, LV.acaB.p);
-                    exp_cnt = expand_lists(LV, helm ? 16 : 8, nbx > nby, st, SC);
+                    exp_cnt = expand_lists(LV, wf[l], helm ? 16 : 8, nbx > nby, st, SC);
                 }
             }
             if (!LV.aca) {
