@@ -2085,11 +2085,16 @@ void plan_build(Plan &P, const double *X, const double *Y, hipStream_t st) {
             const Drain drain(st);
             FFM_HIP(hipMemsetAsync(cnt.p, 0, sizeof(int32_t) * nbin, st));
             FFM_LAUNCH(k_count_cls, nblocks(LV.nfar), kThreads, 0, st, LV.far_cls.p, LV.nfar, per_reg, LV.ncls, cnt.p);
-            // ACA of the transfer matrices (eq. ffmACAmatvec, relative tolerance eps / 4) where it saves MFMA work: a pair
-            // costs 2 rp kp multiply-adds, kp its class's rank in whole 32-row tiles (at most one per four waves of 32
-            // rows: ranks up to aca_cap), instead of rp^2.  Not at FP16 levels (FP16 runs 16x the FP32 rate on full
-            // matrices) nor below r1 = 5 (r = 64: one 32-row tile already costs as much as T).  The factorisation runs
-            // while the class counts come back
+            // ACA of the transfer matrices (eq. ffmACAmatvec, relative tolerance eps / 4) at FP32 levels from r1 = 5 on, where
+            // ranks in whole tiles of 32 keep 2 rp k below 3/4 of rp^2 (mean over the pairs) and no rank is above aca_cap.
+            // Transfers and interpolation, full matrices against factors: r = 216 with mean ranks of 13, 27 and 35
+            // (Laplace, eps 1e-4, 1e-6, 1e-7) 288, 286, 286 against 168, 242, 288 us for 50,000 points on a sphere, 2947,
+            // 2942, 2930 against 936, 1511, 1927 for 300,000; r = 125 with 9, 20 and 34, the last beyond the line,
+            // 133, 132, 133 against 109, 156, 200 and 1130, 1119, 1124 against 465, 782, 1117.  At r = 64 (ranks below
+            // 15) 83 against 90 and 459 against 332 us, in a cube of 100,000 points 275 against 152: factors would pay
+            // there for large sets only, and their error comes on top of that of four nodes per axis, so T is kept.  Not at
+            // FP16 levels, where the caller asks for FP16 transfers: r = 216, eps 1e-3 119 and 1181 us, against 139 and 710
+            // of FP32 factors (and 290 and 2977 of FP32 matrices).  The factorisation runs while the class counts come back
             const bool try_aca = may_aca(LV.r1);
             const int aca_cap = 32 * std::min(4, LV.rp / 32);
             // (Laplace levels of trees with one corner: T_c scales with 1 / d_l, a power of two, so a level with the
