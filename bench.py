@@ -761,14 +761,21 @@ def launch_work(name, level, st):
         return ((8.0 if st.get("_helm") else 4.0) * r * r * st["nfar"][level],
                 "mfma16" if name.startswith("k_lag_mfma16") else "mfma",
                 "flops of T u~ per far pair, r = r1^3: 8 r^2 (complex T) or 4 r^2 (real T, complex u~); MFMA")
-    if name in ("k_lag_anterp", "k_lag_interp"):
-        r = L ** 3
-        pts = st["fwd_points"][level] if name == "k_lag_anterp" else st["bwd_points"][level]
-        return (4.0 * r * pts, "alu", "4 flops per (point, Chebyshev node): a real basis value times complex u, VALU")
+    if name.startswith("k_lag_project") or name.startswith("k_lag_expand"):
+        f = 8.0 if st.get("_helm") else 4.0
+        return (f * L ** 3 * st["aca_rank"][level] * st["nfar"][level], "mfma",
+                "flops of one ACA factor per far pair, r = r1^3, k the classes' mean rank: 8 r k (complex) or 4 r k "
+                "(real factor, complex u~); FP32 MFMA")
+    if name in ("k_lag_anterp", "k_lag_anterp_ord"):
+        return (4.0 * L ** 3 * st["fwd_points"][level], "mfma",
+                "4 flops per (point, Chebyshev node): a real basis value times complex u, FP32 MFMA")
     if name == "k_lag_anterp_dl":
-        return (12.0 * L ** 3 * st["fwd_points"][level], "alu",
-                "12 flops per (point, Chebyshev node): the normal derivative of the node polynomial times complex "
-                "u, VALU")
+        return (8.0 * L ** 3 * st["fwd_points"][level], "mfma",
+                "8 flops per (point, Chebyshev node): the normal derivative of the node polynomial in two products "
+                "with complex u, FP32 MFMA")
+    if name == "k_lag_interp":
+        return (4.0 * L ** 3 * st["bwd_points"][level], "alu",
+                "4 flops per (point, Chebyshev node): a real basis value times complex v~, VALU")
     return None
 
 

@@ -38,3 +38,24 @@ def test_launch_work_models():
     assert bench.launch_work("k_grid_phit", 2, st)[0] == 8 * 9 * 11 * 32 * 32 * 10
     assert bench.launch_work("k_grid_z", 2, st)[0] == 8 * 7 * 6 * 32 ** 3
     assert bench.launch_work("k_sum_segments", 2, st) is None
+
+
+def test_lagrange_work_models():
+    """The kernels of a Lagrange level: 4 r flops per point (8 with the
+    normal derivative), and per far pair 4 r^2 with full matrices, 4 r k per factor of ACA; twice that where the
+    matrices are complex."""
+    import bench
+    st = {"order": [0, 0, 6], "nq": [0, 0, 0], "grid_nodes": [0, 0, 0], "grid_width": [0, 0, 0],
+          "fwd_boxes": [0, 0, 7], "bwd_boxes": [0, 0, 9], "fwd_points": [0, 0, 1000.0], "bwd_points": [0, 0, 900.0],
+          "method": [0, 0, 1], "near_pairs": 5e6, "nclass": [0, 0, 316], "nfar": [0, 0, 100], "aca_rank": [0, 0, 13.5]}
+    for helm in (False, True):
+        st["_helm"] = helm
+        c, t = (8, "true") if helm else (4, "false")
+        assert bench.launch_work("k_lag_mfma<%s>" % t, 2, st)[:2] == (c * 216 ** 2 * 100, "mfma")
+        assert bench.launch_work("k_lag_mfma16<%s, 7>" % t, 2, st)[:2] == (c * 216 ** 2 * 100, "mfma16")
+        assert bench.launch_work("k_lag_project<%s>" % t, 2, st)[:2] == (c * 216 * 13.5 * 100, "mfma")
+        assert bench.launch_work("k_lag_expand<%s, 4>" % t, 2, st)[:2] == (c * 216 * 13.5 * 100, "mfma")
+    assert bench.launch_work("k_lag_anterp", 2, st)[:2] == (4 * 216 * 1000, "mfma")
+    assert bench.launch_work("k_lag_anterp_ord", 2, st)[:2] == (4 * 216 * 1000, "mfma")
+    assert bench.launch_work("k_lag_anterp_dl", 2, st)[:2] == (8 * 216 * 1000, "mfma")
+    assert bench.launch_work("k_lag_interp", 2, st)[:2] == (4 * 216 * 900, "alu")
