@@ -176,3 +176,60 @@ def test_aca_targets_without_far_pairs(orc, kernel):
     print("kernel %d: workspace %.1f of %.1f MB, vs oracle %.3e" % (kernel, gp.workspace_bytes() / 1e6, full / 1e6, rel(v, vo)))
     assert rel(v, vo) < FP32_RTOL
     assert np.array_equal(v, gpu_apply(gp, wu))
+
+
+@pytest.mark.parametrize("aca,r1,precision", [("on", 6, 0), ("off", 3, 0), ("off", 3, 1)])
+def test_many_boxes(orc, aca, r1, precision):
+    """A level of 16,000 boxes and 636,000 far pairs: class groups in eight regions (160 pairs per class and region), and
+    at ACA levels expansion blocks of two waves (4096 blocks and more).  FP16 against FP32 as above (2^-10)."""
+    n = 100000
+    rng = np.random.default_rng(6)
+    X = W.sphere_points(n, rng)
+    wu = ((rng.standard_normal(n) + 1j * rng.standard_normal(n)) / n).astype(np.complex64)
+    kw = dict(n_leaf=16, r1_override=r1, aca=aca)
+    gp = gpu_plan(X, X, 0, 0.0, 1e-3, precision=precision, timing=True, **kw)
+    st = gp.stats()
+    leaf = st["leaf"]
+    assert st["nfar"][leaf] >= 8 * 160 * st["nclass"][leaf]
+    v = gpu_apply(gp, wu)
+    if aca == "on":
+        assert st["aca"][leaf]
+        assert any(r["kernel"].startswith("k_lag_expand") and r["level"] == leaf and r["blocks"] >= 4096
+                   for r in gp.launch_timing())
+    if precision:
+        assert rel(v, gpu_apply(gpu_plan(X, X, 0, 0.0, 1e-3, **kw), wu)) < 2.0 ** -10
+    else:
+        vo = oracle_like(orc, gp, X, X, 0, 0.0, 1e-3, n_leaf=16, r1=r1).apply(wu)
+        print("aca %s r1 %d: vs oracle %.3e" % (aca, r1, rel(v, vo)))
+        assert rel(v, vo) < FP32_RTOL
+    assert np.array_equal(v, gpu_apply(gp, wu))
+
+
+@pytest.mark.parametrize("r1", [2, 4, 6, 7, 8])
+def test_ordered_sums_do_not_depend_on_the_split(r1):
+    """FP16 levels sum u~ in point order, whatever the launch: boxes of a few points go to one block each, and, once the
+    boxes hold 256 on average, their row tiles to blocks of their own with waves that only stage.  Four boxes of one
+    point without weight take the same other boxes from one form to the other; the products are bitwise equal (all
+    targets are far from all sources; the largest box, which sets the scale of u~ in FP16, is there in both)."""
+    import torch
+    import paper_1909_05600_amd as ffm
+    rng = np.random.default_rng(r1)
+    oct_ = lambda n, o: 3.0 + 0.5 * np.array([o >> 2, o >> 1 & 1, o & 1]) + 0.5 * rng.random((n, 3))  # noqa: E731
+    Y = np.concatenate([[[3.0, 3.0, 3.0], [4.0, 4.0, 4.0]], oct_(100, 0), oct_(37, 3), oct_(201, 7), oct_(1500, 5)])
+    Z = np.concatenate([Y] + [oct_(1, o) for o in (1, 2, 4, 6)])
+    X = 0.1 * rng.random((300, 3))
+    wu = np.zeros(len(Z), np.complex64)
+    wu[:340] = (rng.standard_normal(340) + 1j * rng.standard_normal(340)) / 340
+    out = []
+    for S in (Z, Y):
+        gp = ffm.Plan(torch.from_numpy(X).cuda(), torch.from_numpy(S).cuda(), 0, 0.0, 1e-3, n_leaf=8, max_level=1,
+                      r1_override=r1, precision=1, timing=True)
+        st = gp.stats()
+        assert st["prec"][1] and st["nfar"][1] and not st["near_pairs"]
+        v = gpu_apply(gp, wu[:len(S)])
+        blocks = [r["blocks"] for r in gp.launch_timing() if r["kernel"] == "k_lag_anterp_ord"]
+        tiles = (r1 ** 3 + 15) // 16
+        boxes = st["fwd_boxes"][1]
+        assert blocks == [boxes if S is Z else boxes * ((tiles + 7) // 8 if tiles > 16 else (tiles + 3) // 4)], blocks
+        out.append(v)
+    assert np.linalg.norm(out[0]) > 0 and np.array_equal(out[0], out[1])
