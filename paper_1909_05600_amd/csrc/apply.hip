@@ -2419,7 +2419,9 @@ k_lag_project(const LDesc *__restrict__ descs, const IoEntry *__restrict__, cons
 // with Y_e broadcast (LDS or scalar loads in a serial chain per pair).  The complex kernel, whose A_c is twice as
 // long, takes two tiles of eight targets per group for each load of A_c, and leaves a tile out where none of its
 // targets has the class.  The waves' tiles are added in wave order in LDS.  Item (desc, target group, first row tile).
-template <bool HELM, int RT>
+// LONG: unit lists beyond kExpandUnits may occur (plan.hip asks for it by the longest list); the loop over pieces costs the
+// others 1% (two sets, Helmholtz double layer, 200,000 targets).
+template <bool HELM, int RT, bool LONG>
 __device__ __forceinline__ void lag_expand_body(const LDesc &d, const int grp, const int rt0, float *sm) {
     constexpr int CT = HELM ? 2 : 1, NP = HELM ? 2 : 1;        // column tiles of eight targets, planes of A
     const int tid = threadIdx.x, lane = tid & 63, nw = blockDim.x >> 6;
@@ -2427,7 +2429,7 @@ __device__ __forceinline__ void lag_expand_body(const LDesc &d, const int grp, c
     const int col = lane & 15, g = lane >> 4, part = col & 1;
     const int r = d.r1 * d.r1 * d.r1, nrt = (r + 15) >> 4, kt = d.aca_kt;
     const int off = __builtin_amdgcn_readfirstlane(d.exp_ptr[grp]), n = __builtin_amdgcn_readfirstlane(d.exp_cnt[grp]);
-    const int cap = min(n, kExpandUnits);                              // units staged at a time
+    const int cap = LONG ? min(n, kExpandUnits) : n;                   // units staged at a time
     int *se = reinterpret_cast<int *>(sm), *sc = se + 8 * CT * cap;    // [cap][8 CT] pairs, [cap] codes
     int q1 = 0;                                                        // end of the wave's share
     const uint32_t ustride = (uint32_t)nrt * NP * 1024;        // bytes of A per (class, rank tile)
@@ -2487,10 +2489,11 @@ __device__ __forceinline__ void lag_expand_body(const LDesc &d, const int grp, c
             }
         }
     };
-    for (int p0 = 0; p0 < n; p0 += cap) {
+    int p0 = 0;
+    do {
         // the units in LDS: addresses then depend on no load in flight
-        const int cnt = min(cap, n - p0);
-        if (p0) __syncthreads();
+        const int cnt = LONG ? min(cap, n - p0) : n;
+        if (LONG && p0) __syncthreads();
         for (int i = tid; i < 8 * CT * cnt; i += blockDim.x) se[i] = d.exp_e[(int64_t)(off + p0) * (8 * CT) + i];
         for (int i = tid; i < cnt; i += blockDim.x) sc[i] = d.exp_cls[off + p0 + i];
         __syncthreads();
@@ -2507,7 +2510,7 @@ __device__ __forceinline__ void lag_expand_body(const LDesc &d, const int grp, c
                 if (q + i < q1) products(buf[i]);
             }
         }
-    }
+    } while (LONG && (p0 += cap) < n);
     // one column tile after the other, the waves' tiles added in wave order
 #pragma unroll
     for (int h = 0; h < CT; ++h) {
@@ -2533,7 +2536,7 @@ __device__ __forceinline__ void lag_expand_body(const LDesc &d, const int grp, c
     }
 }
 
-template <bool HELM, int RT>
+template <bool HELM, int RT, bool LONG>
 __global__ void __launch_bounds__(RT == 1 ? 1024 : 512)
 k_lag_expand(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const int4 *__restrict__ work) {
     extern __shared__ float expand_sm[];      // the group's units, then [waves][RT][16][16]
@@ -2541,10 +2544,10 @@ k_lag_expand(const LDesc *__restrict__ descs, const IoEntry *__restrict__, const
     const LDesc &d = descs[wk.x];
     const int left = ((d.r1 * d.r1 * d.r1 + 15) >> 4) - wk.z;        // row tiles from this block's first on
     if (RT == 4 && left < 4) {
-        if (left > 1) lag_expand_body<HELM, 2>(d, wk.y, wk.z, expand_sm);
-        else lag_expand_body<HELM, 1>(d, wk.y, wk.z, expand_sm);
+        if (left > 1) lag_expand_body<HELM, 2, LONG>(d, wk.y, wk.z, expand_sm);
+        else lag_expand_body<HELM, 1, LONG>(d, wk.y, wk.z, expand_sm);
     } else {
-        lag_expand_body<HELM, RT>(d, wk.y, wk.z, expand_sm);
+        lag_expand_body<HELM, RT, LONG>(d, wk.y, wk.z, expand_sm);
     }
 }
 
@@ -4052,10 +4055,14 @@ KernelFn kernel_of(const Stage &S, int &threads) {
             }
         case K_ACA: return S.b ? k_lag_project<true> : k_lag_project<false>;
         case K_EXPAND:
-            // a = 100 (row tiles per wave) + waves
+            // a = 1000 (long unit lists) + 100 (row tiles per wave) + waves
             threads = 64 * std::max(1, S.a % 100);
-            if (S.a < 200) return S.b ? k_lag_expand<true, 1> : k_lag_expand<false, 1>;
-            return S.b ? k_lag_expand<true, 4> : k_lag_expand<false, 4>;
+            if (S.a >= 1000) {
+                if (S.a % 1000 < 200) return S.b ? k_lag_expand<true, 1, true> : k_lag_expand<false, 1, true>;
+                return S.b ? k_lag_expand<true, 4, true> : k_lag_expand<false, 4, true>;
+            }
+            if (S.a < 200) return S.b ? k_lag_expand<true, 1, false> : k_lag_expand<false, 1, false>;
+            return S.b ? k_lag_expand<true, 4, false> : k_lag_expand<false, 4, false>;
         case K_INTERP: threads = 64 * std::max(1, S.a); return k_lag_interp;
         // near-field kernels: a = BIG (symmetric ones BIG + 2 NRM) + 16 log2(waves per block)
         case K_NEAR:
@@ -4292,7 +4299,7 @@ std::string kernel_name(int kern, int a, int b) {
         case K_MFMA32: return "k_lag_mfma<" + tf(b) + ">";
         case K_MFMA16: return "k_lag_mfma16<" + tf(b) + ", " + std::to_string(a) + ">";
         case K_ACA: return "k_lag_project<" + tf(b) + ">";
-        case K_EXPAND: return "k_lag_expand<" + tf(b) + (a < 200 ? ", 1>" : ", 4>");
+        case K_EXPAND: return "k_lag_expand<" + tf(b) + (a % 1000 < 200 ? ", 1, " : ", 4, ") + tf(a >= 1000) + ">";
         case K_INTERP: return "k_lag_interp";
         case K_NEAR: return "k_near<" + tf(b) + ", " + tf(b && (a & 1)) + ">";
         case K_NEAR_SYM:

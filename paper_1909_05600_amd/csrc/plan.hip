@@ -2813,7 +2813,8 @@ void plan_stages(Plan &P, const Tune &tu, hipStream_t st, Scratch *keep) {
             }
             if (LV.aca) {
                 LV.stages.push_back(make_stage(K_ACA, 0, P.kernel == FFM_HELMHOLTZ, -1, l, 0, std::move(mf), st, SC));
-                LV.stages.push_back(make_stage(K_EXPAND, 100 * ex_rt + ex_nw, P.kernel == FFM_HELMHOLTZ, s2, l,
+                LV.stages.push_back(make_stage(K_EXPAND, (LV.exp_max > kExpandUnits ? 1000 : 0) + 100 * ex_rt + ex_nw,
+                                               P.kernel == FFM_HELMHOLTZ, s2, l,
                                                ex_shmem, std::move(ex), st, SC));
             }
             else
