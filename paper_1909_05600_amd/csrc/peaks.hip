@@ -148,9 +148,11 @@ int main() {
     std::printf("fma32  %8.2f TFLOP/s\n", threads * kIter * 8 * 2 / t / 1e12);
     t = timeit([&] { hipLaunchKernelGGL(k_fma64, dim3(grid), dim3(kThreads), 0, 0, od, 0.999, 1e-3); });
     std::printf("fma64  %8.2f TFLOP/s\n", threads * kIter * 8 * 2 / t / 1e12);
-    t = timeit([&] { hipLaunchKernelGGL(k_mfma32, dim3(grid / 4), dim3(kThreads), 0, 0, of, 0.999f); });
+    // four blocks per CU, all resident at once (with eight, of which seven fit, the last ones ran alone: 114 TFLOP/s)
+    const int mgrid = ncu * 4;
+    t = timeit([&] { hipLaunchKernelGGL(k_mfma32, dim3(mgrid), dim3(kThreads), 0, 0, of, 0.999f); });
     // per wave and iteration: 8 products of 16 x 16 x 4 multiply-adds
-    std::printf("mfma32 %8.2f TFLOP/s\n", (double)grid / 4 * (kThreads / 64) * kIter * 8 * 16 * 16 * 4 * 2 / t / 1e12);
+    std::printf("mfma32 %8.2f TFLOP/s\n", (double)mgrid * (kThreads / 64) * kIter * 8 * 16 * 16 * 4 * 2 / t / 1e12);
     t = timeit([&] { hipLaunchKernelGGL(k_sin, dim3(grid), dim3(kThreads), 0, 0, of); });
     const double sin_rate = threads * kIter * 8 / t;
     std::printf("sin    %8.2f G/s  (%.2f lanes/clk/CU)\n", sin_rate / 1e9, sin_rate / (ncu * prop.clockRate * 1e3));
