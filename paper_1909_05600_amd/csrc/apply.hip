@@ -2305,10 +2305,11 @@ k_lag_anterp_dl(const LDesc *__restrict__ descs, const IoEntry *__restrict__, co
 // k_lag_project forms Y_e = B_c^T u~_{s(e)} for every far pair e, by class groups; k_lag_expand forms v~_t = sum_e
 // A_c(e) Y_e by target groups, so that only the rank's worth of values per pair goes through memory (128 B per 16
 // ranks, against 1.7 KB for a transferred pair at r1 = 6), and the reductions per target need no buffer of pairs.
-// Both are bound by what the L2s deliver (10 to 14 TB/s measured: the gathered sources, and the classes' tables once
-// per group).  Sphere of 1M points, Laplace, r1 = 6, level 6 (833,000 pairs): one kernel with both products
-// through LDS and Z per pair 1570 us and its sum in the interpolation 326 -> 227 + 335 and 54 us; sphere of 300,000
-// points, Helmholtz gradient, level 6: 1644 + 3 x 278 -> 290 + 600 + 3 x 53 us; workspaces of these plans 1.6 GB ->
+// Both are bound by what the L2s deliver (11 to 14 TB/s measured: the gathered sources, and the classes' tables once
+// per group), the expansion by the memory behind them where the tables are larger (two sets, 665 complex classes: 5.9 GB of
+// A_c in 1.07 ms).  Sphere of 1M points, Laplace, r1 = 6, level 6 (833,000 pairs): one kernel with both products
+// through LDS and Z per pair 1570 us and its sum in the interpolation 326 -> 228 + 342 and 52 us; sphere of 300,000
+// points, Helmholtz gradient, level 6: 1644 + 3 x 278 -> 294 + 602 + 3 x 50 us; workspaces of these plans 1.6 GB ->
 // 0.3 and 0.46 GB.  Rank 4 u + g of a tile of 16 sits at position 4 g + u:
 // a lane of k_lag_expand reads the positions of its g as one 16-byte load and uses them in steps u, so steps
 // beyond the rank are left out.
@@ -3037,9 +3038,9 @@ k_lag_interp_dn(const LDesc *__restrict__ descs, const IoEntry *__restrict__, co
 // are too few to fill the chip, of two (in the symmetric pass of one set up to eight), which share the box's source
 // chunks (plan.hip, near_waves).  A chunk
 // whose list entry, range and points were fetched one after the other cost three memory latencies, more than its
-// evaluation: with the list in LDS and the next chunk's points loaded ahead, and the waves, 26 -> 14 us for 4096 points
-// (Laplace, 260 boxes), 150 -> 55 for 50,000 (1295 boxes), 237 -> 171 for 262,000 (4636), 536 -> 469 for 1M (18,354,
-// one wave each), 4.4 -> 3.1 ms for 10M (Helmholtz, symmetric pass).  Source points
+// evaluation: with the list in LDS and the next chunk's points loaded ahead, and the waves, 23 -> 8.5 us for 4096 points
+// (Laplace, 260 boxes), 236 -> 168 for 262,000 (4636), 525 -> 478 for 1M (18,354, one wave each), 4.4 -> 3.0 ms for 10M
+// (Helmholtz, symmetric pass; times by rocprofv3).  Source points
 // are staged through LDS in chunks of 64, in FP64 relative to the target centre, and every pair's difference is
 // formed in FP64 and rounded once to FP32, so close pairs keep the full FP32 relative accuracy of r.  Helmholtz
 // coordinates are scaled by k / 2 pi when staged (r then reads in revolutions, the phase of e^{ikr}), and the

@@ -55,7 +55,7 @@ __global__ void __launch_bounds__(kThreads) k_mfma32(float *out, float b) {
     floatx4 acc[8];
     for (int i = 0; i < 8; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
     const float a = threadIdx.x * 1e-3f;
-    for (int it = 0; it < kIter; ++it)
+    for (int it = 0; it < 4 * kIter; ++it)
 #pragma unroll
         for (int i = 0; i < 8; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc[i], 0, 0, 0);
     float s = 0.f;
@@ -152,7 +152,7 @@ int main() {
     const int mgrid = ncu * 4;
     t = timeit([&] { hipLaunchKernelGGL(k_mfma32, dim3(mgrid), dim3(kThreads), 0, 0, of, 0.999f); });
     // per wave and iteration: 8 products of 16 x 16 x 4 multiply-adds
-    std::printf("mfma32 %8.2f TFLOP/s\n", (double)mgrid * (kThreads / 64) * kIter * 8 * 16 * 16 * 4 * 2 / t / 1e12);
+    std::printf("mfma32 %8.2f TFLOP/s\n", (double)mgrid * (kThreads / 64) * 4 * kIter * 8 * 16 * 16 * 4 * 2 / t / 1e12);
     t = timeit([&] { hipLaunchKernelGGL(k_sin, dim3(grid), dim3(kThreads), 0, 0, of); });
     const double sin_rate = threads * kIter * 8 / t;
     std::printf("sin    %8.2f G/s  (%.2f lanes/clk/CU)\n", sin_rate / 1e9, sin_rate / (ncu * prop.clockRate * 1e3));
